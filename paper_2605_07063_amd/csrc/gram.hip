@@ -54,7 +54,7 @@
 #include <mutex>
 #include <type_traits>
 
-#include "common.h"
+#include "tile256.h"
 
 namespace dr {
 namespace {
@@ -561,10 +561,10 @@ __global__ __launch_bounds__(kThreads) void gram_small_reduce_kernel(GramArgs a,
 
 // ---------------------------------------------------------------- large n
 
-constexpr int kBT = 256;                   // output tile edge
-constexpr int kBK = 64;                    // bf16 columns per step (128-byte rows)
-constexpr int kBPanel = kBT * kBK * 2;     // bytes of one operand panel per step (32 KiB)
-constexpr int kBStage = 2 * kBPanel;       // A and B panels
+constexpr int kBT = kTileRows;             // output tile edge
+constexpr int kBK = kTileStepCols;         // bf16 columns per step (128-byte rows)
+constexpr int kBPanel = kTilePanel;        // bytes of one operand panel per step (32 KiB)
+constexpr int kBStage = kTileStage;        // A and B panels
 constexpr int kBigMinTiles = 512;
 
 struct BigArgs {
@@ -617,7 +617,7 @@ __device__ __forceinline__ void big_store_block_masked(float* Kp, int n, bool di
 }
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gram_big_kernel(BigArgs a) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * kBStage];
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[kTileRing];
   const int p = blockIdx.y;
   // Workgroup i runs on XCD i % 8, and an XCD's 32 CUs take its workgroups
   // in order.  The lower-triangle tiles are grouped in chunks of 4 tile rows
@@ -684,62 +684,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     if (q & 1) fb[q >> 1] = swz_read(sa + kBPanel + (wc * 8 + (q >> 1)) * 2048, lr, seg);
     else fa[q >> 1] = swz_read(sa + (wr * 8 + (q >> 1)) * 2048, lr, seg);
   };
-  // The 128 x 128 accumulator (256 registers) sits in the AGPRs: each product
-  // is an in-place asm MFMA on its accumulator, so the register allocator
-  // keeps every accumulator where it is (the compiler's own MFMA form moves
-  // them between register files at this size).  Volatile asm also keeps the
-  // written order: each fragment read and DMA issue sits between MFMAs.
   f32x4 acc[8][8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-      // the zeros are in place before the prologue below: the compiler does
-      // not see the MFMAs inside the asm, so it would not space a register
-      // write and the product that reads it apart
-      asm volatile("" : "+a"(acc[i][j]));
-    }
-  auto mma = [&](int i, int j, const u32x4* fa, const u32x4* fb) {
-    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(fa[i]), "v"(fb[j]));
-  };
-  u32x4 fa0[8], fb0[8], fa1[8], fb1[8];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) dma1(0, 0, q);
-  DR_WAIT_VM(0);
-  DR_LDS_SYNC();
-#pragma unroll
-  for (int q = 0; q < 16; ++q) dma1(1, 1, q);
-#pragma unroll
-  for (int q = 0; q < 16; ++q) rd1(fa0, fb0, lds, 0, q);
-  // Per 64-column step t (stage t & 1): the first half's products with the
-  // second half's fragment reads between them; one barrier (step t + 1
-  // landed everywhere, every wave done with stage t & 1); then the second
-  // half's products with the DMA of step t + 2 into stage t & 1 and the reads
-  // of step t + 1's first half between them.  Products accumulate in the
-  // same order as a plain loop over 32-column halves.
-  for (int t = 0; t < nk; ++t) {
-    const unsigned char* sa = lds + (t & 1) * kBStage;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      rd1(fa1, fb1, sa, 1, q);
-#pragma unroll
-      for (int m = 4 * q; m < 4 * q + 4; ++m) mma(m & 7, m >> 3, fa0, fb0);
-    }
-    DR_WAIT_VM(0);
-    DR_LDS_SYNC();
-    const unsigned char* sn = lds + ((t + 1) & 1) * kBStage;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      dma1(t + 2, t & 1, q);
-      rd1(fa0, fb0, sn, 0, q);
-#pragma unroll
-      for (int m = 4 * q; m < 4 * q + 4; ++m) mma(m & 7, m >> 3, fa1, fb1);
-    }
-  }
-  // the last products' results are read below: wait states after an MFMA
-  // that the compiler does not see inside the asm
-  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+  tile256_clear(acc);
+  tile256_loop(lds, nk, dma1, rd1, acc);
 
   float* Kp = a.K + (long long)p * a.n * a.n;
   if (a.vec4 && !diag && rowA0 + kBT <= a.n) {

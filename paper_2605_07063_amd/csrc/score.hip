@@ -13,15 +13,19 @@
 // update-assembly kernel); PIP multiplies by it in bf16 as a hi + lo pair
 // (two MFMAs, relative rounding ~2^-17 instead of bf16's 2^-9).
 //
-// pip_kernel / gip_kernel: 128 x 128 output tiles per workgroup, 4 waves of
-// 64 x 64, operands are row panels whose reduction index is contiguous in
-// memory (token rows of x / dy, rows of gbar*), staged by buffer->LDS DMA
-// in 64-wide steps through a 2-stage ring in the swizzled 128-byte-row
-// layout of the Gram kernel.  Rows past a length and columns past a width
-// load as zeros (out-of-range buffer offsets), so padding is never read.
+// Both kernels work on the valid tokens of all examples packed one after
+// another (packed position p = cum[i] + t), so a tile is full whatever the
+// length mix, and sum its rows per example at the end: a row of the product
+// belongs to one token.  Operands are row panels whose reduction index is
+// contiguous in memory (token rows of x / dy, rows of gbar*), staged by
+// buffer->LDS DMA in 64-wide steps in the swizzled 128-byte-row layout.
+// Rows past the last token and columns past a width load as zeros
+// (out-of-range buffer offsets), so padding is never read.  A tile whose rows
+// could lie further apart than a 32-bit offset takes rows of one example
+// only (`packed` = 0: rows t0 .. of example i, blocks of 256 or 128).
 // Partial sums go to fp64 workspace slots and are reduced in a fixed order.
 
-#include "common.h"
+#include "tile256.h"
 
 namespace dr {
 namespace {
@@ -43,18 +47,6 @@ struct PanelRows {
   int seg[4];
 };
 
-__device__ __forceinline__ PanelRows panel_rows(int w, int lane, int rows_valid, long long row_bytes) {
-  PanelRows p;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int hb = w + 4 * u;
-    const int r = 8 * hb + (lane >> 3);
-    p.seg[u] = swz_seg_of_lane(lane, hb & 1);
-    p.off[u] = r < rows_valid ? (unsigned)((long long)r * row_bytes) : kOobOffset;
-  }
-  return p;
-}
-
 __device__ __forceinline__ void issue_panel(__amdgpu_buffer_rsrc_t rs, const PanelRows& pr, unsigned char* dst, int w,
                                             int k0, int K) {
 #pragma unroll
@@ -65,13 +57,11 @@ __device__ __forceinline__ void issue_panel(__amdgpu_buffer_rsrc_t rs, const Pan
   }
 }
 
-// acc[i][j] += A[64 wr + 16 i + .][k] B[64 wc + 16 j + .][k] over k < K for
-// NB B panels (summed), A and B given as row panels
-template <int NB>
+// acc[i][j] += A[64 wr + 16 i + .][k] B[64 wc + 16 j + .][k] over k < K, A
+// and B given as row panels
 __device__ __forceinline__ void panel_gemm(unsigned char* lds, __amdgpu_buffer_rsrc_t ra, const PanelRows& pa,
-                                           const __amdgpu_buffer_rsrc_t* rb, const PanelRows& pb, int K,
-                                           f32x4 (&acc)[4][4]) {
-  constexpr int kStage = (1 + NB) * kSPanel;
+                                           __amdgpu_buffer_rsrc_t rb, const PanelRows& pb, int K, f32x4 (&acc)[4][4]) {
+  constexpr int kStage = 2 * kSPanel;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = w >> 1, wc = w & 1, lr = lane & 15, lg = lane >> 4;
@@ -79,8 +69,7 @@ __device__ __forceinline__ void panel_gemm(unsigned char* lds, __amdgpu_buffer_r
   auto issue = [&](int t, int st) {
     unsigned char* sb = lds + st * kStage;
     issue_panel(ra, pa, sb, w, t * kSK, K);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) issue_panel(rb[b], pb, sb + (1 + b) * kSPanel, w, t * kSK, K);
+    issue_panel(rb, pb, sb + kSPanel, w, t * kSK, K);
   };
   issue(0, 0);
   for (int t = 0; t < nk; ++t) {
@@ -91,98 +80,325 @@ __device__ __forceinline__ void panel_gemm(unsigned char* lds, __amdgpu_buffer_r
 #pragma unroll
     for (int kh = 0; kh < 2; ++kh) {
       const int seg = 4 * kh + lg;
-      u32x4 fa[4], fb[NB][4];
+      u32x4 fa[4], fb[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) fa[i] = swz_read(sa + (4 * wr + i) * 2048, lr, seg);
 #pragma unroll
-      for (int b = 0; b < NB; ++b)
+      for (int j = 0; j < 4; ++j) fb[j] = swz_read(sa + kSPanel + (4 * wc + j) * 2048, lr, seg);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) fb[b][j] = swz_read(sa + (1 + b) * kSPanel + (4 * wc + j) * 2048, lr, seg);
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] = mma_bf16(fa[i], fb[b][j], acc[i][j]);
+        for (int j = 0; j < 4; ++j) acc[i][j] = mma_bf16(fa[i], fb[j], acc[i][j]);
     }
   }
   DR_LDS_SYNC();   // the ring is free for the next use
 }
 
-__device__ double block_sum_256(double v, double* red) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double t = 0.0;
-  for (int q = 0; q < kSThreads / 64; ++q) t += red[q];
-  return t;
-}
+constexpr int kMaxScoreLayers = 16;
 
 struct ScoreLayer {
   const unsigned char* x;
   const unsigned char* dy;
   long long ldx, lddy;       // elements per token
   long long exx, exdy;       // bytes per example
-  int d_in, d_out, T, n, m;
-  const int* len;            // [n + m] or null
+  const unsigned char* ghi;  // PIP: gbar* as bf16 hi + lo, [d_out][d_in]
+  const unsigned char* glo;
+  double* part;              // partial sums of this layer
+  int d_in, d_out;
+  int OB;                    // PIP: 256-column blocks of d_out
 };
+
+struct ScoreArgs {
+  ScoreLayer L[kMaxScoreLayers];
+  int num_layers;
+  int T, n, m;
+  int packed;                // rows of a tile: packed positions, or one example's tokens
+  int SB;                    // GIP: 128-row blocks of the target tokens (upper bound)
+  const int* len;            // [n + m] or null
+  const int* cum;            // [n + 1] token prefix of the general examples, then [m + 1] of the targets
+};
+
+// exclusive prefixes of the clamped lengths: block 0 the n general examples,
+// block 1 the m targets
+__global__ __launch_bounds__(1024) void score_plan_kernel(const int* len, int n, int m, int T, int* cum) {
+  __shared__ int wsum[17];
+  const int first = blockIdx.x ? n : 0, cnt = blockIdx.x ? m : n;
+  int* out = cum + (blockIdx.x ? n + 1 : 0);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int per = (cnt + 1023) / 1024;
+  const int i0 = tid * per < cnt ? tid * per : cnt, i1 = i0 + per < cnt ? i0 + per : cnt;
+  int loc = 0;
+  for (int i = i0; i < i1; ++i) loc += clamp_len(len, first + i, T);
+  int inc = loc;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int v = __shfl_up(inc, off, 64);
+    if (lane >= off) inc += v;
+  }
+  if (lane == 63) wsum[wave] = inc;
+  __syncthreads();
+  if (tid == 0) {
+    int run = 0;
+    for (int w = 0; w < 16; ++w) {
+      const int v = wsum[w];
+      wsum[w] = run;
+      run += v;
+    }
+    wsum[16] = run;
+  }
+  __syncthreads();
+  int base = wsum[wave] + inc - loc;
+  for (int i = i0; i < i1; ++i) {
+    out[i] = base;
+    base += clamp_len(len, first + i, T);
+  }
+  if (tid == 0) out[cnt] = wsum[16];
+}
+
+// Rows of a tile of ROWS rows: example (relative to e0) and token of each, in LDS.
+template <int ROWS>
+struct TileRows {
+  int cum[ROWS + 1];   // cum[e0 + r] - p0
+  int rel[ROWS];       // -1 past the last row
+  int tok[ROWS];
+};
+
+// Fills the table for row block rt of `cnt` examples with prefix `cum` (a
+// whole 256-thread workgroup; ends with a barrier) and returns the number of
+// valid rows; e0: the example of the first row, e_last: of the last.
+template <int ROWS>
+__device__ __forceinline__ int tile_rows(TileRows<ROWS>& tr, const int* cum, const int* len, int first, int cnt, int T,
+                                         int packed, int rt, int& e0, int& e_last) {
+  const int tid = threadIdx.x;
+  if (!packed) {
+    const int TB = (T + ROWS - 1) / ROWS;
+    e0 = e_last = rt / TB;
+    const int t0 = (rt - e0 * TB) * ROWS, L = clamp_len(len, first + e0, T);
+    for (int r = tid; r < ROWS; r += 256) {
+      tr.rel[r] = t0 + r < L ? 0 : -1;
+      tr.tok[r] = t0 + r;
+    }
+    if (tid == 0) {
+      tr.cum[0] = 0;
+      tr.cum[1] = L - t0;
+    }
+    __syncthreads();
+    return L - t0 < ROWS ? L - t0 : ROWS;
+  }
+  const int total = cum[cnt], p0 = rt * ROWS;
+  const int rows = total - p0 < ROWS ? total - p0 : ROWS;
+  int lo = 0, hi = cnt;   // the last example with cum <= p0 (not empty, since p0 < total)
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (cum[mid] <= p0) lo = mid;
+    else hi = mid - 1;
+  }
+  e0 = lo;
+  // at most ROWS non-empty examples; runs of empty ones can only push an
+  // example past the staged prefix, which is then read from memory
+  for (int r = tid; r <= ROWS; r += 256) tr.cum[r] = e0 + r <= cnt ? cum[e0 + r] - p0 : 0x7fffffff;
+  __syncthreads();
+  for (int r = tid; r < ROWS; r += 256) {
+    int e = 0, t = 0;
+    if (r < rows) {
+      while ((e + 1 <= ROWS ? tr.cum[e + 1] : cum[e0 + e + 1] - p0) <= r) ++e;
+      t = r - (e <= ROWS ? tr.cum[e] : cum[e0 + e] - p0);
+    }
+    tr.rel[r] = r < rows ? e : -1;
+    tr.tok[r] = t;
+  }
+  __syncthreads();
+  e_last = e0 + tr.rel[rows - 1];
+  return rows;
+}
+
+// row sums of a tile (rs[h][row], two column halves) -> one partial per
+// example of the tile, in slot (row block + example) of a column block: the
+// pairs (row block, example) in order step at least one of the two, so the
+// slots are distinct (row block alone when it holds rows of one example)
+template <int ROWS>
+__device__ __forceinline__ void tile_example_sums(const TileRows<ROWS>& tr, const double (*rs)[ROWS], const int* cum,
+                                                  int rows, int packed, int rt, int e0, int e_last, double* part,
+                                                  int stride, int col) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int p0 = rt * ROWS;
+  for (int e = e0 + w; e <= e_last; e += 4) {
+    const int r = e - e0;
+    int lo = r <= ROWS ? tr.cum[r] : cum[e] - p0, hi = r + 1 <= ROWS ? tr.cum[r + 1] : cum[e + 1] - p0;
+    lo = lo > 0 ? lo : 0;
+    hi = hi < rows ? hi : rows;
+    if (lo >= hi) continue;   // an empty example
+    double v = 0.0;
+    for (int k = lo + lane; k < hi; k += 64) v += rs[0][k] + rs[1][k];
+    v = wave_sum_l63(v);
+    if (lane == 63) part[(long long)(packed ? rt + e : rt) * stride + col] = v;
+  }
+}
 
 // ---------------------------------------------------------------- PIP
 
-// workgroup (i, token block tb, output block ob):
-// part[(i TB + tb) OB + ob] = sum_{t in block, t < len_i} sum_{o in block} dy_{i,t,o} (gbar* x_{i,t})_o
-__global__ __launch_bounds__(kSThreads) void pip_kernel(ScoreLayer a, const unsigned char* ghi,
-                                                        const unsigned char* glo, int TB, int OB, double* part) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * 3 * kSPanel];
-  __shared__ double red[kSThreads / 64];
-  const int i = blockIdx.x / TB, tb = blockIdx.x % TB, ob = blockIdx.y;
-  const int L = clamp_len(a.len, i, a.T);
-  const int t0 = tb * kST, o0 = ob * kST;
-  if (t0 >= L) return;
+// row block rt of 256 tokens x column block ob of 256 outputs of one layer:
+// the products of the tokens with gbar* (2 d_in columns: hi and lo of each
+// 64-column step in turn), dotted with the dy rows.  Bound by the MFMA rate:
+// 2.3 ms for the small block's 2.75 TFLOP (64 examples of 128..512 tokens,
+// eight 2048 x 2048 layers), 1.2 PFLOP/s.  128 x 128 tiles of one example
+// with both parts of gbar* staged (one workgroup of 96 KB per CU, its DMA
+// waited for at every fragment read) took 0.92 ms per layer.  Whole call
+// 8.03 -> 2.55 ms.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void pip_kernel(ScoreArgs a) {
+  // one LDS object: beside a second one the compiler makes every fragment
+  // read wait for all DMA in flight (7.9 instead of 1.9 ms on the small block)
+  __shared__ __attribute__((aligned(1024))) unsigned char
+      lds[kTileRing + 2 * kTileRows * sizeof(double) + sizeof(TileRows<kTileRows>)];
+  double (*rs)[kTileRows] = reinterpret_cast<double (*)[kTileRows]>(lds + kTileRing);
+  TileRows<kTileRows>& tr = *reinterpret_cast<TileRows<kTileRows>*>(lds + kTileRing + 2 * kTileRows * sizeof(double));
+  const int R = a.packed ? (a.cum[a.n] + kTileRows - 1) / kTileRows : a.n * ((a.T + kTileRows - 1) / kTileRows);
+  // Workgroup b runs on XCD b % 8; each XCD takes runs of 32 tiles: eight
+  // column blocks of four row blocks, whose panels its L2 then holds.
+  const int x = blockIdx.x & 7, sl = blockIdx.x >> 3;
+  long long q = ((long long)(sl >> 5) * 8 + x) * 32 + (sl & 31);
+  int li = 0;
+  while (li < a.num_layers && q >= (long long)R * a.L[li].OB) {
+    q -= (long long)R * a.L[li].OB;
+    ++li;
+  }
+  if (li == a.num_layers) return;
+  const ScoreLayer& L = a.L[li];
+  const int band = (int)(q / ((long long)R * 8));
+  const int wb = L.OB - 8 * band < 8 ? L.OB - 8 * band : 8;
+  const int qb = (int)(q - (long long)band * R * 8);
+  const int rt = qb / wb, ob = 8 * band + qb % wb;
+  if (!a.packed) {
+    const int TB = (a.T + kTileRows - 1) / kTileRows, i = rt / TB;
+    if ((rt - i * TB) * kTileRows >= clamp_len(a.len, i, a.T)) return;
+  }
+  int e0, e_last;
+  const int rows = tile_rows(tr, a.cum, a.len, 0, a.n, a.T, a.packed, rt, e0, e_last);
+  const int o0 = ob * kTileRows;
+  const int d_in = L.d_in, d_out = L.d_out;
+
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wr = w >> 1, wc = w & 1, lc = lane & 15, g = lane >> 4;
-  const unsigned char* xb = a.x + (long long)i * a.exx + (long long)t0 * a.ldx * 2;
-  const __amdgpu_buffer_rsrc_t ra = make_rsrc(xb, kOobOffset);
-  __amdgpu_buffer_rsrc_t rb[2] = {make_rsrc(ghi + (long long)o0 * a.d_in * 2, kOobOffset),
-                                  make_rsrc(glo + (long long)o0 * a.d_in * 2, kOobOffset)};
-  const PanelRows pa = panel_rows(w, lane, L - t0, a.ldx * 2);
-  const PanelRows pb = panel_rows(w, lane, a.d_out - o0, (long long)a.d_in * 2);
-  f32x4 acc[4][4];
+  const int wr = w >> 1, wc = w & 1;   // 128-token half, 128-output half
+  const int lr = lane & 15, lg = lane >> 4;
+  const __amdgpu_buffer_rsrc_t ra = make_rsrc(L.x + (long long)e0 * L.exx, kOobOffset);
+  const __amdgpu_buffer_rsrc_t rh = make_rsrc(L.ghi + (long long)o0 * d_in * 2, kOobOffset);
+  const __amdgpu_buffer_rsrc_t rl = make_rsrc(L.glo + (long long)o0 * d_in * 2, kOobOffset);
+  unsigned offA[8], offB[8];
+  int segs[8];
 #pragma unroll
-  for (int p = 0; p < 4; ++p)
+  for (int u = 0; u < 8; ++u) {
+    const int hb = w + 4 * u;             // half block: rows 8 hb .. 8 hb + 7
+    const int r = 8 * hb + (lane >> 3);
+    segs[u] = 8 * swz_seg_of_lane(lane, hb & 1);
+    const int rel = tr.rel[r];
+    offA[u] = rel >= 0 ? (unsigned)(rel * L.exx + tr.tok[r] * L.ldx * 2) : kOobOffset;
+    offB[u] = o0 + r < d_out ? (unsigned)((long long)r * d_in * 2) : kOobOffset;
+  }
+  auto dma1 = [&](int t, int st, int q) {
+    unsigned char* sb = lds + st * kTileStage;
+    const int u = q >> 1;
+    const int col = (t >> 1) * kTileStepCols + segs[u];
+    const bool cok = col < d_in;
+    if (q & 1) {
+      const unsigned cb = (offB[u] == kOobOffset || !cok) ? kOobOffset : offB[u] + (unsigned)(col * 2);
+      dma16<kAuxCached>(t & 1 ? rl : rh, sb + kTilePanel + (w + 4 * u) * 1024, cb);
+    } else {
+      const unsigned ca = (offA[u] == kOobOffset || !cok) ? kOobOffset : offA[u] + (unsigned)(col * 2);
+      dma16<kAuxCached>(ra, sb + (w + 4 * u) * 1024, ca);
+    }
+  };
+  auto rd1 = [&](u32x4* fa, u32x4* fb, const unsigned char* sa, int kh, int q) {
+    const int seg = 4 * kh + lg;
+    if (q & 1) fb[q >> 1] = swz_read(sa + kTilePanel + (wc * 8 + (q >> 1)) * 2048, lr, seg);
+    else fa[q >> 1] = swz_read(sa + (wr * 8 + (q >> 1)) * 2048, lr, seg);
+  };
+  f32x4 acc[8][8];
+  tile256_clear(acc);
+  tile256_loop(lds, 2 * ((d_in + kTileStepCols - 1) / kTileStepCols), dma1, rd1, acc);
+  // Dot with the dy rows of the tile: the whole tile (256 rows x 512 bytes)
+  // goes into the ring by DMA, in the slot order of slot_xor, and the
+  // transposing LDS read gives each lane its column of the four rows that one
+  // accumulator register quad holds (2-byte loads from memory in that layout
+  // took 0.75 ms of 3.2 on the small block).
+  DR_WAIT_VM(0);
+  DR_LDS_SYNC();   // every wave is done with the ring
+  const __amdgpu_buffer_rsrc_t rd = make_rsrc(L.dy + (long long)e0 * L.exdy + o0 * 2LL, kOobOffset);
+#pragma unroll 8
+  for (int h = 0; h < 32; ++h) {
+    const int blk = w + 4 * h, r = 2 * blk + (lane >> 5), u = lane & 31;
+    const int col = 16 * ((u >> 1) ^ slot_xor(r)) + 8 * (u & 1);
+    const int rel = tr.rel[r];
+    dma16<kAuxCached>(rd, lds + blk * 1024,
+                      rel >= 0 && o0 + col < d_out
+                          ? (unsigned)(rel * L.exdy + tr.tok[r] * L.lddy * 2 + col * 2) : kOobOffset);
+  }
+  DR_WAIT_VM(0);
+  DR_LDS_SYNC();
+  const int dq = (lane >> 2) & 3, dr = lane & 3;
+  const bool full = o0 + kTileRows <= d_out;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) acc[p][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  panel_gemm<2>(lds, ra, pa, rb, pb, a.d_in, acc);
-  // dot with the dy rows of the block (valid tokens and outputs only)
-  const __bf16* dyb = reinterpret_cast<const __bf16*>(a.dy + (long long)i * a.exdy);
-  float d = 0.f;
+  for (int p = 0; p < 8; ++p) {
+    const int rrow = wr * 128 + 16 * p + 4 * lg + dq;   // the row this lane addresses
+    float d[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int p = 0; p < 4; ++p)
+    for (int j = 0; j < 8; ++j) {
+      const v4s v = lds_read_tr16(lds + rrow * 512 + (((wc * 8 + j) ^ slot_xor(rrow)) * 32) + dr * 8);
+      const bool ok = full || o0 + wc * 128 + 16 * j + lr < d_out;   // else zeros against any product
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        d[r] = ok ? fmaf(acc[p][j][r], __uint_as_float((unsigned)(unsigned short)v[r] << 16), d[r]) : d[r];
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int t = t0 + 64 * wr + 16 * p + 4 * g + r;
-      if (t >= L) continue;
-      const __bf16* row = dyb + (long long)t * a.lddy;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int o = o0 + 64 * wc + 16 * q + lc;
-        if (o < a.d_out) d = fmaf(acc[p][q][r], (float)row[o], d);
-      }
+      double s = (double)d[r];
+      s += dpp_d<0xB1, 0xF>(s);
+      s += dpp_d<0x4E, 0xF>(s);
+      s += dpp_d<0x141, 0xF>(s);
+      s += dpp_d<0x140, 0xF>(s);
+      if (lr == 0) rs[wc][wr * 128 + 16 * p + 4 * lg + r] = s;
     }
-  const double tot = block_sum_256((double)d, red);
-  if (tid == 0) part[((long long)i * TB + tb) * OB + ob] = tot;
+  }
+  __syncthreads();
+  tile_example_sums(tr, rs, a.cum, rows, a.packed, rt, e0, e_last, L.part, L.OB, ob);
 }
 
-__global__ void pip_reduce_kernel(const double* part, int n, int T, const int* len, int TB, int OB, float* s) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int L = clamp_len(len, i, T);
-  const int nb = (L + kST - 1) / kST;
+// s[l][i] = scale * the sum of the example's partials over its row blocks
+// (in order) and the nc column blocks of each, one wave per (layer, example);
+// OBS: the layer's own column count
+template <int ROWS, bool OBS>
+__global__ __launch_bounds__(256) void score_reduce_kernel(ScoreArgs a, float* s, double scale) {
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6), l = blockIdx.y, lane = threadIdx.x & 63;
+  if (i >= a.n) return;
+  const int len = clamp_len(a.len, i, a.T);
+  int stride, nc;   // columns of a slot, and those written
+  if (OBS) {
+    stride = nc = a.L[l].OB;
+  } else {
+    stride = a.SB;
+    nc = a.SB;
+    if (a.packed) nc = (a.cum[a.n + 1 + a.m] + ROWS - 1) / ROWS;
+  }
+  const int TB = (a.T + ROWS - 1) / ROWS;
+  int b0, nb;   // first slot, and how many
+  if (a.packed) {
+    b0 = a.cum[i] / ROWS + i;
+    nb = len > 0 ? (a.cum[i] + len - 1) / ROWS - a.cum[i] / ROWS + 1 : 0;
+  } else {
+    b0 = i * TB;
+    nb = (len + ROWS - 1) / ROWS;
+  }
+  const double* p = a.L[l].part + (long long)b0 * stride;
   double t = 0.0;
-  for (int tb = 0; tb < nb; ++tb)
-    for (int ob = 0; ob < OB; ++ob) t += part[((long long)i * TB + tb) * OB + ob];
-  s[i] = (float)t;
+  for (long long k = lane; k < (long long)nb * nc; k += 64) {
+    const int blk = (int)(k / nc), c = (int)(k - (long long)blk * nc);
+    if (!OBS && !a.packed) {   // column blocks past a target's length hold nothing
+      const int j = c / TB;
+      if ((c - j * TB) * ROWS >= clamp_len(a.len, a.n + j, a.T)) continue;
+    }
+    t += p[(long long)blk * stride + c];
+  }
+  t = wave_sum_l63(t);
+  if (lane == 63) s[(long long)l * a.n + i] = (float)(t * scale);
 }
 
 // gbar* (fp32) -> bf16 hi + lo (hi = RNE(g), lo = RNE(g - hi))
@@ -197,64 +413,89 @@ __global__ void split_kernel(const float* g, long long count, __bf16* hi, __bf16
 
 // ---------------------------------------------------------------- GIP
 
-// workgroup (i, tb) x (j, sb): part = sum over the 128 x 128 block of
-// (D_i D*_j^T) .* (X_i X*_j^T)
-__global__ __launch_bounds__(kSThreads) void gip_kernel(ScoreLayer a, int TB, double* part) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * 2 * kSPanel];
-  __shared__ double red[kSThreads / 64];
-  const int i = blockIdx.x / TB, tb = blockIdx.x % TB;
-  const int j = blockIdx.y / TB, sb = blockIdx.y % TB;
-  const int L = clamp_len(a.len, i, a.T), Lj = clamp_len(a.len, a.n + j, a.T);
-  const int t0 = tb * kST, s0 = sb * kST;
-  if (t0 >= L || s0 >= Lj) return;
+// 128 general tokens x 128 target tokens of one layer: the row sums of
+// (D D*^T) .* (X X*^T).  Rows and columns are packed tokens, so the tile count
+// follows the valid tokens (with one tile per pair of examples, 64 examples
+// of 32..128 tokens against 8 targets filled 39 % of the products: whole call
+// over eight 2048 x 2048 layers 0.67 -> 0.26 ms, all layers in one launch).
+__global__ __launch_bounds__(kSThreads, 2) void gip_kernel(ScoreArgs a) {
+  constexpr int kRing = 2 * 2 * kSPanel;
+  __shared__ __attribute__((aligned(1024))) unsigned char
+      lds[kRing + 2 * kST * sizeof(double) + 2 * sizeof(TileRows<kST>)];   // one LDS object, as in pip_kernel
+  double (*rs)[kST] = reinterpret_cast<double (*)[kST]>(lds + kRing);
+  TileRows<kST>& tr = *reinterpret_cast<TileRows<kST>*>(lds + kRing + 2 * kST * sizeof(double));
+  TileRows<kST>& tc = *(&tr + 1);
+  const int TB = (a.T + kST - 1) / kST;
+  const int R = a.packed ? (a.cum[a.n] + kST - 1) / kST : a.n * TB;
+  const int C = a.packed ? (a.cum[a.n + 1 + a.m] + kST - 1) / kST : a.m * TB;
+  // XCD b % 8 takes runs of 32 tiles, the column blocks of a row block next
+  // to each other
+  const int x = blockIdx.x & 7, sl = blockIdx.x >> 3;
+  long long q = ((long long)(sl >> 5) * 8 + x) * 32 + (sl & 31);
+  const long long per = (long long)R * C;
+  if (per == 0) return;
+  const int li = (int)(q / per);
+  if (li >= a.num_layers) return;
+  q -= li * per;
+  const int rt = (int)(q / C), sb = (int)(q - (long long)rt * C);
+  const ScoreLayer& L = a.L[li];
+  if (!a.packed) {
+    const int i = rt / TB, j = sb / TB;
+    if ((rt - i * TB) * kST >= clamp_len(a.len, i, a.T) || (sb - j * TB) * kST >= clamp_len(a.len, a.n + j, a.T)) return;
+  }
+  int e0, e_last, f0, f_last;
+  const int rows = tile_rows(tr, a.cum, a.len, 0, a.n, a.T, a.packed, rt, e0, e_last);
+  const int cols = tile_rows(tc, a.cum + a.n + 1, a.len, a.n, a.m, a.T, a.packed, sb, f0, f_last);
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr = w >> 1, wc = w & 1, lr = lane & 15, lg = lane >> 4;
+  auto panel = [&](const TileRows<kST>& t, long long ex, long long ld) {
+    PanelRows p;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int hb = w + 4 * u;
+      const int r = 8 * hb + (lane >> 3);
+      p.seg[u] = swz_seg_of_lane(lane, hb & 1);
+      const int rel = t.rel[r];
+      p.off[u] = rel >= 0 ? (unsigned)(rel * ex + t.tok[r] * ld * 2) : kOobOffset;
+    }
+    return p;
+  };
   f32x4 dd[4][4], xx[4][4];
 #pragma unroll
   for (int p = 0; p < 4; ++p)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      dd[p][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-      xx[p][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int q4 = 0; q4 < 4; ++q4) {
+      dd[p][q4] = f32x4{0.f, 0.f, 0.f, 0.f};
+      xx[p][q4] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
   {
-    const __amdgpu_buffer_rsrc_t ra =
-        make_rsrc(a.dy + (long long)i * a.exdy + (long long)t0 * a.lddy * 2, kOobOffset);
-    const __amdgpu_buffer_rsrc_t rb[1] = {
-        make_rsrc(a.dy + (long long)(a.n + j) * a.exdy + (long long)s0 * a.lddy * 2, kOobOffset)};
-    panel_gemm<1>(lds, ra, panel_rows(w, lane, L - t0, a.lddy * 2), rb, panel_rows(w, lane, Lj - s0, a.lddy * 2),
-                  a.d_out, dd);
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(L.dy + (long long)e0 * L.exdy, kOobOffset);
+    const __amdgpu_buffer_rsrc_t rb = make_rsrc(L.dy + (long long)(a.n + f0) * L.exdy, kOobOffset);
+    panel_gemm(lds, ra, panel(tr, L.exdy, L.lddy), rb, panel(tc, L.exdy, L.lddy), L.d_out, dd);
   }
   {
-    const __amdgpu_buffer_rsrc_t ra = make_rsrc(a.x + (long long)i * a.exx + (long long)t0 * a.ldx * 2, kOobOffset);
-    const __amdgpu_buffer_rsrc_t rb[1] = {
-        make_rsrc(a.x + (long long)(a.n + j) * a.exx + (long long)s0 * a.ldx * 2, kOobOffset)};
-    panel_gemm<1>(lds, ra, panel_rows(w, lane, L - t0, a.ldx * 2), rb, panel_rows(w, lane, Lj - s0, a.ldx * 2),
-                  a.d_in, xx);
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(L.x + (long long)e0 * L.exx, kOobOffset);
+    const __amdgpu_buffer_rsrc_t rb = make_rsrc(L.x + (long long)(a.n + f0) * L.exx, kOobOffset);
+    panel_gemm(lds, ra, panel(tr, L.exx, L.ldx), rb, panel(tc, L.exx, L.ldx), L.d_in, xx);
   }
-  // rows past a length are zero in both products: no masking needed
-  float d = 0.f;
 #pragma unroll
   for (int p = 0; p < 4; ++p)
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int r = 0; r < 4; ++r) {
+      float d = 0.f;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) d = fmaf(dd[p][q][r], xx[p][q][r], d);
-  const double tot = block_sum_256((double)d, red);
-  if (tid == 0) part[((long long)i * TB + tb) * ((long long)a.m * TB) + (long long)j * TB + sb] = tot;
-}
-
-__global__ void gip_reduce_kernel(const double* part, int n, int m, int T, const int* len, int TB, float* s) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int nb = (clamp_len(len, i, T) + kST - 1) / kST;
-  double t = 0.0;
-  for (int tb = 0; tb < nb; ++tb)
-    for (int j = 0; j < m; ++j) {
-      const int nsb = (clamp_len(len, n + j, T) + kST - 1) / kST;
-      for (int sb = 0; sb < nsb; ++sb) t += part[((long long)i * TB + tb) * ((long long)m * TB) + (long long)j * TB + sb];
+      for (int q4 = 0; q4 < 4; ++q4)
+        d = 64 * wc + 16 * q4 + lr < cols ? fmaf(dd[p][q4][r], xx[p][q4][r], d) : d;
+      double v = (double)d;
+      v += dpp_d<0xB1, 0xF>(v);
+      v += dpp_d<0x4E, 0xF>(v);
+      v += dpp_d<0x141, 0xF>(v);
+      v += dpp_d<0x140, 0xF>(v);
+      if (lr == 0) rs[wc][64 * wr + 16 * p + 4 * lg + r] = v;
     }
-  s[i] = (float)(t / (double)m);
+  __syncthreads();
+  tile_example_sums(tr, rs, a.cum, rows, a.packed, rt, e0, e_last, L.part, a.SB, sb);
 }
 
 __global__ void fill_kernel(float* p, long long count, float v) {
@@ -265,8 +506,49 @@ __global__ void fill_kernel(float* p, long long count, float v) {
 // ---------------------------------------------------------------- host
 
 struct ScorePlan {
-  size_t off_wm, off_g, off_upd, off_hi, off_lo, off_part, off_direct, bytes;
+  size_t off_wm, off_g, off_upd, off_hi, off_lo, off_cum, off_part, off_direct, bytes;
 };
+
+// Layers are taken in groups of at most kMaxScoreLayers consecutive ones: a
+// group's gbar* are assembled in one call and its tiles share one launch, so
+// that the last round of tiles is a small part of it (eight 2048 x 2048
+// layers one at a time: 2.4 rounds of the chip each).  A group's gbar* hold
+// at most kGroupElems elements (256 MiB of workspace for PIP), or one layer.
+constexpr int64_t kGroupElems = (int64_t)32 << 20;
+
+int group_end(const dr_layer* layers, int num_layers, int first, int method) {
+  int64_t g = 0;
+  int l = first;
+  for (; l < num_layers && l - first < kMaxScoreLayers; ++l) {
+    g += layers[l].d_out * layers[l].d_in;
+    if (method != DR_SCORE_GIP && l > first && g > kGroupElems) break;
+  }
+  return l;
+}
+
+// Packed tiles address a tile's rows from its first example with 32-bit
+// offsets, and positions are 32-bit: possible when the examples that one
+// tile can hold span less than 4 GiB.
+bool score_packed(const dr_layer* layers, int num_layers, int64_t n, int64_t m, int64_t T, int64_t rows) {
+  const int64_t most = n > m ? n : m;
+  const int64_t span = (most < rows ? most : rows) * T;
+  if (most * T >= ((int64_t)1 << 31) - 2 * rows) return false;
+  for (int l = 0; l < num_layers; ++l) {
+    const int64_t ld = layers[l].ldx > layers[l].lddy ? layers[l].ldx : layers[l].lddy;
+    if ((uint64_t)span * (uint64_t)ld * 2 >= (uint64_t)kOobOffset - 64) return false;
+  }
+  return true;
+}
+
+// 128-token column blocks of the m targets (upper bound)
+int64_t gip_cols(int64_t m, int64_t T, bool packed) {
+  return packed ? (m * T + kST - 1) / kST : m * ((T + kST - 1) / kST);
+}
+
+// row blocks of ROWS tokens over n examples: (row block, example) slots
+int64_t score_slots(int64_t n, int64_t T, int64_t rows, bool packed) {
+  return packed ? (n * T + rows - 1) / rows + n : n * ((T + rows - 1) / rows);
+}
 
 dr_layer target_layer(const dr_layer& L, int64_t n, int64_t T) {
   dr_layer t = L;
@@ -278,24 +560,31 @@ dr_layer target_layer(const dr_layer& L, int64_t n, int64_t T) {
 ScorePlan score_plan(const dr_layer* layers, int num_layers, int64_t n, int64_t m, int64_t T, int method) {
   int64_t gmax = 1, partmax = 1;
   size_t updmax = 0, dirmax = 0;
-  const int64_t TB = (T + kST - 1) / kST;
-  for (int l = 0; l < num_layers; ++l) {
-    const dr_layer& L = layers[l];
-    const int64_t g = L.d_out * L.d_in;
+  const int64_t rows = method == DR_SCORE_PIP ? kTileRows : kST;
+  dr_layer t[kMaxScoreLayers];
+  for (int l0 = 0; l0 < num_layers;) {
+    const int l1 = group_end(layers, num_layers, l0, method);
+    const bool packed = score_packed(layers + l0, l1 - l0, n, m, T, rows);
+    const int64_t slots = score_slots(n, T, rows, packed);
+    int64_t g = 0, part = 0;
+    for (int l = l0; l < l1; ++l) {
+      g += layers[l].d_out * layers[l].d_in;
+      t[l - l0] = target_layer(layers[l], n, T);
+      part += slots * (method == DR_SCORE_PIP ? (layers[l].d_out + kTileRows - 1) / kTileRows
+                                              : gip_cols(m, T, packed));
+    }
     gmax = g > gmax ? g : gmax;
-    const dr_layer t = target_layer(L, n, T);
-    const size_t u = dr_update_workspace_size(&t, 1, m, T, DR_BF16);
-    updmax = u > updmax ? u : updmax;
-    if (method == DR_SCORE_PIP) {
-      const int64_t OB = (L.d_out + kST - 1) / kST;
-      partmax = n * TB * OB > partmax ? n * TB * OB : partmax;
+    partmax = part > partmax ? part : partmax;
+    if (method != DR_SCORE_GIP) {
+      const size_t u = dr_update_workspace_size(t, l1 - l0, m, T, DR_BF16);
+      updmax = u > updmax ? u : updmax;
     }
     if (method == DR_SCORE_DIRECT) {
-      const size_t d = direct_workspace(&L, 1, n);
+      const size_t d = direct_workspace(layers + l0, l1 - l0, n);
       dirmax = d > dirmax ? d : dirmax;
     }
+    l0 = l1;
   }
-  if (method == DR_SCORE_GIP) partmax = n * TB * m * TB > 1 ? n * TB * m * TB : 1;
   ScorePlan p;
   size_t o = 0;
   p.off_wm = o;     o = align_up(o + (size_t)(m > 0 ? m : 1) * 4, 256);
@@ -303,6 +592,7 @@ ScorePlan score_plan(const dr_layer* layers, int num_layers, int64_t n, int64_t 
   p.off_upd = o;    if (method != DR_SCORE_GIP) o = align_up(o + updmax, 256);
   p.off_hi = o;     if (method == DR_SCORE_PIP) o = align_up(o + (size_t)gmax * 2, 256);
   p.off_lo = o;     if (method == DR_SCORE_PIP) o = align_up(o + (size_t)gmax * 2, 256);
+  p.off_cum = o;    if (method != DR_SCORE_DIRECT) o = align_up(o + (size_t)(n + m + 2) * 4, 256);
   p.off_part = o;   if (method != DR_SCORE_DIRECT) o = align_up(o + (size_t)partmax * 8, 256);
   p.off_direct = o; if (method == DR_SCORE_DIRECT) o = align_up(o + dirmax, 256);
   p.bytes = o;
@@ -354,58 +644,85 @@ extern "C" dr_status dr_score_exact(const dr_layer* layers, int num_layers, int6
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   float* wm = reinterpret_cast<float*>(ws + pl.off_wm);
   float* gstar = reinterpret_cast<float*>(ws + pl.off_g);
-  hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, hs, wm, (long long)m,
-                     1.0f / (float)m);
-  if ((st = launch_status()) != DR_OK) return st;
-  const int TB = (int)((T + kST - 1) / kST);
-  for (int l = 0; l < num_layers && st == DR_OK; ++l) {
-    const dr_layer& L = layers[l];
-    float* sl = s + (int64_t)l * n;
+  if (method != DR_SCORE_GIP) {
+    hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, hs, wm, (long long)m,
+                       1.0f / (float)m);
+    if ((st = launch_status()) != DR_OK) return st;
+  }
+  int* cum = reinterpret_cast<int*>(ws + pl.off_cum);
+  if (method != DR_SCORE_DIRECT) {
+    hipLaunchKernelGGL(score_plan_kernel, dim3(2), dim3(1024), 0, hs, len, (int)n, (int)m, (int)T, cum);
+    if ((st = launch_status()) != DR_OK) return st;
+  }
+  for (int l0 = 0; l0 < num_layers;) {
+    const int l1 = group_end(layers, num_layers, l0, (int)method), cnt = l1 - l0;
+    float* sl = s + (int64_t)l0 * n;
+    int64_t goff[kMaxScoreLayers + 1] = {0};
+    for (int j = 0; j < cnt; ++j) goff[j + 1] = goff[j] + layers[l0 + j].d_out * layers[l0 + j].d_in;
     if (method != DR_SCORE_GIP) {
-      // gbar* = (1/m) sum_j G*_j from the target rows
-      const dr_layer t = target_layer(L, n, T);
-      const int64_t zero = 0;
-      st = dr_assemble_update(&t, 1, m, T, len ? len + n : nullptr, DR_BF16, wm, 1, m, nullptr, gstar, &zero,
+      // gbar* = (1/m) sum_j G*_j of the group's layers from the target rows
+      dr_layer t[kMaxScoreLayers];
+      for (int j = 0; j < cnt; ++j) t[j] = target_layer(layers[l0 + j], n, T);
+      st = dr_assemble_update(t, cnt, m, T, len ? len + n : nullptr, DR_BF16, wm, 1, m, nullptr, gstar, goff,
                               ws + pl.off_upd, pl.off_hi - pl.off_upd, stream);
-      if (st != DR_OK) break;
+      if (st != DR_OK) return st;
     }
-    ScoreLayer a;
-    a.x = static_cast<const unsigned char*>(L.x);
-    a.dy = static_cast<const unsigned char*>(L.dy);
-    a.ldx = L.ldx;
-    a.lddy = L.lddy;
-    a.exx = T * L.ldx * 2;
-    a.exdy = T * L.lddy * 2;
-    a.d_in = (int)L.d_in;
-    a.d_out = (int)L.d_out;
+    if (method == DR_SCORE_DIRECT) {
+      st = direct_scores(layers + l0, cnt, n, T, len, gstar, goff, sl, ws + pl.off_direct, hs);
+      if (st != DR_OK) return st;
+      l0 = l1;
+      continue;
+    }
+    const int64_t rows = method == DR_SCORE_PIP ? kTileRows : kST;
+    ScoreArgs a = {};
+    a.num_layers = cnt;
     a.T = (int)T;
     a.n = (int)n;
     a.m = (int)m;
+    a.packed = score_packed(layers + l0, cnt, n, m, T, rows);
+    a.SB = (int)gip_cols(m, T, a.packed);
     a.len = len;
+    a.cum = cum;
+    __bf16* hi = reinterpret_cast<__bf16*>(ws + pl.off_hi);
+    __bf16* lo = reinterpret_cast<__bf16*>(ws + pl.off_lo);
+    const int64_t slots = score_slots(n, T, rows, a.packed);
     double* part = reinterpret_cast<double*>(ws + pl.off_part);
-    if (method == DR_SCORE_DIRECT) {
-      const int64_t zero = 0;
-      st = direct_scores(&L, 1, n, T, len, gstar, &zero, sl, ws + pl.off_direct, hs);
-    } else if (method == DR_SCORE_PIP) {
-      const long long cnt = L.d_out * L.d_in;
-      __bf16* hi = reinterpret_cast<__bf16*>(ws + pl.off_hi);
-      __bf16* lo = reinterpret_cast<__bf16*>(ws + pl.off_lo);
-      hipLaunchKernelGGL(split_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, hs, (const float*)gstar, cnt,
-                         hi, lo);
-      const int OB = (int)((L.d_out + kST - 1) / kST);
-      hipLaunchKernelGGL(pip_kernel, dim3((unsigned)(n * TB), OB), dim3(kSThreads), 0, hs, a,
-                         reinterpret_cast<const unsigned char*>(hi), reinterpret_cast<const unsigned char*>(lo), TB,
-                         OB, part);
-      hipLaunchKernelGGL(pip_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, hs, (const double*)part,
-                         (int)n, (int)T, len, TB, OB, sl);
-      st = launch_status();
-    } else {
-      hipLaunchKernelGGL(gip_kernel, dim3((unsigned)(n * TB), (unsigned)(m * TB)), dim3(kSThreads), 0, hs, a, TB,
-                         part);
-      hipLaunchKernelGGL(gip_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, hs, (const double*)part,
-                         (int)n, (int)m, (int)T, len, TB, sl);
-      st = launch_status();
+    int64_t cols = 0;
+    for (int j = 0; j < cnt; ++j) {
+      const dr_layer& L = layers[l0 + j];
+      ScoreLayer& b = a.L[j];
+      b.x = static_cast<const unsigned char*>(L.x);
+      b.dy = static_cast<const unsigned char*>(L.dy);
+      b.ldx = L.ldx;
+      b.lddy = L.lddy;
+      b.exx = T * L.ldx * 2;
+      b.exdy = T * L.lddy * 2;
+      b.d_in = (int)L.d_in;
+      b.d_out = (int)L.d_out;
+      b.OB = (int)((L.d_out + kTileRows - 1) / kTileRows);
+      b.ghi = reinterpret_cast<const unsigned char*>(hi + goff[j]);
+      b.glo = reinterpret_cast<const unsigned char*>(lo + goff[j]);
+      b.part = part;
+      const int64_t c = method == DR_SCORE_PIP ? b.OB : a.SB;
+      part += slots * c;
+      cols += c;
     }
+    // tiles over the most row blocks the lengths allow; workgroups past the
+    // valid tokens return at once
+    const int64_t R = a.packed ? (n * T + rows - 1) / rows : n * ((T + rows - 1) / rows);
+    const unsigned grid = (unsigned)((R * cols + 255) / 256 * 256);
+    const dim3 rgrid((unsigned)((n + 3) / 4), (unsigned)cnt);
+    if (method == DR_SCORE_PIP) {
+      hipLaunchKernelGGL(split_kernel, dim3((unsigned)((goff[cnt] + 255) / 256)), dim3(256), 0, hs,
+                         (const float*)gstar, (long long)goff[cnt], hi, lo);
+      if (grid > 0) hipLaunchKernelGGL(pip_kernel, dim3(grid), dim3(256), 0, hs, a);
+      hipLaunchKernelGGL((score_reduce_kernel<kTileRows, true>), rgrid, dim3(256), 0, hs, a, sl, 1.0);
+    } else {
+      if (grid > 0) hipLaunchKernelGGL(gip_kernel, dim3(grid), dim3(kSThreads), 0, hs, a);
+      hipLaunchKernelGGL((score_reduce_kernel<kST, false>), rgrid, dim3(256), 0, hs, a, sl, 1.0 / (double)m);
+    }
+    if ((st = launch_status()) != DR_OK) return st;
+    l0 = l1;
   }
-  return st;
+  return DR_OK;
 }

@@ -89,3 +89,54 @@ def test_null_lengths_and_no_general_examples():
         assert torch.equal(a, b)
         s = torch.empty(1, 0, device=DEV)
         api.dr_score_exact(layers, 0, m, T, None, method, s)
+
+
+def check_all(layers, n, m, lens, methods):
+    refs = reference(layers, n, m, lens)
+    for method in methods:
+        s = api.score_exact(layers, n, m, lens, method=method)
+        torch.cuda.synchronize()
+        for l, ref in enumerate(refs):
+            got = host64(s[l])
+            assert np.isfinite(got).all()
+            assert (got[lens[:n].cpu().numpy() == 0] == 0.0).all()
+            assert rel(got, ref) <= TOL_SCORE, f"{method} layer {l}: {rel(got, ref):.2e}"
+
+
+def test_packed_tiles_of_many_short_examples():
+    """Tiles that hold many examples, with a run of more empty examples than
+    a tile has rows inside one tile, and output blocks past 256 columns."""
+    n, m, T = 700, 40, 5
+    g = torch.Generator().manual_seed(4)
+    lens = torch.randint(0, T + 1, (n + m,), generator=g, dtype=torch.int32)
+    lens[30:330] = 0
+    lens[n + 3:n + 9] = 0
+    lens = lens.to(DEV)
+    check_all(make([(72, 520), (136, 8)], n + m, T, lens, seed=4), n, m, lens, ["gip", "pip"])
+
+
+@pytest.mark.parametrize("length", [255, 256, 257])
+def test_packed_tile_edges(length):
+    n, m, T = 3, 2, 257
+    lens = torch.tensor([length, 1, length, length, 128], dtype=torch.int32, device=DEV)
+    check_all(make([(64, 264)], n + m, T, lens, seed=5), n, m, lens, ["gip", "pip"])
+
+
+def test_rows_further_apart_than_a_tile_can_address():
+    """Row strides for which the examples of one tile would span 4 GiB: a
+    tile then holds rows of one example only."""
+    n, m, T, ld = 5, 2, 300, 1_500_000
+    lens = torch.tensor([300, 0, 257, 128, 1, 300, 129], dtype=torch.int32, device=DEV)
+    layers = make([(72, 136)], n + m, T, lens, seed=6)
+    wide = torch.empty((n + m) * T * ld, dtype=torch.bfloat16, device=DEV).view(n + m, T, ld)
+    wide[:, :, :72] = layers[0]["x"]
+    layers[0]["x"] = wide[:, :, :72]
+    check_all(layers, n, m, lens, ["gip", "pip"])
+
+
+def test_layer_groups():
+    """More layers than one group holds, of different widths."""
+    n, m, T = 3, 2, 20
+    lens = torch.tensor([20, 7, 16, 20, 3], dtype=torch.int32, device=DEV)
+    specs = [(64 + 8 * (l % 5), 40 + 72 * (l % 4)) for l in range(18)]
+    check_all(make(specs, n + m, T, lens, seed=7), n, m, lens, METHODS)
