@@ -4,7 +4,8 @@
 // right-looking Cholesky factorisation in fp32 followed by iterative
 // refinement with fp64 residuals of the exact fp32 K.
 //
-// Workspace (one group at a time; groups run one after another):
+// Workspace (per group of a batch; groups of up to 4096 rows run side by side,
+// as many as 1 GiB holds, larger ones one after another):
 //   L     fp32 [n][ldL]   the factor (lower triangle; the rest is never read)
 //   inv   fp32 [nblk][128][128]: the inverse of every 128x128 diagonal
 //         block of L (used by the panel solve)
@@ -99,6 +100,14 @@ LgLayout lg_layout(long long n) {
   return l;
 }
 
+// Groups in flight: blockIdx.z is the group within the batch, whose
+// workspaces lie gs bytes apart (and whose K, s and results follow each other).
+template <class T>
+__device__ __forceinline__ T* grp(T* p, long long gs) {
+  typedef typename std::conditional<std::is_const<T>::value, const char, char>::type C;
+  return reinterpret_cast<T*>(reinterpret_cast<C*>(p) + (long long)blockIdx.z * gs);
+}
+
 __device__ __forceinline__ bool finite_f(float v) { return (__float_as_uint(v) & 0x7f800000u) != 0x7f800000u; }
 
 
@@ -117,7 +126,13 @@ __device__ double block_sum_d(double v, double* sh) {
 // ---------------------------------------------------------------- set-up
 
 __global__ void lg_init_kernel(LgCtl* ctl, const float* s, int n, int npad, double* x, double* dx, double* r,
-                               double* z) {
+                               double* z, long long gs) {
+  ctl = grp(ctl, gs);
+  s += (long long)blockIdx.z * n;
+  x = grp(x, gs);
+  dx = grp(dx, gs);
+  r = grp(r, gs);
+  z = grp(z, gs);
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i == 0) {
     ctl->skip = 0;
@@ -139,7 +154,11 @@ __global__ void lg_init_kernel(LgCtl* ctl, const float* s, int n, int npad, doub
 // trace, lam_eff and the early outcomes of s (non-finite entries) and of
 // the trace (empty span); non-finite entries of K are found by lg_load_kernel
 __global__ __launch_bounds__(1024) void lg_setup_kernel(const float* K, const float* s, int n, float lambda, int mode,
-                                                        LgCtl* ctl, float* lam_eff_out) {
+                                                        LgCtl* ctl, float* lam_eff_out, long long gs) {
+  K += (long long)blockIdx.z * n * n;
+  s += (long long)blockIdx.z * n;
+  ctl = grp(ctl, gs);
+  lam_eff_out += blockIdx.z;
   __shared__ double sh[16];
   __shared__ int sbad;
   if (threadIdx.x == 0) sbad = 0;
@@ -177,7 +196,11 @@ __global__ __launch_bounds__(1024) void lg_setup_kernel(const float* K, const fl
 // DR_INFO_NONFINITE, over the empty-span outcome of a zero trace.
 constexpr int kLoadCols = 4096;
 __global__ __launch_bounds__(256) void lg_load_kernel(const float* K, int n, int vec, int c0, int c1, float* L,
-                                                      long long ldL, LgCtl* ctl, float* lam_eff_out) {
+                                                      long long ldL, LgCtl* ctl, float* lam_eff_out, long long gs) {
+  K += (long long)blockIdx.z * n * n;
+  L = grp(L, gs);
+  ctl = grp(ctl, gs);
+  lam_eff_out += blockIdx.z;
   __shared__ int any;
   const int i = blockIdx.x, tid = threadIdx.x;
   if (tid == 0) any = 0;
@@ -286,8 +309,11 @@ __device__ __forceinline__ int otile(int I, int J) { return (I * (I - 1) / 2 + J
 constexpr int kPotrfWaves = 8;   // wave 0 factors the diagonal tiles, the others the rest
 template <int PB>
 __global__ __launch_bounds__(64 * kPotrfWaves) void lg_potrf_kernel(float* L, long long ldL, int k, int kb,
-                                                                    float* inv, LgCtl* ctl) {
+                                                                    float* inv, LgCtl* ctl, long long gs) {
   static_assert(PB == 16, "16x16 tiles");
+  L = grp(L, gs);
+  inv = grp(inv, gs);
+  ctl = grp(ctl, gs);
   constexpr int NW = kPotrfWaves;
   if (ctl->skip) return;
   constexpr int NT = NB / 16;
@@ -499,7 +525,10 @@ constexpr int kPotrfPB = 16;
 // operands, so the four MFMAs of one 16-wide step take the reduction indices
 // {t, 4+t, 8+t, 12+t} -- the same set for A and B, which is all that matters.
 __global__ __launch_bounds__(256) void lg_trsm_kernel(float* L, long long ldL, int n, int k, const float* inv,
-                                                      const LgCtl* ctl) {
+                                                      const LgCtl* ctl, long long gs) {
+  L = grp(L, gs);
+  inv = grp(inv, gs);
+  ctl = grp(ctl, gs);
   if (ctl->skip) return;
   // only the inverse goes through LDS (68 KiB, so the workgroup fits on a CU
   // beside a trailing-update workgroup); each wave reads its 16 rows of A21
@@ -580,7 +609,9 @@ constexpr int SY_CH = 32;                 // panel columns per chunk
 // running on the other stream.
 template <int W, int TS>
 __global__ __launch_bounds__(256, 2) void lg_syrk_kernel(float* L, long long ldL, int n, int k, int h, int head,
-                                                         int ntiles, const LgCtl* ctl) {
+                                                         int ntiles, const LgCtl* ctl, long long gs) {
+  L = grp(L, gs);
+  ctl = grp(ctl, gs);
   static_assert(TS == 128 || TS == 64, "tile edge");
   constexpr int PANEL = TS * SY_CH * 4;   // bytes of one tile row's chunk
   constexpr int RB = TS / 32;             // 16-row blocks per wave
@@ -1029,7 +1060,12 @@ __device__ __forceinline__ f32x4 tile_nn_q(const float* A, int ra, const float* 
 
 __global__ __launch_bounds__(256) void lg_sinv_kernel(const float* L, long long ldL, int n, int nblk,
                                                       const float* inv, float* sinv, float* sinvt, int S0, int ii,
-                                                      const LgCtl* ctl) {
+                                                      const LgCtl* ctl, long long gs) {
+  L = grp(L, gs);
+  inv = grp(inv, gs);
+  sinv = grp(sinv, gs);
+  sinvt = grp(sinvt, gs);
+  ctl = grp(ctl, gs);
   if (ctl->skip) return;
   const int S = S0 + blockIdx.y;   // row ii of super-blocks S0, S0 + 1, ...
   const int jj = blockIdx.x / SV_CQ, cq = blockIdx.x % SV_CQ, d = ii - jj;
@@ -1143,7 +1179,12 @@ __global__ __launch_bounds__(256) void lg_sinv_kernel(const float* L, long long 
 // 4 l + 256 t; each row's sum is a fixed-order DPP reduction.
 template <int RW>
 __global__ __launch_bounds__(256) void lg_rowdot_kernel(const float* M, long long ldM, int rows, int width, int mode,
-                                                        const double* v, double* out, int sub, const LgCtl* ctl) {
+                                                        const double* v, double* out, int sub, const LgCtl* ctl,
+                                                        long long gs) {
+  M = grp(M, gs);
+  v = grp(v, gs);
+  out = grp(out, gs);
+  ctl = grp(ctl, gs);
   if (ctl->skip || ctl->done) return;
   constexpr int CT = SBN / 256;   // float4 columns per lane
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -1189,7 +1230,12 @@ __global__ __launch_bounds__(256) void lg_rowdot_kernel(const float* M, long lon
 // of a column are added in a fixed order.
 constexpr int kColThreads = 1024;
 __global__ __launch_bounds__(kColThreads) void lg_coldot_kernel(const float* M, long long ldM, int rows,
-                                                                const double* v, double* out, const LgCtl* ctl) {
+                                                                const double* v, double* out, const LgCtl* ctl,
+                                                                long long gs) {
+  M = grp(M, gs);
+  v = grp(v, gs);
+  out = grp(out, gs);
+  ctl = grp(ctl, gs);
   if (ctl->skip || ctl->done) return;
   constexpr int NS = kColThreads / 16, CU = SBN / NS;   // row streams, rows of a stream
   __shared__ double vs[SBN], part[NS][64];
@@ -1236,7 +1282,11 @@ __global__ __launch_bounds__(kColThreads) void lg_coldot_kernel(const float* M, 
 // first solution x0 and dx1: if they already pass the convergence test
 // (the geometric estimate |dx1|^2 / |x0| of the error left), the second
 // step's kernels return at once.
-__global__ __launch_bounds__(1024) void lg_axpy_kernel(double* x, const double* dx, int npad, int it, LgCtl* ctl) {
+__global__ __launch_bounds__(1024) void lg_axpy_kernel(double* x, const double* dx, int npad, int it, LgCtl* ctl,
+                                                       long long gs) {
+  x = grp(x, gs);
+  dx = grp(dx, gs);
+  ctl = grp(ctl, gs);
   __shared__ double sh[16], shx[16];
   if (ctl->skip || ctl->done) return;
   double m = 0.0, mx = 0.0;
@@ -1268,7 +1318,13 @@ __global__ __launch_bounds__(1024) void lg_axpy_kernel(double* x, const double* 
 
 // r = s - (K + lam I) x and kx = K x in fp64, one wave per row of K
 __global__ __launch_bounds__(256) void lg_resid_kernel(const float* K, int n, const float* s, const double* x,
-                                                       double* r, double* kx, const LgCtl* ctl) {
+                                                       double* r, double* kx, const LgCtl* ctl, long long gs) {
+  K += (long long)blockIdx.z * n * n;
+  s += (long long)blockIdx.z * n;
+  x = grp(x, gs);
+  r = grp(r, gs);
+  if (kx) kx = grp(kx, gs);
+  ctl = grp(ctl, gs);
   if (ctl->skip || (!kx && ctl->done)) return;   // the final pass (kx != nullptr) always runs
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row >= n) return;
@@ -1296,7 +1352,13 @@ __global__ __launch_bounds__(256) void lg_resid_kernel(const float* K, int n, co
 // columns 4 l + 256 t as a float4 of each row; rows past n reread row n - 1
 // and their sums are dropped.
 __global__ __launch_bounds__(256) void lg_resid4_kernel(const float* K, int n, const float* s, const double* x,
-                                                        double* r, double* kx, const LgCtl* ctl) {
+                                                        double* r, double* kx, const LgCtl* ctl, long long gs) {
+  K += (long long)blockIdx.z * n * n;
+  s += (long long)blockIdx.z * n;
+  x = grp(x, gs);
+  r = grp(r, gs);
+  if (kx) kx = grp(kx, gs);
+  ctl = grp(ctl, gs);
   if (ctl->skip || (!kx && ctl->done)) return;   // the final pass (kx != nullptr) always runs
   const int lane = threadIdx.x & 63;
   const int row0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 4;
@@ -1331,7 +1393,15 @@ __global__ __launch_bounds__(256) void lg_resid4_kernel(const float* K, int n, c
 
 __global__ __launch_bounds__(1024) void lg_final_kernel(const float* s, const float* t2, int n, const double* x,
                                                         const double* kx, const LgCtl* ctl, float* w, float* resid2,
-                                                        int* info) {
+                                                        int* info, long long gs) {
+  s += (long long)blockIdx.z * n;
+  t2 += blockIdx.z;
+  x = grp(x, gs);
+  kx = grp(kx, gs);
+  ctl = grp(ctl, gs);
+  w += (long long)blockIdx.z * n;
+  resid2 += blockIdx.z;
+  info += blockIdx.z;
   __shared__ double sh[16];
   __shared__ double shm[16];
   const bool skip = ctl->skip != 0;
@@ -1361,7 +1431,25 @@ __global__ __launch_bounds__(1024) void lg_final_kernel(const float* s, const fl
 
 }  // namespace
 
-size_t span_large_workspace(int64_t n) { return lg_layout(n).total; }
+// Groups that run side by side: a group of up to kBatchMaxN rows is bound by
+// the latency of its chain of panels and leaves most CUs idle (n = 1000: 0.46
+// ms for one group; seven in turn 3.2 ms, side by side 0.5 ms); a larger one
+// fills the chip with its trailing updates (the four-panel bf16 bulk, which
+// starts above 6000 rows, is never batched).  The workspace of a batch is
+// held to kBatchBytes.
+constexpr int64_t kBatchMaxN = 4096;
+constexpr size_t kBatchBytes = (size_t)1 << 30;
+
+static int batch_groups(const LgLayout& lay, int P) {
+  if (lay.n > kBatchMaxN) return 1;
+  const size_t g = kBatchBytes / lay.total;
+  return g < 1 ? 1 : (g < (size_t)P ? (int)g : P);
+}
+
+size_t span_large_workspace(int64_t n, int P) {
+  const LgLayout lay = lg_layout(n);
+  return lay.total * batch_groups(lay, P);
+}
 
 // the blocked solver's own streams and events (default priority), besides
 // the caller's stream: aux runs the diagonal-block chain one pair ahead;
@@ -1373,7 +1461,8 @@ struct LgStreams {
 };
 static dr_status span_large_groups(const float* K, const float* s, const float* t2, int n, int P, float lambda,
                                    int mode, float* w, float* lam_eff, float* resid2, int32_t* info,
-                                   const LgLayout& lay, unsigned char* base, hipStream_t hs, const LgStreams& st);
+                                   const LgLayout& lay, int G, unsigned char* base, hipStream_t hs,
+                                   const LgStreams& st);
 
 // The solver's two extra streams (default priority) and their events: one
 // set per device, created by the first blocked solve on that device and
@@ -1408,6 +1497,9 @@ dr_status span_large(const float* K, const float* s, const float* t2, int64_t n6
   const LgLayout lay = lg_layout(n64);
   if (!ws || ws_bytes < lay.total) return DR_ERR_WORKSPACE;
   if (!aligned16(ws)) return DR_ERR_ARG;
+  // a workspace of one group is enough: as many groups at a time as it holds
+  const int fit = ws_bytes / lay.total < (size_t)P ? (int)(ws_bytes / lay.total) : P;
+  const int most = batch_groups(lay, P);
   const int n = (int)n64;
   unsigned char* base = static_cast<unsigned char*>(ws);
   int dev = 0;
@@ -1428,12 +1520,14 @@ dr_status span_large(const float* K, const float* s, const float* t2, int64_t n6
     }
     a.ready = true;
   }
-  return span_large_groups(K, s, t2, n, P, lambda, mode, w, lam_eff, resid2, info, lay, base, hs, a.st);
+  return span_large_groups(K, s, t2, n, P, lambda, mode, w, lam_eff, resid2, info, lay, fit < most ? fit : most, base,
+                           hs, a.st);
 }
 
 static dr_status span_large_groups(const float* K, const float* s, const float* t2, int n, int P, float lambda,
                                    int mode, float* w, float* lam_eff, float* resid2, int32_t* info,
-                                   const LgLayout& lay, unsigned char* base, hipStream_t hs, const LgStreams& st) {
+                                   const LgLayout& lay, int G, unsigned char* base, hipStream_t hs,
+                                   const LgStreams& st) {
   hipStream_t aux = st.aux, sol = st.sol;
   hipEvent_t ev_col = st.ev_col, ev_next = st.ev_next, ev_blk = st.ev_blk, ev_bulk = st.ev_bulk, ev_sol = st.ev_sol;
   // the bulk trailing update runs persistent on 7/8 of the two-per-CU
@@ -1459,12 +1553,17 @@ static dr_status span_large_groups(const float* K, const float* s, const float* 
   const long long ldL = lay.ldL;
   const int nblk = (int)lay.nblk, npad = (int)lay.npad;
   const long long nn = (long long)n * n;
-  for (int p = 0; p < P; ++p) {
+  // G groups at a time, side by side in every launch (grid z)
+  const long long gs = (long long)lay.total;
+  for (int p = 0; p < P; p += G) {
+    const int g = P - p < G ? P - p : G;
     const float* Kp = K + (long long)p * nn;
     const float* sp = s + (long long)p * n;
-    hipLaunchKernelGGL(lg_init_kernel, dim3((npad + 255) / 256), dim3(256), 0, hs, ctl, sp, n, npad, x, dx, r, z);
+    hipLaunchKernelGGL(lg_init_kernel, dim3((npad + 255) / 256, 1, g), dim3(256), 0, hs, ctl, sp, n, npad, x, dx, r,
+                       z, gs);
     const int vec = aligned16(Kp) && n % 4 == 0;
-    hipLaunchKernelGGL(lg_setup_kernel, dim3(1), dim3(1024), 0, hs, Kp, sp, n, lambda, mode, ctl, lam_eff + p);
+    hipLaunchKernelGGL(lg_setup_kernel, dim3(1, 1, g), dim3(1024), 0, hs, Kp, sp, n, lambda, mode, ctl, lam_eff + p,
+                       gs);
 
     // Right-looking blocked factorisation by steps of four or two panels,
     // with look-ahead.  The trailing matrix takes one rank-512 update per
@@ -1484,13 +1583,15 @@ static dr_status span_large_groups(const float* K, const float* s, const float* 
       const int rows = n - k - W;
       const int T = (rows + NB - 1) / NB;
       const int n128 = h * T - h * (h - 1) / 2;
-      if (n128 >= cus) {
-        hipLaunchKernelGGL((lg_syrk_kernel<W, 128>), dim3(n128), dim3(256), 0, strm, L, ldL, n, k, h, 1, n128, ctl);
+      if (n128 * g >= cus) {
+        hipLaunchKernelGGL((lg_syrk_kernel<W, 128>), dim3(n128, 1, g), dim3(256), 0, strm, L, ldL, n, k, h, 1, n128,
+                           ctl, gs);
       } else {
         const int T64 = (rows + 63) / 64;
         int n64 = 0;
         for (int J = 0; J < 2 * h; ++J) n64 += T64 - J > 0 ? T64 - J : 0;
-        hipLaunchKernelGGL((lg_syrk_kernel<W, 64>), dim3(n64), dim3(256), 0, strm, L, ldL, n, k, h, 1, n64, ctl);
+        hipLaunchKernelGGL((lg_syrk_kernel<W, 64>), dim3(n64, 1, g), dim3(256), 0, strm, L, ldL, n, k, h, 1, n64,
+                           ctl, gs);
       }
     };
     auto head_update = [&](int W, int k, int h, hipStream_t strm) {
@@ -1505,10 +1606,11 @@ static dr_status span_large_groups(const float* K, const float* s, const float* 
       const int k = NB * b;
       const int kb = n - k < NB ? n - k : NB;
       float* ib = inv + (long long)b * NB * NB;
-      hipLaunchKernelGGL(lg_potrf_kernel<kPotrfPB>, dim3(1), dim3(64 * kPotrfWaves), 0, strm, L, ldL, k, kb, ib, ctl);
+      hipLaunchKernelGGL(lg_potrf_kernel<kPotrfPB>, dim3(1, 1, g), dim3(64 * kPotrfWaves), 0, strm, L, ldL, k, kb,
+                         ib, ctl, gs);
       const int rest = n - k - NB;
       if (rest > 0)
-        hipLaunchKernelGGL(lg_trsm_kernel, dim3((rest + 63) / 64), dim3(256), 0, strm, L, ldL, n, k, ib, ctl);
+        hipLaunchKernelGGL(lg_trsm_kernel, dim3((rest + 63) / 64, 1, g), dim3(256), 0, strm, L, ldL, n, k, ib, ctl, gs);
     };
     // Triangular solves by super-blocks of SB diagonal blocks (lg_sinv_kernel
     // forms the inverses).  L z = r for super-block S (r is consumed): its
@@ -1518,13 +1620,14 @@ static dr_status span_large_groups(const float* K, const float* s, const float* 
     auto fwd_step = [&](int S, hipStream_t strm) {
       const int o0 = SBN * S, nb = nblk - SB * S < SB ? nblk - SB * S : SB, width = NB * nb;
       const float* Xs = sinv + (long long)S * SBN * SBN;
-      hipLaunchKernelGGL(lg_rowdot_kernel<1>, dim3((width + 3) / 4), dim3(256), 0, strm, Xs, (long long)SBN, width,
-                         width, 1, r + o0, z + o0, 0, ctl);
+      hipLaunchKernelGGL(lg_rowdot_kernel<1>, dim3((width + 3) / 4, 1, g), dim3(256), 0, strm, Xs, (long long)SBN,
+                         width,
+                         width, 1, r + o0, z + o0, 0, ctl, gs);
       const int below = n - o0 - width;
       if (below > 0)
-        hipLaunchKernelGGL(lg_rowdot_kernel<4>, dim3((below + 15) / 16), dim3(256), 0, strm,
+        hipLaunchKernelGGL(lg_rowdot_kernel<4>, dim3((below + 15) / 16, 1, g), dim3(256), 0, strm,
                            L + (long long)(o0 + width) * ldL + o0, ldL, below, width, 0, z + o0, r + o0 + width, 1,
-                           ctl);
+                           ctl, gs);
     };
     // Block bb of the factor is final (factored, and its column below
     // solved): on the sol stream, row bb % SB of its super-block's inverse,
@@ -1537,8 +1640,9 @@ static dr_status span_large_groups(const float* K, const float* s, const float* 
     // are queued at once, then each block as soon as it is final.
     auto after_block = [&](int bb) {
       const int S = bb / SB, ii = bb % SB;
-      hipLaunchKernelGGL(lg_sinv_kernel, dim3((ii + 1) * SV_CQ), dim3(256), 0, sol, L, ldL, n, nblk, inv, sinv, sinvt,
-                         S, ii, ctl);
+      hipLaunchKernelGGL(lg_sinv_kernel, dim3((ii + 1) * SV_CQ, 1, g), dim3(256), 0, sol, L, ldL, n, nblk, inv, sinv,
+                         sinvt,
+                         S, ii, ctl, gs);
       if (ii == SB - 1 || bb == nblk - 1) fwd_step(S, sol);
     };
     const int slots6 = cus - cus / 8;
@@ -1549,7 +1653,7 @@ static dr_status span_large_groups(const float* K, const float* s, const float* 
       const int restq = n - NB * b - 4 * NB;
       if (b + 4 <= nblk && restq > 0) {
         const int T2 = (restq + S6_T - 1) / S6_T;
-        if (T2 > 2 && (T2 - 2) * (T2 - 1) / 2 >= kS6MinRounds * slots6) return 4;
+        if (g == 1 && T2 > 2 && (T2 - 2) * (T2 - 1) / 2 >= kS6MinRounds * slots6) return 4;
       }
       return b + 1 < nblk ? 2 : 1;
     };
@@ -1560,8 +1664,9 @@ static dr_status span_large_groups(const float* K, const float* s, const float* 
     int b = 0, m = width_at(0);
     auto load = [&](int c0, int c1) {
       if (c1 > c0)
-        hipLaunchKernelGGL(lg_load_kernel, dim3(n, (c1 - c0 + kLoadCols - 1) / kLoadCols), dim3(256), 0, hs, Kp, n, vec,
-                           c0, c1, L, ldL, ctl, lam_eff + p);
+        hipLaunchKernelGGL(lg_load_kernel, dim3(n, (c1 - c0 + kLoadCols - 1) / kLoadCols, g), dim3(256), 0, hs, Kp,
+                           n, vec,
+                           c0, c1, L, ldL, ctl, lam_eff + p, gs);
     };
     load(0, NB * m < n ? NB * m : n);
     if (hipEventRecord(ev_col, hs) != hipSuccess) return DR_ERR_HIP;
@@ -1590,7 +1695,7 @@ static dr_status span_large_groups(const float* K, const float* s, const float* 
       const int skip = NB * m2 / S6_T;
       const int T2 = rest > 0 ? (rest + S6_T - 1) / S6_T : 0;
       const int n6 = T2 > skip ? (T2 - skip) * (T2 - skip + 1) / 2 : 0;
-      const bool bulk6 = m >= 2 && m2 >= 2 && rest > 0 && n6 >= kS6MinRounds * slots6;
+      const bool bulk6 = g == 1 && m >= 2 && m2 >= 2 && rest > 0 && n6 >= kS6MinRounds * slots6;
       late = late || !bulk6;
       if (late && queued < b2) {
         if (hipStreamWaitEvent(sol, ev_next, 0) != hipSuccess) return DR_ERR_HIP;
@@ -1600,8 +1705,9 @@ static dr_status span_large_groups(const float* K, const float* s, const float* 
         const int S_lo = queued / SB, S_hi = b2 / SB;
         if (S_hi > S_lo) {
           for (int ii = 0; ii < SB; ++ii)
-            hipLaunchKernelGGL(lg_sinv_kernel, dim3((ii + 1) * SV_CQ, S_hi - S_lo), dim3(256), 0, sol, L, ldL, n, nblk,
-                               inv, sinv, sinvt, S_lo, ii, ctl);
+            hipLaunchKernelGGL(lg_sinv_kernel, dim3((ii + 1) * SV_CQ, S_hi - S_lo, g), dim3(256), 0, sol, L, ldL, n,
+                               nblk,
+                               inv, sinv, sinvt, S_lo, ii, ctl, gs);
           for (int S = S_lo; S < S_hi; ++S) fwd_step(S, sol);
           queued = SB * S_hi;
         }
@@ -1630,15 +1736,17 @@ static dr_status span_large_groups(const float* K, const float* s, const float* 
           // many rounds of tiles: the chain has slack, 15/16 of the slots;
           // under two rounds: the chain is the longer path, 3/4 of them
           const int slots =
-              nrest >= 8 * cus ? 2 * cus - cus / 8 : (nrest < 4 * cus ? 2 * cus - cus / 2 : rest_slots);
-          const int grid = nrest < slots ? nrest : slots;
+              nrest * g >= 8 * cus ? 2 * cus - cus / 8 : (nrest * g < 4 * cus ? 2 * cus - cus / 2 : rest_slots);
+          const int grid = nrest * g <= slots ? nrest : (slots / g > 1 ? slots / g : 1);
           // (a step of one panel is the last: it has no bulk)
           if (W == 4 * NB)
-            hipLaunchKernelGGL((lg_syrk_kernel<4 * NB, 128>), dim3(grid), dim3(256), 0, hs, L, ldL, n, k, m2, 0, nrest,
-                               ctl);
+            hipLaunchKernelGGL((lg_syrk_kernel<4 * NB, 128>), dim3(grid, 1, g), dim3(256), 0, hs, L, ldL, n, k, m2,
+                               0, nrest,
+                               ctl, gs);
           else
-            hipLaunchKernelGGL((lg_syrk_kernel<2 * NB, 128>), dim3(grid), dim3(256), 0, hs, L, ldL, n, k, m2, 0, nrest,
-                               ctl);
+            hipLaunchKernelGGL((lg_syrk_kernel<2 * NB, 128>), dim3(grid, 1, g), dim3(256), 0, hs, L, ldL, n, k, m2,
+                               0, nrest,
+                               ctl, gs);
         }
       }
       if (hipEventRecord(ev_bulk, hs) != hipSuccess) return DR_ERR_HIP;
@@ -1649,9 +1757,9 @@ static dr_status span_large_groups(const float* K, const float* s, const float* 
     const bool rows4 = n % 4 == 0 && aligned16(Kp);
     auto resid = [&](double* kx) {
       if (rows4)
-        hipLaunchKernelGGL(lg_resid4_kernel, dim3((n + 15) / 16), dim3(256), 0, hs, Kp, n, sp, x, r, kx, ctl);
+        hipLaunchKernelGGL(lg_resid4_kernel, dim3((n + 15) / 16, 1, g), dim3(256), 0, hs, Kp, n, sp, x, r, kx, ctl, gs);
       else
-        hipLaunchKernelGGL(lg_resid_kernel, dim3((n + 3) / 4), dim3(256), 0, hs, Kp, n, sp, x, r, kx, ctl);
+        hipLaunchKernelGGL(lg_resid_kernel, dim3((n + 3) / 4, 1, g), dim3(256), 0, hs, Kp, n, sp, x, r, kx, ctl, gs);
     };
     // the inverses and the first forward solve are in
     if (hipEventRecord(ev_sol, sol) != hipSuccess || hipStreamWaitEvent(hs, ev_sol, 0) != hipSuccess)
@@ -1666,18 +1774,21 @@ static dr_status span_large_groups(const float* K, const float* s, const float* 
       for (int S = nsb - 1; S >= 0; --S) {
         const int o0 = SBN * S, nb = nblk - SB * S < SB ? nblk - SB * S : SB, width = NB * nb;
         const float* XTs = sinvt + (long long)S * SBN * SBN;
-        hipLaunchKernelGGL(lg_rowdot_kernel<1>, dim3((width + 3) / 4), dim3(256), 0, hs, XTs, (long long)SBN, width,
-                           width, 2, z + o0, dx + o0, 0, ctl);
+        hipLaunchKernelGGL(lg_rowdot_kernel<1>, dim3((width + 3) / 4, 1, g), dim3(256), 0, hs, XTs, (long long)SBN,
+                           width,
+                           width, 2, z + o0, dx + o0, 0, ctl, gs);
         const int rows = n - o0 < width ? n - o0 : width;
         if (o0 > 0)
-          hipLaunchKernelGGL(lg_coldot_kernel, dim3(o0 / 64), dim3(kColThreads), 0, hs, L + (long long)o0 * ldL, ldL,
-                             rows, dx + o0, z, ctl);
+          hipLaunchKernelGGL(lg_coldot_kernel, dim3(o0 / 64, 1, g), dim3(kColThreads), 0, hs,
+                             L + (long long)o0 * ldL, ldL,
+                             rows, dx + o0, z, ctl, gs);
       }
-      hipLaunchKernelGGL(lg_axpy_kernel, dim3(1), dim3(1024), 0, hs, x, dx, npad, it, ctl);
+      hipLaunchKernelGGL(lg_axpy_kernel, dim3(1, 1, g), dim3(1024), 0, hs, x, dx, npad, it, ctl, gs);
     }
     resid(z);
-    hipLaunchKernelGGL(lg_final_kernel, dim3(1), dim3(1024), 0, hs, sp, t2 + p, n, x, z, ctl, w + (long long)p * n,
-                       resid2 + p, info + p);
+    hipLaunchKernelGGL(lg_final_kernel, dim3(1, 1, g), dim3(1024), 0, hs, sp, t2 + p, n, x, z, ctl,
+                       w + (long long)p * n,
+                       resid2 + p, info + p, gs);
     const dr_status rc = launch_status();
     if (rc != DR_OK) return rc;
   }

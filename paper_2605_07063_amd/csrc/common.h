@@ -237,7 +237,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // blocked Cholesky ridge solve for large groups (chol.hip)
 constexpr int64_t kSpanLargeMaxN = 65536;
-size_t span_large_workspace(int64_t n);
+size_t span_large_workspace(int64_t n, int P);
 dr_status span_large(const float* K, const float* s, const float* t2, int64_t n, int P, float lambda, int mode,
                      float* w, float* lam_eff, float* resid2, int32_t* info, void* ws, size_t ws_bytes,
                      hipStream_t hs);

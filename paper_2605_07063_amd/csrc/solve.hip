@@ -1493,9 +1493,8 @@ __global__ void empty_group_kernel(const float* t2, int P, float* lam_eff, float
 }  // namespace dr
 
 extern "C" size_t dr_span_workspace_size(int64_t n, int P) {
-  (void)P;   // groups above kSpanMaxN are solved one after another in one workspace
-  if (n <= dr::kSpanMaxN || n > dr::kSpanLargeMaxN) return 0;
-  return dr::span_large_workspace(n);
+  if (n <= dr::kSpanMaxN || n > dr::kSpanLargeMaxN || P < 1) return 0;
+  return dr::span_large_workspace(n, P);
 }
 
 extern "C" size_t dr_cone_workspace_size(int64_t n, int P) {

@@ -529,3 +529,46 @@ def test_combine_groups(dtype, n):
     torch.cuda.synchronize()
     ref = oracle.combine_ref(host64(G), host64(w), goff)
     assert rel(host64(u), ref) <= 1e-6
+
+
+@pytest.mark.parametrize("n,P", [(257, 6), (300, 40), (1000, 5)])
+def test_span_blocked_groups_side_by_side(n, P):
+    """Blocked groups that share their launches: bit for bit what each group
+    gives alone, whatever its neighbours' outcomes (a NaN, an empty span, a
+    non-positive pivot), and with a workspace of one group."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    G = torch.randn(P, n, 2 * n, generator=g, device=DEV)
+    K = G @ G.transpose(1, 2)
+    K = torch.tril(K) + torch.tril(K, -1).transpose(1, 2)
+    s = torch.randn(P, n, generator=g, device=DEV)
+    K[1, n - 1, 3] = K[1, 3, n - 1] = float("nan")
+    K[2] = 0.0
+    s[2] = 0.0
+    K[3, 200, 200] = -1.0
+    K = K.contiguous()
+    t2 = torch.rand(P, generator=g, device=DEV) + 1.0
+
+    def outputs(count):
+        return (torch.empty(count, n, device=DEV), torch.empty(count, device=DEV), torch.empty(count, device=DEV),
+                torch.empty(count, dtype=torch.int32, device=DEV))
+
+    alone = [outputs(1) for _ in range(P)]
+    one = api.dr_span_workspace_size(n, 1)
+    assert api.dr_span_workspace_size(n, P) >= one
+    ws = torch.empty(one, dtype=torch.uint8, device=DEV)
+    for p in range(P):
+        api.dr_project_span(K[p:p + 1], s[p:p + 1], t2[p:p + 1], 1e-3, 1, *alone[p], workspace=ws)
+    many, small = outputs(P), outputs(P)
+    api.dr_project_span(K, s, t2, 1e-3, 1, *many)
+    from paper_2605_07063_amd import _lib
+    lib = _lib.load()
+    st = lib.dr_project_span(api._ptr(K), api._ptr(s), api._ptr(t2), n, P, 1e-3, 1, *[api._ptr(t) for t in small],
+                             api._ptr(ws), one, api._stream(None))
+    assert st == 0
+    torch.cuda.synchronize()
+    infos = [int(a[3]) for a in alone]
+    assert infos[1] == -3 and infos[2] == 0 and infos[3] == 201
+    for k in range(4):
+        ref = torch.cat([a[k] for a in alone])
+        assert torch.equal(many[k], ref) and torch.equal(small[k], ref)
