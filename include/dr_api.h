@@ -155,8 +155,11 @@ size_t dr_sketch_workspace_size(const dr_layer* layers, int num_layers, int64_t 
  *                             DR_BF16), n >= 0, m >= 1, ld >= goff[P].
  *   goff  (host) int64 [P+1], 0 <= goff[0] <= ... <= goff[P], P >= 1.
  *   K     fp32 [P][n][n], both triangles written.  s fp32 [P][n].  t2 fp32 [P].
- * Arithmetic: fp32 inputs -> fp32 MFMA products with fp32 accumulation;
- * bf16 inputs -> bf16 MFMA with fp32 accumulation.
+ * Arithmetic: fp32 inputs -> fp32 products with fp32 accumulation (n < 128:
+ * fp32 MFMA; n >= 128: each value as three bf16 parts, which hold it to
+ * 2^-25, and each product as six bf16 MFMA products, exact in fp32; fp32 MFMA
+ * from the first value of 2^50 or more on); bf16 inputs -> bf16 MFMA with fp32
+ * accumulation.
  * Requirements: ldG, ldGt and every goff[p] multiples of 4 (f32) or 8 (bf16);
  * G and Gt 16-byte aligned.
  * ------------------------------------------------------------------------- */

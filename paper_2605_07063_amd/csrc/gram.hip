@@ -11,14 +11,13 @@
 //                        the group's columns (lower-triangle tile pairs only),
 //                        bf16 16x16x32 MFMA, fp32 accumulate; operands stream
 //                        from memory straight into registers.
-//   gram_tile_lds_kernel : fp32 rows, the same tiles and chunks on fp32
-//                        16x16x4 MFMA, the workgroup's rows staged once per
-//                        step through a three-stage LDS ring.  A diagonal
-//                        tile stages its rows once plus the target mean, and
-//                        its wave above the diagonal forms s_p for the
-//                        tile's rows (tile 0 also t2_p), so the same pass
-//                        yields them.
-//   gram_reduce_kernel : sums the chunk partials of a tile in chunk order and
+//   gram_split_kernel  : fp32 rows: 256-row tiles of K_p over one chunk of the
+//                        group's columns, each value split into three bf16
+//                        parts and each product taken as six bf16 MFMAs.  A
+//                        diagonal tile also forms the target mean of its
+//                        columns, the scores s_p of its rows and (tile 0)
+//                        t2_p, so the same pass yields them.
+//   gram_reduce_kernel : sums the chunk partials of a 64x64 tile in fp64 and
 //                        writes the lower triangle and its mirror, so K is
 //                        exactly symmetric, and for fp32 sketches s_p and
 //                        t2_p from the diagonal tiles.
@@ -63,7 +62,8 @@ constexpr int kThreads = 256;
 constexpr int kTile = 64;
 constexpr int kMaxGroups = 256;   // groups per launch (more groups -> more launches)
 constexpr int kTargetWGs = 1024;
-constexpr int kLdsSlots = 256 * 3;   // gram_tile_lds_kernel workgroups resident at once: 256 CUs x 3 (48 KB of LDS each)
+constexpr int kSplitSlots = 256;     // gram_split_kernel workgroups resident at once (one per CU)
+constexpr int64_t kSplitPartials = (int64_t)44 << 20;   // bytes of its chunk partials
 
 struct GramArgs {
   const unsigned char* G;
@@ -79,6 +79,10 @@ struct GramArgs {
   float* s;                         // maxchunks == 1); group p of the launch is pbase + p
   float* t2;
   long long pbase;
+  int vec4;                         // rows of K start 16-byte aligned
+  const float* Gt;                  // fp32 target rows (gram_split_kernel forms their mean itself)
+  long long ldGt;
+  int m;
 };
 
 template <bool BF16>
@@ -113,9 +117,8 @@ __device__ __forceinline__ void pair_to_tiles(int q, int& I, int& J) {
   J = q - i * (i + 1) / 2;
 }
 
-template <bool BF16>
 __global__ __launch_bounds__(kThreads, 2) void gram_tile_kernel(GramArgs a) {
-  using E = GTr<BF16>;
+  using E = GTr<true>;
   constexpr int NV = 2;              // vectors per row-block per step
   constexpr int STEP = NV * 4 * E::EPV;   // columns per step (4 lane groups)
   const int chunk = blockIdx.x, q = blockIdx.y, p = blockIdx.z;
@@ -138,13 +141,10 @@ __global__ __launch_bounds__(kThreads, 2) void gram_tile_kernel(GramArgs a) {
   for (int b = 0; b < 2; ++b) {
     rowA[b] = I * kTile + wr * 32 + b * 16 + lr;
     rowB[b] = J * kTile + wc * 32 + b * 16 + lr;
-    okA[b] = rowA[b] < a.rows;
-    okB[b] = rowB[b] < a.rows;
-    // row n of the augmented problem is the fp32 target mean (fp32 path only)
-    baseA[b] = rowA[b] < a.n ? a.G + (long long)rowA[b] * a.ldG * E::ES
-                             : reinterpret_cast<const unsigned char*>(a.gbar);
-    baseB[b] = rowB[b] < a.n ? a.G + (long long)rowB[b] * a.ldG * E::ES
-                             : reinterpret_cast<const unsigned char*>(a.gbar);
+    okA[b] = rowA[b] < a.n;
+    okB[b] = rowB[b] < a.n;
+    baseA[b] = a.G + (long long)rowA[b] * a.ldG * E::ES;
+    baseB[b] = a.G + (long long)rowB[b] * a.ldG * E::ES;
   }
 
   f32x4 acc[2][2];
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kThreads, 2) void gram_tile_kernel(GramArgs a) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j) acc[i][j] = mma_v<BF16>(ba[d][i][v], bb[d][j][v], acc[i][j]);
+          for (int j = 0; j < 2; ++j) acc[i][j] = mma_v<true>(ba[d][i][v], bb[d][j][v], acc[i][j]);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -209,237 +209,505 @@ __global__ __launch_bounds__(kThreads, 2) void gram_tile_kernel(GramArgs a) {
 }
 
 
-// fp32 rows, n + 1 > 128: 64 x 64 tile pairs over the n general rows, with
-// the operands staged through LDS.  Per step of 32 columns the workgroup's
-// rows are loaded once into registers (16-byte segments), written to a
-// three-stage LDS ring in the conflict-free operand layout, and read by the
-// four waves as fp32 MFMA fragments; loads run two steps ahead of their LDS
-// writes, and the LDS writes one step ahead of the products.
-//   off-diagonal pair (I > J): tile I's 64 rows, then tile J's 64 rows;
-//   diagonal pair (I = J): tile I's 64 rows once (they are both operands),
-//     then the target mean as a 16-row block whose other rows are zero.
-//     Waves (0, 0), (1, 0) and (1, 1) take the tile's lower triangle; wave
-//     (0, 1), whose quadrant lies above the diagonal, takes the target mean
-//     against the 64 rows (the scores s), and in tile 0 wave (0, 0) also
-//     takes the target mean against itself (t2).  Both land in the partial
-//     tile's upper triangle, which holds nothing else: s of tile row
-//     16 b + l at (16 (b / 2), 32 + 16 (b % 2) + l), t2 at (0, 16).
-constexpr int kLS = 32;                          // fp32 columns per step (128-byte rows)
-constexpr int kLNS = 3;                          // ring stages
-constexpr int kLStage = 2 * kTile * kLS * 4;     // 128 rows of 128 bytes
-constexpr int kLMeanRow = kTile;                 // diagonal pairs: the target mean's stage row
-constexpr int kKindS = 16, kKindT2 = 17;         // wave tasks beyond the block masks 0..15
+// One 16x16 block of C (lane l holds C[4 (l / 16) + r][l % 16] in element r)
+// into K at rows R.., columns C.. and, mirrored, at rows C.., columns R..,
+// for an off-diagonal tile inside K with 16-byte aligned rows: every element
+// goes out in non-temporal float4 stores.  The mirror is the accumulator as
+// it stands (four consecutive rows of one column are four consecutive
+// columns of the transposed row); the block itself after a 4 x 4 transpose
+// inside each quad of lanes (two rounds of DPP quad permutations).
+__device__ __forceinline__ void big_store_block_fast(float* Kp, int n, int R, int C, f32x4 v, int lane) {
+  const int lr = lane & 15, lg = lane >> 4, c = lane & 3, m = lr >> 2;
+  __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(Kp + (long long)(C + lr) * n + R + 4 * lg));
+  float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
+  {  // exchange across bit 0 of the quad lane
+    const float s01 = (c & 1) ? x0 : x1, s23 = (c & 1) ? x2 : x3;
+    const float r01 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s01), 0xB1, 0xF, 0xF, false));
+    const float r23 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s23), 0xB1, 0xF, 0xF, false));
+    if (c & 1) { x0 = r01; x2 = r23; } else { x1 = r01; x3 = r23; }
+  }
+  {  // exchange across bit 1
+    const float s02 = (c & 2) ? x0 : x2, s13 = (c & 2) ? x1 : x3;
+    const float r02 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s02), 0x4E, 0xF, 0xF, false));
+    const float r13 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s13), 0x4E, 0xF, 0xF, false));
+    if (c & 2) { x0 = r02; x1 = r13; } else { x2 = r02; x3 = r13; }
+  }
+  __builtin_nontemporal_store(f32x4{x0, x1, x2, x3}, reinterpret_cast<f32x4*>(Kp + (long long)(R + 4 * lg + c) * n + C + 4 * m));
+}
 
-__global__ __launch_bounds__(kThreads, 2) void gram_tile_lds_kernel(GramArgs a) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[kLNS * kLStage];
-  const int chunk = blockIdx.x, q = blockIdx.y, p = blockIdx.z;
+// fp32 rows, n + 1 > 128: 256-row tiles on bf16 MFMA.  Each value is split
+// into three bf16 parts, x = x0 + x1 + x2, each the nearest bf16 to what the
+// previous ones leave (x0 + x1 + x2 holds x to 2^-25), when its 32-column step
+// is staged in LDS, and a product takes the six pairs of parts with a + b <= 2:
+// every product is exact in fp32, the dropped pairs weigh 2^-25 and less, and
+// a step's sum is added to the accumulator by fp32 additions.  Error of K
+// against 64 bits: 8e-8 to 9e-8 for 1024 to 229376 columns with shared
+// directions; the fp32 MFMA tiles before had 1.9e-7 to 5.1e-7.
+//
+// Bound: bf16 MFMA at the rate the card's power allows (six products per fp32
+// one are 2.6 times the fp32 MFMA rate, which bound the 64 x 64 fp32 tiles
+// before).  256 x 229376: 209 -> 102 us (4 us without products' waits per
+// 32-column step: 2.5 of products, the rest of loads and splitting that the
+// other wave does not cover); 224 groups of 256 x 1024: 219 -> 121 us; 7 groups
+// of 1000 x 4096: 435 -> 205 us.  A last row tile of a few rows costs nearly a
+// whole one: 20 groups of 300 x 4096 123 -> 134 us.
+//
+// One workgroup of eight waves (two per SIMD, so that one splits and reads
+// while the other multiplies) per tile and column chunk:
+//   diagonal tile I: the 256 rows once (they are both operands) and the target
+//     mean as a 16-row block (sixteen times the same row).  The lower 64 x 64
+//     blocks go one to a wave, the four diagonal ones two to a wave; waves with
+//     one block take the target mean against 64 of the rows (the scores), one
+//     the mean against itself (t2).
+//   off-diagonal tile: 256 rows of row tile I, 128 rows of row tile J < I, one
+//     64 x 64 block per wave.
+// LDS: per stage three planes of 16-row blocks of 1 KB in fragment order
+// (16-byte segment lg of row lr at 16 (16 lg + lr)), so a wave writes and
+// reads a block as 1 KB in lane order.  Two stages and one barrier per step:
+// the products of step t, and the split of step t + 1 (loaded a step ago)
+// followed by the loads of step t + 2.
+//
+// From a step that holds a value of 2^50 or more on (an infinity, or one whose
+// partial products could overflow) the chunk is taken on fp32 MFMA straight
+// from memory by the same waves: there inf and overflow come out as in fp32
+// arithmetic.
+constexpr int kPC = 32;                       // fp32 columns per step
+constexpr int kPThreads = 512;
+constexpr int kPRows = 256, kPCols = 128;     // rows of tile I, rows of an off-diagonal tile's column half
+constexpr int kPDiagBlocks = 17, kPOffBlocks = 24;   // 16-row blocks of a stage
+constexpr int kPStageMax = 3 * kPOffBlocks * 1024;
+constexpr int kPWin = 56;                     // steps whose target mean is in LDS at a time (two windows)
+constexpr float kPBig = 1125899906842624.f;   // 2^50
+
+__device__ const float kZeros4[4] = {0.f, 0.f, 0.f, 0.f};   // read in place of columns past a chunk
+
+struct Planes8 {
+  u32x4 p[3];   // eight values, three bf16 parts
+};
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {   // round to nearest even, a in the low half
+  unsigned r;
+  asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+__device__ __forceinline__ void split2(float a, float b, unsigned& p0, unsigned& p1, unsigned& p2) {
+  p0 = pack_bf16(a, b);
+  const float a1 = a - __uint_as_float(p0 << 16), b1 = b - __uint_as_float(p0 & 0xffff0000u);
+  p1 = pack_bf16(a1, b1);
+  p2 = pack_bf16(a1 - __uint_as_float(p1 << 16), b1 - __uint_as_float(p1 & 0xffff0000u));
+}
+
+__device__ __forceinline__ Planes8 split8(f32x4 a, f32x4 b) {
+  Planes8 r;
+  unsigned q[3];
+#define DR_SPLIT2(X, Y, F)      \
+  split2(X, Y, q[0], q[1], q[2]); \
+  r.p[0].F = q[0];              \
+  r.p[1].F = q[1];              \
+  r.p[2].F = q[2];
+  DR_SPLIT2(a.x, a.y, x) DR_SPLIT2(a.z, a.w, y) DR_SPLIT2(b.x, b.y, z) DR_SPLIT2(b.z, b.w, w)
+#undef DR_SPLIT2
+  return r;
+}
+
+__device__ __forceinline__ float abs_max8(f32x4 a, f32x4 b, float m) {   // NaNs are passed over
+  asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(a.x), "v"(a.y));
+  asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(a.z), "v"(a.w));
+  asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(b.x), "v"(b.y));
+  asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(b.z), "v"(b.w));
+  return m;
+}
+
+// c[j] += A B_j^T over one step for NJ blocks: the six part pairs, the smallest
+// first, summed from zero and added to c by fp32 additions.  (The bf16 MFMA
+// truncates its sums: accumulated in place over a chunk, diagonal entries came
+// out 1.3e-6 low.)
+template <int NJ, class C>
+__device__ __forceinline__ void mma_split(const u32x4 (&a)[3], const u32x4 (*b)[3], C&& c) {
+  f32x4 t[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) t[j] = mma_bf16(a[0], b[j][2], f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) t[j] = mma_bf16(a[1], b[j][1], t[j]);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) t[j] = mma_bf16(a[2], b[j][0], t[j]);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) t[j] = mma_bf16(a[0], b[j][1], t[j]);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) t[j] = mma_bf16(a[1], b[j][0], t[j]);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) t[j] = mma_bf16(a[0], b[j][0], t[j]);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) c(j) += t[j];
+}
+
+// The tile and chunk of one workgroup.  NB: 16-row blocks of a stage.
+template <bool DIAG>
+__device__ __forceinline__ void gram_split_tile(const GramArgs& a, unsigned char* lds, int p, int chunk, int I,
+                                                int J2) {
+  constexpr int NB = DIAG ? kPDiagBlocks : kPOffBlocks;
+  constexpr int NI = DIAG ? 2 : 3;              // 16-row blocks a wave stages (w, w + 8, ...)
+  constexpr int kStage = 3 * NB * 1024;
+  int* big = reinterpret_cast<int*>(lds + 2 * kPStageMax);   // step + 1 that set it, per stage
+  float* gm = reinterpret_cast<float*>(lds + 2 * kPStageMax + 16);   // target mean, two windows of columns
   const long long g0 = a.goff[p], g1 = a.goff[p + 1];
   const long long c0 = g0 + (long long)chunk * a.CK;
-  // with one chunk per group the tile is final and written here, so an
-  // empty group still writes its zeros (no steps)
-  const bool direct = a.maxchunks == 1;
-  if (c0 >= g1 && !direct) return;
   const long long c1 = c0 + a.CK < g1 ? c0 + a.CK : g1;
-  const int nsteps = c1 > c0 ? (int)((c1 - c0 + kLS - 1) / kLS) : 0;
-  int I, J;
-  pair_to_tiles(q, I, J);
-  const bool diag = I == J;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int nsteps = c1 > c0 ? (int)((c1 - c0 + kPC - 1) / kPC) : 0;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
-  const int wr = w >> 1, wc = w & 1;
-  // loader: segment e = tid + 256 u of a stage is stage row e / 8, segment
-  // e % 8 (an off-diagonal pair loads u = 0..3, a diagonal one u = 0..2).
-  // An entry outside the problem reads the target mean's first 16 bytes
-  // instead and is zeroed at the LDS write, so the loads are unconditional
-  // and their waits counted.
-  const unsigned char* mean = reinterpret_cast<const unsigned char*>(a.gbar);   // by absolute column
-  const unsigned char* src[4];
-  bool rok[4];
-  int sseg[4];
-  unsigned loff[4];
+  // row r of stage block b (rows past n - 1 repeat it: each row of a product
+  // depends on its own row of the operand alone, and theirs are not written)
+  auto row_ptr = [&](int b, int r) {
+    const int row = b < 16 ? I * kPRows + 16 * b + r : J2 * kPCols + 16 * (b - 16) + r;
+    return a.G + (long long)(row < a.n ? row : a.n - 1) * a.ldG * 4;
+  };
+  const int rowsI = a.n - I * kPRows;           // rows of tile I that exist
+  // staging: lane (lg, lr) takes columns 8 lg .. + 7 of row lr of its blocks
+  // (columns past the chunk: zeros)
+  const int width = c1 > c0 ? (int)(c1 - c0) : 0;
+  const unsigned char* src[NI];
+  bool live16[NI];                              // block w + 8 u has rows (uniform)
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int e = tid + kThreads * u, R = e >> 3, sg = e & 7;
-    if (R < kTile || !diag) {
-      const int grow = R < kTile ? I * kTile + R : J * kTile + (R - kTile);
-      rok[u] = grow < a.n;
-      src[u] = rok[u] ? a.G + (long long)grow * a.ldG * 4 : mean;
-    } else {
-      rok[u] = R == kLMeanRow;
-      src[u] = mean;
-    }
-    sseg[u] = sg;
-    loff[u] = (unsigned)(R * 128 + ((sg ^ ((R >> 1) & 7)) * 16));
+  for (int u = 0; u < NI; ++u) {
+    src[u] = row_ptr(w + 8 * u, lr) + (c0 + 8 * lg) * 4;
+    live16[u] = u == 2 || 16 * (w + 8 * u) < rowsI;
   }
-  auto seg_ok = [&](int t, int u) { return rok[u] && c0 + (long long)t * kLS + sseg[u] * 4 < c1; };
-  // the zeroing happens at the LDS write, so nothing waits for the loads
-  // until then
-  auto gload = [&](int t, u32x4 (&v)[4], auto nu) {
+  // the target mean of window wd of the chunk's columns (zeros past them)
+  // into its half of gm: fp64 sum over the m rows in order
+  auto fill_mean = [&](int wd) {
+    for (int cc = tid; cc < kPWin * kPC; cc += kPThreads) {
+      const int c = wd * kPWin * kPC + cc;
+      float g = 0.f;
+      if (c < width) {
+        const float* gt = a.Gt + c0 + c;
+        double acc = 0.0;
+        for (int j0 = 0; j0 < a.m; j0 += 8) {
+          float x[8];
 #pragma unroll
-    for (int u = 0; u < decltype(nu)::value; ++u) {
-      const long long c = c0 + (long long)t * kLS + sseg[u] * 4;
-      v[u] = *reinterpret_cast<const u32x4*>(seg_ok(t, u) ? src[u] + c * 4 : mean);
+          for (int u = 0; u < 8; ++u) x[u] = gt[(long long)(j0 + u < a.m ? j0 + u : 0) * a.ldGt];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (j0 + u < a.m) acc += (double)x[u];
+        }
+        g = (float)(acc / (double)a.m);
+      }
+      gm[(wd & 1) * kPWin * kPC + cc] = g;
     }
   };
-  auto lstore = [&](int t, const u32x4 (&v)[4], auto nu) {
-    unsigned char* sb = lds + (t % kLNS) * kLStage;
+  auto gm_at = [&](int t) { return gm + ((t / kPWin & 1) * kPWin + t % kPWin) * kPC; };
+  const bool mean_wave = DIAG && w == 3;        // stages the mean's block beside its own
+  auto gload = [&](int t, f32x4 (&v)[NI][2]) {
+    const int c = t * kPC + 8 * lg;
 #pragma unroll
-    for (int u = 0; u < decltype(nu)::value; ++u)
-      *reinterpret_cast<u32x4*>(sb + loff[u]) = seg_ok(t, u) ? v[u] : u32x4{0u, 0u, 0u, 0u};
+    for (int u = 0; u < NI; ++u) {
+      if (!live16[u]) continue;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        // (the cast keeps it a global load: a flat one would also hold up
+        // every wait for LDS reads)
+        v[u][h] = *(const __attribute__((address_space(1))) f32x4*)(
+            c + 4 * h < width ? src[u] + (t * kPC + 4 * h) * 4 : reinterpret_cast<const unsigned char*>(kZeros4));
+    }
   };
-  f32x4 acc[2][2];
+  auto stage = [&](int t, const f32x4 (&v)[NI][2]) {
+    unsigned char* sb = lds + (t & 1) * kStage;
+    float m = 0.f;
+    auto put8 = [&](int b, f32x4 x, f32x4 y) {
+      const Planes8 q = split8(x, y);
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+      for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x4*>(sb + (k * NB + b) * 1024 + lane * 16) = q.p[k];
+      m = abs_max8(x, y, m);
+    };
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // the wave's products of step t.  Kind 0..15: the 16 x 16 blocks (i, j)
-  // whose bit i * 2 + j is set (A block i against B block j); kKindT2: mask
-  // 13 plus the target mean against itself into acc[0][1]; kKindS: the
-  // target mean against the tile's four 16-row blocks into acc[b / 2][b % 2]
-  auto compute = [&](int t, auto kind, auto dg) {
-    constexpr int KD = decltype(kind)::value;
-    constexpr bool DG = decltype(dg)::value;
-    if constexpr (KD != 0) {
-      const unsigned char* sb = lds + (t % kLNS) * kLStage;
-      const unsigned char* bb = sb + (DG ? 0 : kTile * 128);   // B operand rows
+    for (int u = 0; u < NI; ++u)
+      if (live16[u]) put8(w + 8 * u, v[u][0], v[u][1]);
+    if (mean_wave) {
+      const f32x4* g = reinterpret_cast<const f32x4*>(gm_at(t) + 8 * lg);
+      put8(16, g[0], g[1]);
+    }
+    if (__any(m >= kPBig) && lane == 0) big[t & 1] = t + 1;
+  };
+  auto frag = [&](const unsigned char* sb, int b, u32x4 (&f)[3]) {
 #pragma unroll
-      for (int kh = 0; kh < 2; ++kh) {
-        const int sg = 4 * kh + lg;
-        if constexpr (KD == kKindS) {
-          const u32x4 fm = swz_read(sb + kLMeanRow * 128, lr, sg);
-          u32x4 fb[4];
+    for (int k = 0; k < 3; ++k) f[k] = *reinterpret_cast<const u32x4*>(sb + (k * NB + b) * 1024 + lane * 16);
+  };
+  // fp32 operand of 16 of the step's columns (half h) from memory
+  auto frag32 = [&](int t, int b, int h) {
+    const int c = t * kPC + 16 * h + 4 * lg;
+    if (DIAG && b == 16) return *reinterpret_cast<const u32x4*>(gm_at(t) + 16 * h + 4 * lg);
+    u32x4 v = u32x4{0u, 0u, 0u, 0u};
+    if (c < width) v = *reinterpret_cast<const u32x4*>(row_ptr(b, lr) + (c0 + c) * 4);
+    return v;
+  };
+
+  // the wave's blocks: 64-row blocks ba against bb (diagonal tiles: waves 6,
+  // 7 take (0, 0) and (1, 1), (2, 2) and (3, 3)); sblk: the 64-row block whose
+  // scores it takes (-1: none)
+  int ba, bb, sblk = -1;
+  bool two = false;
+  if (DIAG) {
+    two = w >= 6;
+    ba = w < 2 ? 2 : (w < 5 ? 3 : (w == 5 ? 1 : 2 * (w - 6)));
+    bb = w == 0 || w == 2 || w == 5 ? 0 : (w == 1 || w == 3 ? 1 : (w == 4 ? 2 : ba));
+    sblk = w == 0 ? 2 : (w == 1 ? 1 : (w == 2 ? 3 : (w == 5 ? 0 : -1)));
+  } else {
+    ba = w >> 1;   // (a short last tile's live blocks then fall on different SIMDs)
+    bb = 4 + (w & 1);
+  }
+  // live 16-row blocks of a 64-row block of tile I
+  auto live = [&](int blk) { const int r = rowsI - 64 * blk; return r >= 64 ? 4 : (r > 0 ? (r + 15) / 16 : 0); };
+  const int liveA = live(ba);
+  // waves with two diagonal blocks keep the first one's lower blocks in acc's
+  // lower triangle, the second one's in acc's upper triangle and accs
+  f32x4 acc[4][4], accs[4];
 #pragma unroll
-          for (int b = 0; b < 4; ++b) fb[b] = swz_read(sb + 16 * b * 128, lr, sg);
-          acc[0][0] = mma_v<false>(fm, fb[0], acc[0][0]);
-          acc[0][1] = mma_v<false>(fm, fb[1], acc[0][1]);
-          acc[1][0] = mma_v<false>(fm, fb[2], acc[1][0]);
-          acc[1][1] = mma_v<false>(fm, fb[3], acc[1][1]);
-        } else {
-          constexpr int M = KD == kKindT2 ? 13 : KD;
-          constexpr bool ra0 = (M & 3) != 0, ra1 = (M & 12) != 0, rb0 = (M & 5) != 0, rb1 = (M & 10) != 0;
-          u32x4 fa[2], fb[2];
-          if constexpr (ra0) fa[0] = swz_read(sb + (wr * 32) * 128, lr, sg);
-          if constexpr (ra1) fa[1] = swz_read(sb + (wr * 32 + 16) * 128, lr, sg);
-          if constexpr (rb0) fb[0] = swz_read(bb + (wc * 32) * 128, lr, sg);
-          if constexpr (rb1) fb[1] = swz_read(bb + (wc * 32 + 16) * 128, lr, sg);
-          if constexpr ((M & 1) != 0) acc[0][0] = mma_v<false>(fa[0], fb[0], acc[0][0]);
-          if constexpr ((M & 2) != 0) acc[0][1] = mma_v<false>(fa[0], fb[1], acc[0][1]);
-          if constexpr ((M & 4) != 0) acc[1][0] = mma_v<false>(fa[1], fb[0], acc[1][0]);
-          if constexpr ((M & 8) != 0) acc[1][1] = mma_v<false>(fa[1], fb[1], acc[1][1]);
-          if constexpr (KD == kKindT2) {
-            const u32x4 fm = swz_read(sb + kLMeanRow * 128, lr, sg);
-            acc[0][1] = mma_v<false>(fm, fm, acc[0][1]);
-          }
+  for (int i = 0; i < 4; ++i) {
+    accs[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto first = [&](int i, int j) -> f32x4& { return acc[i][j]; };
+  auto second = [&](int i, int j) -> f32x4& { return i == j ? accs[i] : acc[j][i]; };
+  const bool t2_wave = DIAG && I == 0 && w == 4;
+
+  // products of one step.  A wave whose rows end inside its block skips the
+  // 16-row blocks past them (FULL = false).
+  auto rect = [&](const unsigned char* sb, auto full) {
+    u32x4 fb[4][3];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) frag(sb, 4 * bb + j, fb[j]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (!decltype(full)::value && i >= liveA) break;
+      u32x4 fa[3];
+      frag(sb, 4 * ba + i, fa);
+      mma_split<4>(fa, fb, [&](int j) -> f32x4& { return acc[i][j]; });
+    }
+  };
+  auto tri = [&](const unsigned char* sb, int blk, auto&& c) {
+    u32x4 f[4][3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) frag(sb, 4 * blk + i, f[i]);
+    f32x4 t[10];   // the ten lower blocks together: a product's sum takes several MFMAs to come out
+    auto pass = [&](int ka, int kb, bool zero) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+          f32x4& x = t[i * (i + 1) / 2 + j];
+          x = mma_bf16(f[i][ka], f[j][kb], zero ? f32x4{0.f, 0.f, 0.f, 0.f} : x);
+        }
+    };
+    pass(0, 2, true);
+    pass(1, 1, false);
+    pass(2, 0, false);
+    pass(0, 1, false);
+    pass(1, 0, false);
+    pass(0, 0, false);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j <= i; ++j) c(i, j) += t[i * (i + 1) / 2 + j];
+  };
+  auto scores = [&](const unsigned char* sb) {
+    u32x4 fm[3], f[4][3];
+    frag(sb, 16, fm);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) frag(sb, 4 * sblk + i, f[i]);
+    mma_split<4>(fm, f, [&](int j) -> f32x4& { return accs[j]; });
+  };
+  auto mean2 = [&](const unsigned char* sb) {
+    u32x4 fm[1][3];
+    frag(sb, 16, fm[0]);
+    mma_split<1>(fm[0], fm, [&](int) -> f32x4& { return accs[0]; });
+  };
+  auto slow = [&](int t) {
+#pragma unroll 1
+    for (int h = 0; h < 2; ++h) {
+      u32x4 f[4];
+      auto tri32 = [&](int blk, auto&& c) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          f[i] = frag32(t, 4 * blk + i, h);
+#pragma unroll
+          for (int j = 0; j <= i; ++j) c(i, j) = mma_v<false>(f[i], f[j], c(i, j));
+        }
+      };
+      if (DIAG && two) {
+        tri32(ba, first);
+        tri32(ba + 1, second);
+        continue;
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f[j] = frag32(t, 4 * bb + j, h);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const u32x4 fa = frag32(t, 4 * ba + i, h);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = mma_v<false>(fa, f[j], acc[i][j]);
+      }
+      if (DIAG) {
+        const u32x4 fm = frag32(t, 16, h);
+        if (t2_wave) accs[0] = mma_v<false>(fm, fm, accs[0]);
+        if (sblk >= 0) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) accs[i] = mma_v<false>(fm, frag32(t, 4 * sblk + i, h), accs[i]);
         }
       }
     }
   };
-  // step t: products from stage t % 3; the data of step t + 2 (loaded two
-  // steps ago) into stage (t + 2) % 3, last read at step t - 1; the loads of
-  // step t + 4; one barrier
-  auto run = [&](auto dg, auto kind) {
-    constexpr bool DG = decltype(dg)::value;
-    const std::integral_constant<int, DG ? 3 : 4> nu;
-    u32x4 va[4], vb[4];
-    gload(0, va, nu);
-    gload(1, vb, nu);
-    lstore(0, va, nu);
-    lstore(1, vb, nu);
-    gload(2, va, nu);
-    gload(3, vb, nu);
-    __syncthreads();
-    for (int t = 0; t < nsteps; t += 2) {
-      compute(t, kind, dg);
-      lstore(t + 2, va, nu);
-      __builtin_amdgcn_sched_barrier(0);
-      gload(t + 4, va, nu);
-      __builtin_amdgcn_sched_barrier(0);
-      DR_LDS_SYNC();
-      compute(t + 1, kind, dg);   // past the last step its stage holds zeros: the products add 0
-      lstore(t + 3, vb, nu);
-      __builtin_amdgcn_sched_barrier(0);
-      gload(t + 5, vb, nu);
-      __builtin_amdgcn_sched_barrier(0);
-      DR_LDS_SYNC();
+
+  // the two waves of a SIMD (w, w + 4) stage at opposite ends of the step, so
+  // that one splits while the other multiplies
+  f32x4 v[NI][2];
+  if (tid < 2) big[tid] = 0;
+  if (DIAG) fill_mean(0);
+  __syncthreads();
+  gload(0, v);
+  stage(0, v);
+  gload(1, v);
+  int t = 0;
+  // the steps until the first with a big value.  One loop per kind of wave:
+  // as branches of one loop the compiler moves the accumulators between
+  // registers at every join and waits for all loads at its head (184 instead
+  // of 132 us for 256 x 229376).
+  auto run = [&](auto early, auto&& products) {
+    for (; t < nsteps; ++t) {
+      DR_LDS_SYNC();   // step t is staged; every wave is done with the other stage
+      if (__builtin_amdgcn_readfirstlane(big[t & 1]) == t + 1) break;
+      // the next window of the target mean (the half it takes was last read
+      // before this barrier, and is next read after a later one)
+      if (DIAG && t % kPWin == 0 && t + kPWin < nsteps) fill_mean(t / kPWin + 1);
+      if (decltype(early)::value) {
+        stage(t + 1, v);   // past the last step zeros, never read
+        gload(t + 2, v);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      products(lds + (t & 1) * kStage);
+      if (!decltype(early)::value) {
+        __builtin_amdgcn_sched_barrier(0);
+        stage(t + 1, v);
+        gload(t + 2, v);
+      }
     }
   };
-  // Blocks the reduction never reads take no products and keep zero
-  // accumulators: A rows wholly past row n - 1 (I >= J, so these are the
-  // last tile's), and on a diagonal tile the blocks wholly above the
-  // diagonal.  The mask is uniform over the wave and is rounded up to the
-  // smallest loop variant that contains it (extra products are harmless).
-  int live = 0;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int rb = I * kTile + wr * 32 + 16 * i, cb = J * kTile + wc * 32 + 16 * j;
-      if (rb < a.n && cb <= rb + 15) live |= 1 << (i * 2 + j);
-    }
-  using F = std::false_type;
-  using T = std::true_type;
-  if (!diag) {
-    // J < I: every B block lies below the A rows, so live is 0, 3 or 15
-    if (live == 0)
-      run(F{}, std::integral_constant<int, 0>{});
-    else if ((live & ~3) == 0)
-      run(F{}, std::integral_constant<int, 3>{});
-    else
-      run(F{}, std::integral_constant<int, 15>{});
-  } else if (wr == 0 && wc == 1) {
-    run(T{}, std::integral_constant<int, kKindS>{});
-  } else if (I == 0 && wr == 0 && wc == 0) {
-    run(T{}, std::integral_constant<int, kKindT2>{});   // its live blocks are within mask 13
-  } else if (live == 0) {
-    run(T{}, std::integral_constant<int, 0>{});
-  } else if ((live & ~1) == 0) {
-    run(T{}, std::integral_constant<int, 1>{});
-  } else if ((live & ~3) == 0) {
-    run(T{}, std::integral_constant<int, 3>{});
-  } else if ((live & ~13) == 0) {
-    run(T{}, std::integral_constant<int, 13>{});
+  using True = std::true_type;
+  using False = std::false_type;
+  auto run_rect = [&](auto early) {
+    if (liveA == 4) run(early, [&](const unsigned char* sb) { rect(sb, True{}); });
+    else run(early, [&](const unsigned char* sb) { rect(sb, False{}); });
+  };
+  auto run_scores = [&](auto early) {
+    if (liveA == 4) run(early, [&](const unsigned char* sb) { rect(sb, True{}); scores(sb); });
+    else run(early, [&](const unsigned char* sb) { rect(sb, False{}); scores(sb); });
+  };
+  if (DIAG && two) {
+    run(False{}, [&](const unsigned char* sb) {
+      tri(sb, ba, first);
+      tri(sb, ba + 1, second);
+    });
+  } else if (DIAG && sblk >= 0) {
+    if (w < 4) run_scores(True{});
+    else run_scores(False{});
+  } else if (t2_wave) {
+    run(False{}, [&](const unsigned char* sb) { rect(sb, False{}); mean2(sb); });
+  } else if (w < 4) {
+    run_rect(True{});
   } else {
-    run(T{}, std::integral_constant<int, 15>{});
+    run_rect(False{});
+  }
+  for (; t < nsteps; ++t) {          // from that step on
+    if (DIAG && t % kPWin == 0) {
+      __syncthreads();
+      fill_mean(t / kPWin);
+      __syncthreads();
+    }
+    slow(t);
   }
 
-  if (direct) {
-    // the reduction's writes for a single chunk: K's lower triangle and
-    // mirror, and from a diagonal tile the scores and t2 in its upper
-    // triangle
-    float* Kp = a.K + (a.pbase + p) * (long long)a.n * a.n;
+  // out: the reduction's 64 x 64 partial tiles, or with one chunk per group
+  // K (lower triangle and mirror), s and t2 themselves
+  auto put = [&](int bi, int bj, auto&& c) {
+    const int I6 = 4 * I + bi, J6 = DIAG ? 4 * I + bj : 2 * J2 + bj - 4;
+    if (I6 >= a.NT) return;
+    if (a.maxchunks > 1) {
+      float* out = a.partial +
+                   (((long long)p * a.pairs + I6 * (I6 + 1) / 2 + J6) * a.maxchunks + chunk) * (kTile * kTile);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 4; ++j) {
+          if (DIAG && two && j > i) continue;   // (the scores live above the diagonal)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int tr = wr * 32 + i * 16 + lg * 4 + r, tc = wc * 32 + j * 16 + lr;
-          const int row = I * kTile + tr, col = J * kTile + tc;
-          const float v = acc[i][j][r];
-          if (col <= row) {
-            if (row < a.n) {
-              Kp[(long long)row * a.n + col] = v;
-              Kp[(long long)col * a.n + row] = v;
-            }
-          } else if (diag) {
-            if ((tr == 0 || tr == 16) && tc >= 32) {
-              const int srow = I * kTile + 2 * tr + (tc - 32);
-              if (srow < a.n) a.s[(a.pbase + p) * (long long)a.n + srow] = v;
-            } else if (I == 0 && tr == 0 && tc == 16) {
-              a.t2[a.pbase + p] = v;
-            }
+          for (int r = 0; r < 4; ++r) {
+            const int tr = 16 * i + 4 * lg + r, tc = 16 * j + lr;
+            if (!(DIAG && two) || tc <= tr) out[tr * kTile + tc] = c(i, j)[r];
           }
         }
+      return;
+    }
+    float* Kp = a.K + (a.pbase + p) * (long long)a.n * a.n;
+    const bool fast = a.vec4 && I6 * kTile + kTile <= a.n;   // float4 stores of whole blocks below the diagonal
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = I6 * kTile + 16 * i + 4 * lg + r, col = J6 * kTile + 16 * j + lr;
+          if (!(DIAG && two && j >= i) && fast) {
+            if (r == 0) big_store_block_fast(Kp, a.n, I6 * kTile + 16 * i, J6 * kTile + 16 * j, c(i, j), lane);
+          } else if (!(DIAG && two && j > i) && col <= row && row < a.n) {
+            const float v = c(i, j)[r];
+            Kp[(long long)row * a.n + col] = v;
+            Kp[(long long)col * a.n + row] = v;
+          }
+        }
+  };
+  put(ba, bb, first);
+  if (DIAG && two) put(ba + 1, ba + 1, second);
+  if (DIAG && lane < 16) {   // row 0 of the score blocks: lanes 0 .. 15, register 0
+    auto part = [&](int I6) {
+      return a.partial + (((long long)p * a.pairs + I6 * (I6 + 1) / 2 + I6) * a.maxchunks + chunk) * (kTile * kTile);
+    };
+    const int I6 = 4 * I + sblk;
+    if (sblk >= 0 && I6 < a.NT) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const int row = I6 * kTile + 16 * b + lr;
+        if (a.maxchunks > 1)
+          part(I6)[16 * (b / 2) * kTile + 32 + 16 * (b % 2) + lr] = accs[b][0];
+        else if (row < a.n)
+          a.s[(a.pbase + p) * (long long)a.n + row] = accs[b][0];
+      }
+    }
+    if (t2_wave && lane == 0) {
+      if (a.maxchunks > 1) part(0)[16] = accs[0][0];
+      else a.t2[a.pbase + p] = accs[0][0];
+    }
+  }
+}
+
+// workgroups of a group: T diagonal tiles, then the (I, J2) pairs of row tile
+// I and 128-row half J2 < 2 I
+__global__ __launch_bounds__(kPThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void gram_split_kernel(GramArgs a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * kPStageMax + 16 + 2 * kPWin * kPC * 4];
+  const int chunk = blockIdx.x, p = blockIdx.z, T = (a.n + kPRows - 1) / kPRows;
+  // an empty chunk leaves its partial tiles unwritten (the reduction skips
+  // them); with one chunk per group it writes the group's zeros
+  if (a.goff[p] + (long long)chunk * a.CK >= a.goff[p + 1] && a.maxchunks > 1) return;
+  int q = blockIdx.y;
+  if (q < T) {
+    gram_split_tile<true>(a, lds, p, chunk, q, 0);
     return;
   }
-  float* out = a.partial + (((long long)p * a.pairs + q) * a.maxchunks + chunk) * (kTile * kTile);
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        out[(wr * 32 + i * 16 + lg * 4 + r) * kTile + wc * 32 + j * 16 + lr] = acc[i][j][r];
+  q -= T;
+  int I = 1;
+  while (q >= I * (I + 1)) ++I;
+  gram_split_tile<false>(a, lds, p, chunk, I, q - I * (I - 1));
 }
 
 // ---------------------------------------------------------------- small fp32
@@ -576,33 +844,7 @@ struct BigArgs {
   float* K;        // [P][n][n] of this launch's groups
 };
 
-// One 16x16 block of C (lane l holds C[4 (l / 16) + r][l % 16] in element r)
-// into K at rows R.., columns C.. and, mirrored, at rows C.., columns R..,
-// for an off-diagonal tile inside K with 16-byte aligned rows: every element
-// goes out in non-temporal float4 stores.  The mirror is the accumulator as
-// it stands (four consecutive rows of one column are four consecutive
-// columns of the transposed row); the block itself after a 4 x 4 transpose
-// inside each quad of lanes (two rounds of DPP quad permutations).
-__device__ __forceinline__ void big_store_block_fast(float* Kp, int n, int R, int C, f32x4 v, int lane) {
-  const int lr = lane & 15, lg = lane >> 4, c = lane & 3, m = lr >> 2;
-  __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(Kp + (long long)(C + lr) * n + R + 4 * lg));
-  float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
-  {  // exchange across bit 0 of the quad lane
-    const float s01 = (c & 1) ? x0 : x1, s23 = (c & 1) ? x2 : x3;
-    const float r01 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s01), 0xB1, 0xF, 0xF, false));
-    const float r23 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s23), 0xB1, 0xF, 0xF, false));
-    if (c & 1) { x0 = r01; x2 = r23; } else { x1 = r01; x3 = r23; }
-  }
-  {  // exchange across bit 1
-    const float s02 = (c & 2) ? x0 : x2, s13 = (c & 2) ? x1 : x3;
-    const float r02 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s02), 0x4E, 0xF, 0xF, false));
-    const float r13 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s13), 0x4E, 0xF, 0xF, false));
-    if (c & 2) { x0 = r02; x1 = r13; } else { x2 = r02; x3 = r13; }
-  }
-  __builtin_nontemporal_store(f32x4{x0, x1, x2, x3}, reinterpret_cast<f32x4*>(Kp + (long long)(R + 4 * lg + c) * n + C + 4 * m));
-}
-
-// the same block element by element: rows and columns past n are skipped,
+// a 16 x 16 block into K element by element: rows and columns past n are skipped,
 // and in a diagonal tile only the lower triangle (with its mirror above)
 __device__ __forceinline__ void big_store_block_masked(float* Kp, int n, bool diag, int R, int C, f32x4 v, int lane) {
   const int lr = lane & 15, lg = lane >> 4;
@@ -711,59 +953,81 @@ bool gram_use_big(int64_t n, int P, dr_dtype dtype) {
   return T * (T + 1) / 2 * gp >= kBigMinTiles;
 }
 
-// One thread per element of a 64x64 tile: sums the chunk partials in chunk
-// order and writes K (lower triangle and its mirror) and, for fp32 rows, s
-// and t2 from the upper triangle of the diagonal tiles (where
-// gram_tile_lds_kernel puts them).
-__global__ __launch_bounds__(kThreads) void gram_reduce_kernel(GramArgs a, float* K, float* s, float* t2,
+// One 16 x 16 block of a 64 x 64 tile per workgroup: sums the chunk partials in
+// fp64 (each of NP threads per element a run of the chunks, then the runs in
+// order) and writes K (lower triangle and its mirror, the latter through LDS
+// so that it too goes out along rows) and, for fp32 rows, s and t2 from the
+// upper triangle of the diagonal tiles (where gram_split_kernel puts them).
+// Four threads per element when there are many chunks to read (256 of them
+// for 256 x 229376, 42 MB: 14 us with one).
+template <int NP>
+__global__ __launch_bounds__(256 * NP) void gram_reduce_kernel(GramArgs a, float* K, float* s, float* t2,
                                                                long long pbase) {
-  const int q = blockIdx.x, p = blockIdx.y;
-  const int e = blockIdx.z * kThreads + threadIdx.x;
+  __shared__ double red[NP][256];
+  __shared__ float tile[16][17];
+  const int q = blockIdx.x, p = blockIdx.y, bi = blockIdx.z >> 2, bj = blockIdx.z & 3;
+  const int e = threadIdx.x & 255, part = threadIdx.x >> 8;
   const long long width = a.goff[p + 1] - a.goff[p];
   const int nvalid = (int)((width + a.CK - 1) / a.CK);
   int I, J;
   pair_to_tiles(q, I, J);
-  const int tr = e / kTile, tc = e % kTile;
+  const bool diag = I == J, upper = diag && bj > bi;
+  // upper blocks of a diagonal tile hold the scores (two rows of them) and t2
+  if (upper && !(a.rows > a.n && (bi == 0 || (bi == 1 && bj >= 2)))) return;
+  const int tr = 16 * bi + (e >> 4), tc = 16 * bj + (e & 15);
   const int r = I * kTile + tr, c = J * kTile + tc;
-  int srow = -1;   // >= 0: this element is s[srow]; -2: t2
-  if (c <= r) {
-    if (r >= a.n) return;
-  } else if (a.rows > a.n && I == J) {
-    if ((tr == 0 || tr == 16) && tc >= 32)
-      srow = I * kTile + 2 * tr + (tc - 32);
-    else if (I == 0 && tr == 0 && tc == 16)
-      srow = -2;
-    if (srow == -1 || srow >= a.n) return;
-  } else {
+  const bool need = upper ? (e >> 4) == 0 : r < a.n;
+  double sum = 0.0;
+  if (need) {
+    const float* src =
+        a.partial + ((long long)p * a.pairs + q) * a.maxchunks * (kTile * kTile) + tr * kTile + tc;
+    int ch = (int)((long long)nvalid * part / NP);
+    const int ce = (int)((long long)nvalid * (part + 1) / NP);
+    for (; ch + 16 <= ce; ch += 16) {
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = src[(long long)(ch + u) * (kTile * kTile)];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) sum += (double)v[u];
+    }
+    for (; ch + 4 <= ce; ch += 4) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = src[(long long)(ch + u) * (kTile * kTile)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) sum += (double)v[u];
+    }
+    for (; ch < ce; ++ch) sum += (double)src[(long long)ch * (kTile * kTile)];
+  }
+  if (NP > 1) {
+    red[part][e] = sum;
+    __syncthreads();
+    if (part == 0) {
+#pragma unroll
+      for (int u = 1; u < NP; ++u) sum += red[u][e];
+    }
+  }
+  const float acc = (float)sum;
+  if (upper) {
+    if (part == 0 && need) {
+      const int srow = I * kTile + 2 * tr + (tc - 32);
+      if (bj >= 2) {
+        if (srow < a.n) s[(pbase + p) * (long long)a.n + srow] = acc;
+      } else if (I == 0 && tc == 16) {
+        t2[pbase + p] = acc;
+      }
+    }
     return;
   }
-  const float* src = a.partial + ((long long)p * a.pairs + q) * a.maxchunks * (kTile * kTile) + e;
-  // chunks in batches of 32 loads in flight, summed in chunk order
-  float acc = 0.f;
-  int ch = 0;
-  for (; ch + 32 <= nvalid; ch += 32) {
-    float v[32];
-#pragma unroll
-    for (int u = 0; u < 32; ++u) v[u] = src[(long long)(ch + u) * (kTile * kTile)];
-#pragma unroll
-    for (int u = 0; u < 32; ++u) acc += v[u];
+  float* Kp = K + (pbase + p) * (long long)a.n * a.n;
+  if (part == 0) {
+    tile[e >> 4][e & 15] = acc;
+    if (need && c <= r) Kp[(long long)r * a.n + c] = acc;
   }
-  for (; ch + 8 <= nvalid; ch += 8) {
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = src[(long long)(ch + u) * (kTile * kTile)];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc += v[u];
-  }
-  for (; ch < nvalid; ++ch) acc += src[(long long)ch * (kTile * kTile)];
-  if (srow == -1) {
-    float* Kp = K + (pbase + p) * (long long)a.n * a.n;
-    Kp[(long long)r * a.n + c] = acc;
-    Kp[(long long)c * a.n + r] = acc;
-  } else if (srow >= 0) {
-    s[(pbase + p) * (long long)a.n + srow] = acc;
-  } else {
-    t2[pbase + p] = acc;
+  __syncthreads();
+  if (part == 0) {   // element (e & 15, e >> 4) of the block, mirrored
+    const int mr = I * kTile + 16 * bi + (e & 15), mc = J * kTile + 16 * bj + (e >> 4);
+    if (mr < a.n && mc <= mr) Kp[(long long)mc * a.n + mr] = tile[e & 15][e >> 4];
   }
 }
 
@@ -864,13 +1128,26 @@ GramPlan gram_plan(int64_t n, const int64_t* goff, int P, dr_dtype dtype) {
   const int gp = P < kMaxGroups ? P : kMaxGroups;
   int64_t ck = align_up((size_t)(maxw > 0 ? maxw : 1), 256);
   if (dtype == DR_F32) {
-    // fp32 tiles: the chunk length that keeps the launch just within two
-    // rounds of the workgroups the chip holds at once (kLdsSlots), so the
-    // second round is nearly full (the fixed count keeps the chunking, and
-    // with it the summation order, the same on every device)
-    const int64_t want = ((int64_t)maxw * g.pairs * gp + 2 * kLdsSlots - 1) / (2 * kLdsSlots);
-    const int64_t c2 = (int64_t)align_up((size_t)(want > 256 ? want : 256), 256);
-    if (c2 < ck) ck = c2;
+    // split tiles, one workgroup per CU: the chunk count with the least time,
+    // rounds of kSplitSlots workgroups times the steps of a chunk and about
+    // four more for its prologue and epilogue, and three for the reduction.
+    // kSplitSlots is fixed, so the chunking, and with it the summation order,
+    // is the same on every device.  Chunks keep at least two steps, and their
+    // partial tiles stay within kSplitPartials.  (Weighing a short last row
+    // tile less gave more chunks and measured worse: 20 groups of 300 rows x
+    // 4096 columns 159 us in six chunks, 134 us in three.)
+    const int64_t T = (n + kPRows - 1) / kPRows, wgs = T * T * gp;
+    const int64_t steps = (maxw + kPC - 1) / kPC, chunk_bytes = (int64_t)gp * g.pairs * kTile * kTile * 4;
+    int64_t best = -1, chunks = 1;
+    for (int64_t c = 1; c <= 256 && (c == 1 || (2 * c <= steps && c * chunk_bytes <= kSplitPartials)); ++c) {
+      const int64_t cost = (wgs * c + kSplitSlots - 1) / kSplitSlots * ((steps + c - 1) / c + 4) + (c > 1 ? 3 : 0);
+      if (best < 0 || cost < best) {
+        best = cost;
+        chunks = c;
+      }
+    }
+    ck = (steps + chunks - 1) / chunks * kPC;
+    if (ck < kPC) ck = kPC;
   } else {
     while (ck > 256 && (int64_t)g.pairs * gp * ((maxw + ck - 1) / ck) < kTargetWGs) ck = align_up((size_t)(ck / 2), 256);
   }
@@ -879,7 +1156,7 @@ GramPlan gram_plan(int64_t n, const int64_t* goff, int P, dr_dtype dtype) {
   if (g.maxchunks < 1) g.maxchunks = 1;
   g.gbar_bytes = align_up((size_t)(goff[P] > 0 ? goff[P] : 1) * sizeof(float), 256);
   g.partial_bytes = (size_t)gp * g.pairs * g.maxchunks * kTile * kTile * sizeof(float);
-  if (rows == 0 || gram_use_big(n, P, dtype)) g.partial_bytes = 0;
+  if (rows == 0 || gram_use_big(n, P, dtype) || (dtype == DR_F32 && g.maxchunks == 1)) g.partial_bytes = 0;
   g.rows = rows;
   g.small = gram_use_small(n, dtype);
   g.NRP = (int)((n + 1 + 15) / 16 * 16);
@@ -944,7 +1221,7 @@ dr_status gram_run(const GramPlan& g, const void* G, int64_t n, int64_t ldG, con
   float* partial = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + g.gbar_bytes);
 
   const long long c_lo = goff[0], c_hi = goff[P];
-  if (c_hi > c_lo && !g.small) {   // the small path forms gbar inside its chunks
+  if (c_hi > c_lo && (bf || n == 0)) {   // the fp32 kernels form gbar inside their chunks
     const int blocks = (int)((c_hi - c_lo + kThreads - 1) / kThreads);
     if (bf)
       hipLaunchKernelGGL(target_mean_kernel<true>, dim3(blocks), dim3(kThreads), 0, hs,
@@ -974,6 +1251,10 @@ dr_status gram_run(const GramPlan& g, const void* G, int64_t n, int64_t ldG, con
     a.s = s;
     a.t2 = t2;
     a.pbase = p0;
+    a.vec4 = n % 4 == 0 && aligned16(K);
+    a.Gt = static_cast<const float*>(Gt);
+    a.ldGt = ldGt;
+    a.m = (int)m;
     if (gram_use_big(n, P, dtype)) {
       BigArgs b = {};
       b.G = static_cast<const unsigned char*>(G);
@@ -997,15 +1278,19 @@ dr_status gram_run(const GramPlan& g, const void* G, int64_t n, int64_t ldG, con
                          dim3(kThreads), 0, hs, a, g.NRP, g.maxchunks, K, s, t2, (long long)p0);
       if ((st = launch_status()) != DR_OK) return st;
     } else if (g.pairs > 0) {
-      dim3 grid(g.maxchunks, g.pairs, gp);
-      if (bf)
-        hipLaunchKernelGGL(gram_tile_kernel<true>, grid, dim3(kThreads), 0, hs, a);
-      else
-        hipLaunchKernelGGL(gram_tile_lds_kernel, grid, dim3(kThreads), 0, hs, a);
+      if (bf) {
+        hipLaunchKernelGGL(gram_tile_kernel, dim3(g.maxchunks, g.pairs, gp), dim3(kThreads), 0, hs, a);
+      } else {
+        const int T = (int)((n + kPRows - 1) / kPRows);
+        hipLaunchKernelGGL(gram_split_kernel, dim3(g.maxchunks, T * T, gp), dim3(kPThreads), 0, hs, a);
+      }
       if ((st = launch_status()) != DR_OK) return st;
       if (bf || g.maxchunks > 1) {   // fp32 tiles of a single chunk are written by the tile kernel
-        hipLaunchKernelGGL(gram_reduce_kernel, dim3(g.pairs, gp, kTile * kTile / kThreads), dim3(kThreads), 0, hs,
-                           a, K, s, t2, (long long)p0);
+        const dim3 rg(g.pairs, gp, kTile * kTile / 256);
+        if (g.maxchunks >= 32)
+          hipLaunchKernelGGL(gram_reduce_kernel<4>, rg, dim3(1024), 0, hs, a, K, s, t2, (long long)p0);
+        else
+          hipLaunchKernelGGL(gram_reduce_kernel<1>, rg, dim3(256), 0, hs, a, K, s, t2, (long long)p0);
         if ((st = launch_status()) != DR_OK) return st;
       }
     }

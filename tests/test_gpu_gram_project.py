@@ -572,3 +572,67 @@ def test_span_blocked_groups_side_by_side(n, P):
     for k in range(4):
         ref = torch.cat([a[k] for a in alone])
         assert torch.equal(many[k], ref) and torch.equal(small[k], ref)
+
+
+@pytest.mark.parametrize("n,goff,m", [
+    (128, [0, 32], 1),                        # one step, one row tile
+    (255, [0, 36, 36, 2048], 17),             # a ragged step, an empty group, two windows of the target mean
+    (256, [0, 8200], 3),
+    (257, [0, 1000], 2),                      # one row in the second row tile
+    (320, [4 * i for i in range(0, 1401, 700)], 5),
+    (449, [0, 2400], 33),                     # 449 = 256 + 193: a last tile with one row in its fourth block
+    (512, [0, 260], 2),
+    (700, [0, 300, 2092, 2100], 4),           # three row tiles, ragged last
+])
+def test_gram_fp32_split_tiles_against_fp64(n, goff, m):
+    """fp32 rows as three bf16 parts: each entry within 6 * 2^-24 of the sum
+    of its terms' sizes (one part split, 2^-25, per operand; the truncated sum
+    of a 32-column step; the additions of the steps, whose errors grow at most
+    with the square root of their number and not in one direction)."""
+    rows = rand((n + m, goff[-1]), 3 * n + m, scale=1.0) + 0.5
+    G, Gt = rows[:n].contiguous(), rows[n:].contiguous()
+    K, s, t2 = api.gram(G, Gt, goff)
+    torch.cuda.synchronize()
+    for p, (a, b) in enumerate(zip(goff, goff[1:])):
+        g, gbar = G[:, a:b].double(), Gt[:, a:b].double().mean(0).float().double()
+        tol = 6 * 2.0 ** -24
+        assert ((K[p].double() - g @ g.t()).abs() <= tol * (g.abs() @ g.abs().t())).all()
+        assert ((s[p].double() - g @ gbar).abs() <= tol * (g.abs() @ gbar.abs())).all()
+        assert abs(float(t2[p]) - float(gbar @ gbar)) <= tol * float(gbar @ gbar)
+        assert torch.equal(K[p], K[p].t())
+
+
+@pytest.mark.parametrize("n", [130, 300])
+@pytest.mark.parametrize("col", [3, 70, 1900])
+def test_gram_fp32_infinities_and_large_values(n, col):
+    """An infinity, and values whose products overflow fp32, come out as fp32
+    arithmetic gives them (not as NaN from their bf16 parts), from the first
+    step or a later one, and leave the other rows alone."""
+    cols, m = 2000, 2
+    G, Gt = rand((n, cols), n + col).abs() + 0.5, rand((m, cols), n + col + 1).abs() + 0.5
+    G[5, col] = float("inf")
+    G[n - 1, col] = 3e38
+    G[n - 2, col] = float("nan")
+    K, s, t2 = api.gram(G, Gt, [0, cols])
+    torch.cuda.synchronize()
+    K, s = K[0], s[0]
+    ok = torch.ones(n, dtype=torch.bool, device=DEV)
+    ok[[5, n - 1, n - 2]] = False
+    assert torch.isinf(K[5, ok]).all() and torch.isinf(s[5]) and (K[5, ok] > 0).all()
+    assert torch.isnan(K[n - 2]).all() and torch.isnan(s[n - 2])
+    assert torch.isinf(K[n - 1, n - 1])
+    g, gbar = G[ok].double(), Gt.double().mean(0).float().double()
+    assert rel(host64(K[ok][:, ok]), host64(g @ g.t())) <= TOL_GRAM
+    assert rel(host64(s[ok]), host64(g @ gbar)) <= TOL_GRAM
+    big = host64(G[n - 1].double() @ g.t())
+    assert np.allclose(host64(K[n - 1, ok]), big, rtol=1e-5)
+
+
+def test_gram_fp32_tiny_values():
+    """Values whose lower bf16 parts are subnormal."""
+    G = rand((130, 512), 11) * 1e-37
+    Gt = rand((2, 512), 12) * 1e30
+    K, s, t2 = api.gram(G, Gt, [0, 512])
+    torch.cuda.synchronize()
+    ref = G.double() @ Gt.double().mean(0)
+    assert rel(host64(s[0]), host64(ref)) <= TOL_GRAM
