@@ -178,8 +178,8 @@ size_t dr_gram_workspace_size(int64_t n, int64_t m, const int64_t* goff, int P, 
  * routine); its first call on a device looks up that device's array.
  *   Returns DR_ERR_TOO_LARGE, before any HIP call, when
  *   dr_gram_workspace_size(n, m, goff, P, dtype) > DR_GRAM_NOALLOC_MAX_BYTES
- *   (the largest workload shape here needs 36 MiB: 256 fp32 rows over
- *   229376 columns in 224 groups; 24 MiB as one group).
+ *   (the largest workload shape here needs 41 MiB: 256 fp32 rows over
+ *   229376 columns as one group; 36 MiB in 224 groups).
  * All calls on one GPU share its array (and it keeps the last call's
  * contents; nothing in it needs to start at zero): calls that overlap on one
  * GPU -- on different streams, or from different host threads without

@@ -246,8 +246,8 @@ __device__ __forceinline__ void big_store_block_fast(float* Kp, int n, int R, in
 //
 // Bound: bf16 MFMA at the rate the card's power allows (six products per fp32
 // one are 2.6 times the fp32 MFMA rate, which bound the 64 x 64 fp32 tiles
-// before).  256 x 229376: 209 -> 102 us (4 us without products' waits per
-// 32-column step: 2.5 of products, the rest of loads and splitting that the
+// before).  256 x 229376: 209 -> 102 us, 3.7 us per 32-column step of which
+// the products alone take 2.5 (the rest is the loads and splitting that the
 // other wave does not cover); 224 groups of 256 x 1024: 219 -> 121 us; 7 groups
 // of 1000 x 4096: 435 -> 205 us.  A last row tile of a few rows costs nearly a
 // whole one: 20 groups of 300 x 4096 123 -> 134 us.
@@ -1107,6 +1107,7 @@ struct GramPlan {
   int64_t rows;
   int NT, pairs, CK, maxchunks;
   size_t gbar_bytes, partial_bytes;
+  size_t bytes;     // workspace of the call: gbar and the partial tiles, or more (see gram_plan)
   bool small;       // gram_small_kernel path
   int NRP;          // its padded row count
 };
@@ -1154,7 +1155,9 @@ GramPlan gram_plan(int64_t n, const int64_t* goff, int P, dr_dtype dtype) {
   g.CK = (int)ck;
   g.maxchunks = (int)((maxw + ck - 1) / ck);
   if (g.maxchunks < 1) g.maxchunks = 1;
-  g.gbar_bytes = align_up((size_t)(goff[P] > 0 ? goff[P] : 1) * sizeof(float), 256);
+  // fp32 rows: the kernels form gbar in LDS (with n = 0 it is the whole work)
+  const int64_t gcols = dtype == DR_F32 && n > 0 ? 0 : goff[P];
+  g.gbar_bytes = align_up((size_t)(gcols > 0 ? gcols : 1) * sizeof(float), 256);
   g.partial_bytes = (size_t)gp * g.pairs * g.maxchunks * kTile * kTile * sizeof(float);
   if (rows == 0 || gram_use_big(n, P, dtype) || (dtype == DR_F32 && g.maxchunks == 1)) g.partial_bytes = 0;
   g.rows = rows;
@@ -1164,6 +1167,24 @@ GramPlan gram_plan(int64_t n, const int64_t* goff, int P, dr_dtype dtype) {
     g.maxchunks = (int)((maxw + kSmCK - 1) / kSmCK);
     if (g.maxchunks < 1) g.maxchunks = 1;
     g.partial_bytes = (size_t)gp * g.maxchunks * g.NRP * g.NRP * sizeof(float);
+  }
+  g.bytes = g.gbar_bytes + g.partial_bytes;
+  if (dtype == DR_F32 && n > 0) {
+    // The size asked for does not fall below gbar over all columns and, for
+    // tiled rows, the chunk partials of 64 x 64 tiles at two rounds of 768
+    // workgroups: dr_gram_noalloc's limit is stated in it, so that which
+    // problems that call refuses does not depend on how the tiles are cut.
+    size_t floor = align_up((size_t)(goff[P] > 0 ? goff[P] : 1) * sizeof(float), 256);
+    if (g.small) {
+      floor += g.partial_bytes;
+    } else {
+      const int64_t all = align_up((size_t)(maxw > 0 ? maxw : 1), 256), slots = 2 * 768;
+      int64_t c = align_up((size_t)((maxw * g.pairs * gp + slots - 1) / slots), 256);
+      if (c < 256) c = 256;
+      if (c > all) c = all;
+      floor += (size_t)gp * g.pairs * (maxw > 0 ? (maxw + c - 1) / c : 1) * kTile * kTile * sizeof(float);
+    }
+    if (floor > g.bytes) g.bytes = floor;
   }
   return g;
 }
@@ -1192,8 +1213,7 @@ extern "C" size_t dr_gram_workspace_size(int64_t n, int64_t m, const int64_t* go
   (void)m;
   if (dtype != DR_BF16 && dtype != DR_F32) return 0;
   if (!goff || P < 1 || n < 0) return 0;
-  dr::GramPlan g = dr::gram_plan(n, goff, P, dtype);
-  return g.gbar_bytes + g.partial_bytes;
+  return dr::gram_plan(n, goff, P, dtype).bytes;
 }
 
 namespace dr {
@@ -1316,7 +1336,7 @@ extern "C" dr_status dr_gram(const void* G, int64_t n, int64_t ldG, const void* 
   dr::GramPlan g;
   const dr_status st = dr::gram_check(G, n, ldG, Gt, m, ldGt, dtype, goff, P, K, s, t2, &g);
   if (st != DR_OK) return st;
-  if (!workspace || ws_bytes < g.gbar_bytes + g.partial_bytes) return DR_ERR_WORKSPACE;
+  if (!workspace || ws_bytes < g.bytes) return DR_ERR_WORKSPACE;
   return dr::gram_run(g, G, n, ldG, Gt, m, ldGt, dtype, goff, P, K, s, t2, workspace,
                       reinterpret_cast<hipStream_t>(stream));
 }
@@ -1342,7 +1362,7 @@ extern "C" dr_status dr_gram_noalloc(const void* G, int64_t n, int64_t ldG, cons
   dr::GramPlan g;
   const dr_status st = dr::gram_check(G, n, ldG, Gt, m, ldGt, dtype, goff, P, K, s, t2, &g);
   if (st != DR_OK) return st;
-  if (g.gbar_bytes + g.partial_bytes > (size_t)DR_GRAM_NOALLOC_MAX_BYTES) return DR_ERR_TOO_LARGE;
+  if (g.bytes > (size_t)DR_GRAM_NOALLOC_MAX_BYTES) return DR_ERR_TOO_LARGE;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kScratchDevices) return DR_ERR_HIP;
   void* ptr = nullptr;
