@@ -178,7 +178,7 @@ size_t dr_gram_workspace_size(int64_t n, int64_t m, const int64_t* goff, int P, 
  * routine); its first call on a device looks up that device's array.
  *   Returns DR_ERR_TOO_LARGE, before any HIP call, when
  *   dr_gram_workspace_size(n, m, goff, P, dtype) > DR_GRAM_NOALLOC_MAX_BYTES
- *   (the largest workload shape here needs 41 MiB: 256 fp32 rows over
+ *   (the largest workload shape here needs just over 40 MiB: 256 fp32 rows over
  *   229376 columns as one group; 36 MiB in 224 groups).
  * All calls on one GPU share its array (and it keeps the last call's
  * contents; nothing in it needs to start at zero): calls that overlap on one
@@ -358,7 +358,8 @@ size_t dr_combine_workspace_size(int64_t n, const int64_t* goff, int P);
  * weighted examples of a layer are taken in |w|-ascending order into one
  * fp32 accumulator holding sum_e (w_e / w_cur) G_e, multiplied by
  * w_cur / w_next when the weight changes and by the last weight at the end
- * (every factor lies in [-1, 1]; equal weights cost nothing).  DR_F32
+ * (every factor lies in [-1, 1]; equal weights cost nothing, and their
+ * examples' tokens follow each other without padding).  DR_F32
  * inputs on fp32 MFMA.
  *
  * Arguments

@@ -46,6 +46,23 @@ template <int AUX>
 __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, unsigned char* lds_block, unsigned voff) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)lds_block, 16, voff, 0, 0, AUX);
 }
+// The same DMA (cached) written out, for kernels that read LDS by the
+// transposing reads below: the compiler makes every such read wait for all
+// DMA in flight that it knows of.  Here the kernel's own waits (DR_WAIT_VM)
+// and barriers alone order them.  base and dst (lds_offset) are uniform; the
+// descriptor covers everything below kOobOffset from base.  (The wait states
+// cover M0 and a descriptor register that a vector instruction wrote last.)
+__device__ __forceinline__ unsigned lds_offset(const unsigned char* p) {   // of a block in LDS
+  return (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)reinterpret_cast<uintptr_t>((lds_void_t*)p));
+}
+__device__ __forceinline__ void dma16_untracked(const void* base, unsigned dst, unsigned voff) {
+  const unsigned long long b = reinterpret_cast<unsigned long long>(base);
+  const u32x4 rsrc = {(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)b),
+                      (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32)) & 0xffffu, kOobOffset,
+                      0x00020000u};
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :: "s"(dst), "v"(voff), "s"(rsrc) : "memory", "m0");
+}
 constexpr int kAuxStream = 2;
 constexpr int kAuxCached = 0;
 
@@ -95,6 +112,27 @@ __device__ __forceinline__ double wave_sum_l63(double v) {
   v += dpp_d<0x142, 0xA>(v);   // row_bcast15 into rows 1 and 3
   v += dpp_d<0x143, 0xC>(v);   // row_bcast31 into rows 2 and 3
   return v;
+}
+
+// 4 x 4 transpose inside each quad of lanes: element r of lane c becomes
+// element c of lane r (two rounds of DPP quad permutations).  A 16 x 16 MFMA
+// result then holds four consecutive columns of one row per lane.
+__device__ __forceinline__ f32x4 quad_transpose(f32x4 v) {
+  const int c = threadIdx.x & 3;
+  float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
+  {  // exchange across bit 0 of the quad lane
+    const float s01 = (c & 1) ? x0 : x1, s23 = (c & 1) ? x2 : x3;
+    const float r01 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s01), 0xB1, 0xF, 0xF, false));
+    const float r23 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s23), 0xB1, 0xF, 0xF, false));
+    if (c & 1) { x0 = r01; x2 = r23; } else { x1 = r01; x3 = r23; }
+  }
+  {  // exchange across bit 1
+    const float s02 = (c & 2) ? x0 : x2, s13 = (c & 2) ? x1 : x3;
+    const float r02 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s02), 0x4E, 0xF, 0xF, false));
+    const float r13 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s13), 0x4E, 0xF, 0xF, false));
+    if (c & 2) { x0 = r02; x1 = r13; } else { x2 = r02; x3 = r13; }
+  }
+  return f32x4{x0, x1, x2, x3};
 }
 
 // the same fixed-order DPP wave sum for fp32 (total in lane 63 only)

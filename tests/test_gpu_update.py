@@ -223,3 +223,73 @@ def test_weights_spanning_sixty_orders_of_magnitude():
     Ub = api.assemble_update(layers, top, n=n, lengths=lens)
     for a, b in zip(Ua, Ub):
         assert rel(host64(a), host64(b)) <= 1e-5
+
+
+def equal_weights(n, skip=()):
+    w = torch.full((n,), -0.25, device=DEV)
+    for r in skip:
+        w[r] = 0.0
+    return w
+
+
+def sample(d, edges):
+    g = torch.Generator().manual_seed(d)
+    return torch.unique(torch.cat([torch.randint(0, d, (60,), generator=g), torch.tensor(edges)])).to(DEV)
+
+
+# wide layers: calls of less than 1.5e10 products leave every list to the
+# kernel for several weights
+@pytest.mark.parametrize("T,d_in,d_out,lens", [
+    (100, 2312, 2568, [16, 15, 17, 16, 16, 31, 32, 33, 1, 100, 47, 16, 0, 99]),   # up to three examples in a step
+    (15, 6008, 6016, [15, 1, 8, 14, 15, 0, 15, 3, 7, 15, 15, 2, 9, 11]),          # all below the packing length
+    (64, 2904, 3016, [64] * 14),                                                  # whole steps only
+    (40, 3672, 3680, [40] * 14),                                                  # every example ends inside a step
+])
+def test_equal_weights_packed_steps(T, d_in, d_out, lens):
+    """Lists of equal weights, whose examples share token steps, some examples
+    skipped between; with and without a split over workgroups."""
+    n = len(lens)
+    lens = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    layers = make_layers([(d_in, d_out)], n, T, torch.bfloat16, lens, seed=11, nan_rows=(4, 5))
+    check(layers, equal_weights(n, skip=(4, 5)), n, lens, rows=sample(d_out, [0, 255, 256, d_out - 1]),
+          cols=sample(d_in, [0, 255, 256, d_in - 1]))
+
+
+def test_small_calls_of_equal_weights():
+    n, T = 14, 100
+    lens = torch.tensor([16, 15, 17, 16, 16, 31, 32, 33, 1, 100, 47, 16, 0, 99], dtype=torch.int32, device=DEV)
+    check(make_layers([(64, 64), (264, 72)], n, T, torch.bfloat16, lens, seed=12), equal_weights(n), n, lens)
+
+
+def test_equal_and_mixed_weight_rows_in_one_call():
+    """Groups whose weight rows go to different kernels, and an all-zero row."""
+    n, T = 9, 70
+    lens = torch.tensor([70, 3, 64, 20, 33, 70, 16, 69, 50], dtype=torch.int32, device=DEV)
+    layers = make_layers([(2312, 264), (136, 2600), (64, 64), (3000, 3000)], n, T, torch.bfloat16, lens, seed=13)
+    w = torch.stack([equal_weights(n, skip=(1,)), mixed_weights(n, 3), torch.zeros(n, device=DEV)])
+    picks = torch.tensor([0, 1, 40, 63], device=DEV)
+    check(layers, w, n, lens, group_of_layer=[0, 1, 2, 0], rows=picks, cols=picks)
+
+
+def test_more_examples_than_one_workgroup_sorts():
+    """Above 1024 examples the lists take three kernels."""
+    n, T = 1100, 4
+    g = torch.Generator().manual_seed(5)
+    lens = torch.randint(0, T + 1, (n,), generator=g, dtype=torch.int32).to(DEV)
+    layers = make_layers([(1400, 1400), (264, 264)], n, T, torch.bfloat16, lens, seed=15)
+    picks = torch.tensor([0, 100, 255, 263], device=DEV)
+    check(layers, equal_weights(n, skip=range(0, n, 3)), n, lens, rows=picks, cols=picks)
+    check(layers, mixed_weights(n, 6), n, lens, rows=picks, cols=picks)
+
+
+def test_equal_weights_rows_further_apart_than_a_step_can_address():
+    """Row strides for which the batch spans more than 4 GiB: every example
+    then starts on a step of its own."""
+    n, T, ld = 6, 300, 1_500_000
+    lens = torch.tensor([300, 0, 257, 17, 299, 33], dtype=torch.int32, device=DEV)
+    layers = make_layers([(2048, 2064)], n, T, torch.bfloat16, lens, seed=14)
+    wide = torch.empty(n * T * ld, dtype=torch.bfloat16, device=DEV).view(n, T, ld)
+    wide[:, :, :2048] = layers[0]["x"]
+    layers[0]["x"] = wide[:, :, :2048]
+    picks = sample(2048, [0, 2047])
+    check(layers, equal_weights(n), n, lens, rows=picks, cols=picks)
