@@ -22,24 +22,26 @@
 //   n <= 16       span_wave_kernel / cone_wave_kernel, one 64-lane wave,
 //                 lane i owns row i, no block barriers;
 //   16 < n <= 64  span_cols_kernel (rows across lanes, 16-column slices
-//                 across waves, one barrier per pivot) and cone_quad_kernel
-//                 (four lanes per row, one barrier per step).
+//                 across waves, one barrier per pivot).
 //
-// cone_pg_kernel (n <= 256): projected gradient on the Jacobi-scaled
+// cone_tile_kernel (16 < n <= 256): projected gradient on the Jacobi-scaled
 // problem, written on the unscaled variable: with r_i = K_ii^-1/2,
 //   w_i <- max(0, w_i - r_i^2 (K w - s)_i / Lhat),  Lhat = max_i sum_j r_i |K_ij| r_j,
 // which is exactly w~ <- max(0, w~ - (K~ w~ - s~)/Lhat) for w~ = w / r.
-// K stays in registers as the exact fp32 input (rows split over a
-// power-of-two group of lanes within one wave); w and all sums are fp64.
+// K stays in registers (4 rows x n / 16 columns per lane); w and all sums are
+// fp64, one barrier per step.
 //
 // simplex_pg_kernel (n <= 256, dr_project_simplex): soft weighting over the
 // probability simplex, min_{w in simplex} w^T K w - 2 s^T w, by accelerated
 // projected gradient (FISTA) with step 1/L, L = 2 max_i sum_j |K_ij|, and
 // the exact Euclidean projection onto the simplex (Michelot's iteration:
 // theta = (sum_{v_i > theta} v_i - 1) / #{v_i > theta} until the set stops
-// shrinking, a handful of block reductions).  Same K layout as the cone.
+// shrinking, a handful of block reductions).  K stays in registers as the
+// exact fp32 input, rows split over a power-of-two group of lanes of a wave.
 // simplex_wave_kernel (n <= 64): the same iteration on one wave, every
 // reduction a wave reduction (no block barrier per step).
+
+#include <type_traits>
 
 #include "common.h"
 
@@ -518,158 +520,12 @@ __global__ __launch_bounds__(kSpanThreads) void span_small_kernel(const float* K
   }
 }
 
-// MAXC: K entries held per thread (columns part, part + tpr, ...)
-template <int MAXC>
-__global__ __launch_bounds__(kConeThreads) void cone_pg_kernel(const float* K, const float* s, const float* t2, int n,
-                                                               int max_iter, float kkt_tol, float* w, float* resid2,
-                                                               int* iters, float* kkt, int* info) {
-  __shared__ double wbuf[2][kConeMaxN];
-  __shared__ double rsc[kConeMaxN];
-  __shared__ double scratch[kConeThreads / 64 + 1];
-  __shared__ int flag;
-  const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-  const float* Kp = K + (long long)p * n * n;
-  const float* sp = s + (long long)p * n;
-
-  // lanes per row: a power of two <= 64 with rows * tpr <= kConeThreads
-  int npad = 1;
-  while (npad < n) npad <<= 1;
-  int tpr = kConeThreads / npad;
-  if (tpr > 64) tpr = 64;
-  const int row = tid / tpr, part = tid % tpr;
-  const bool has_row = row < n;
-
-  if (tid == 0) flag = 0;
-  __syncthreads();
-  int bad = 0;
-  for (int e = tid; e < n * n; e += kConeThreads)
-    if (!isfinite(Kp[e])) bad = 1;
-  for (int i = tid; i < n; i += kConeThreads)
-    if (!isfinite(sp[i])) bad = 1;
-  if (bad) flag = 1;
-  for (int i = tid; i < n; i += kConeThreads) {
-    const float d = Kp[(long long)i * n + i];
-    rsc[i] = d > 0.f ? 1.0 / sqrt((double)d) : 0.0;
-    wbuf[0][i] = 0.0;
-  }
-  __syncthreads();
-  if (flag) {
-    for (int i = tid; i < n; i += kConeThreads) w[(long long)p * n + i] = 0.f;
-    if (tid == 0) {
-      resid2[p] = t2[p];
-      iters[p] = 0;
-      kkt[p] = 0.f;
-      info[p] = DR_INFO_NONFINITE;
-    }
-    return;
-  }
-
-  // this thread's slice of row `row`: columns part, part + tpr, ...
-  // MAXC > 0: the slice lives in registers; MAXC == 0: it is re-read from
-  // global memory (L2-resident) every iteration (n > 128)
-  constexpr int KREG = MAXC > 0 ? MAXC : 1;
-  float kr[KREG];
-  double lrow = 0.0;
-  if constexpr (MAXC > 0) {
-#pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
-      const int j = part + c * tpr;
-      kr[c] = (has_row && j < n) ? Kp[(long long)row * n + j] : 0.f;
-      if (has_row && j < n) lrow += fabs((double)kr[c]) * rsc[j];
-    }
-  } else {
-    kr[0] = 0.f;
-    if (has_row)
-      for (int j = part; j < n; j += tpr) lrow += fabs((double)Kp[(long long)row * n + j]) * rsc[j];
-  }
-  for (int off = tpr / 2; off > 0; off >>= 1) lrow += __shfl_xor(lrow, off, 64);
-  double lmax = has_row ? lrow * rsc[row] : 0.0;
-  for (int off = 32; off > 0; off >>= 1) lmax = fmax(lmax, __shfl_xor(lmax, off, 64));
-  if (lane == 0) scratch[tid >> 6] = lmax;
-  double sabs = 0.0;
-  for (int i = 0; i < n; ++i) sabs = fmax(sabs, fabs(rsc[i] * (double)sp[i]));
-  __syncthreads();
-  double Lhat = 0.0;
-  for (int q = 0; q < kConeThreads / 64; ++q) Lhat = fmax(Lhat, scratch[q]);
-  __syncthreads();
-  const double den = sabs > 0.0 ? sabs : 2.2250738585072014e-308;
-  const double ri = has_row ? rsc[row] : 0.0;
-  const double si = has_row ? (double)sp[row] : 0.0;
-
-  int it = 0, cur = 0;
-  double rho = 0.0, gi = 0.0;
-  while (true) {
-    const double* wc = wbuf[cur];
-    double acc = 0.0;
-    if constexpr (MAXC > 0) {
-#pragma unroll
-      for (int c = 0; c < MAXC; ++c) {
-        const int j = part + c * tpr;
-        if (j < n) acc += (double)kr[c] * wc[j];
-      }
-    } else {
-      if (has_row)
-        for (int j = part; j < n; j += tpr) acc += (double)Kp[(long long)row * n + j] * wc[j];
-    }
-    for (int off = tpr / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    gi = acc - si;                        // (K w - s)_row
-    const double wi = has_row ? wc[row] : 0.0;
-    // scaled KKT residual |min(w~_i, g~_i)|
-    double v = 0.0;
-    if (has_row && ri > 0.0) v = fabs(fmin(wi / ri, ri * gi));
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-    if (lane == 0) scratch[tid >> 6] = v;
-    __syncthreads();
-    double vmax = 0.0;
-    for (int q = 0; q < kConeThreads / 64; ++q) vmax = fmax(vmax, scratch[q]);
-    rho = vmax / den;
-    if ((kkt_tol > 0.f && rho <= (double)kkt_tol) || it >= max_iter || Lhat == 0.0) break;
-    if (has_row && part == 0) {
-      const double nw = wi - ri * ri * gi / Lhat;
-      wbuf[cur ^ 1][row] = nw > 0.0 ? nw : 0.0;
-    }
-    __syncthreads();
-    cur ^= 1;
-    ++it;
-  }
-
-  // resid2 = t2 - s.w + w.(K w - s)
-  __syncthreads();   // every wave has read the last residual maxima
-  double contrib = 0.0;
-  if (has_row && part == 0) {
-    const double wi = wbuf[cur][row];
-    contrib = wi * gi - si * wi;
-    w[(long long)p * n + row] = (float)wi;
-  }
-  const double q = block_sum<kConeThreads>(contrib, scratch);
-  if (tid == 0) {
-    resid2[p] = (float)((double)t2[p] + q);
-    iters[p] = it;
-    kkt[p] = (float)rho;
-    info[p] = (kkt_tol > 0.f && rho > (double)kkt_tol) ? DR_INFO_NOT_CONVERGED : 0;
-  }
-}
-
-
 // ---------------------------------------------------------------------------
 // Single-wave solvers for n <= 64 (one 64-lane wave per group, lane i owns
 // row i, everything in fp64 on the exact fp32 inputs; no block barriers).
 
 
 typedef __attribute__((ext_vector_type(2))) double f64x2;
-
-// sum over the 4 lanes of a quad with DPP quad permutes (xor 1, xor 2)
-__device__ __forceinline__ double quad_sum(double v) {
-  int lo = __double2loint(v), hi = __double2hiint(v);
-  double o = __hiloint2double(__builtin_amdgcn_mov_dpp(hi, 0xB1, 0xF, 0xF, false),
-                              __builtin_amdgcn_mov_dpp(lo, 0xB1, 0xF, 0xF, false));
-  v += o;
-  lo = __double2loint(v);
-  hi = __double2hiint(v);
-  o = __hiloint2double(__builtin_amdgcn_mov_dpp(hi, 0x4E, 0xF, 0xF, false),
-                       __builtin_amdgcn_mov_dpp(lo, 0x4E, 0xF, 0xF, false));
-  return v + o;
-}
 
 // Cholesky of K + lam I in fp64: lane i keeps row i of the factor in
 // registers.  Every broadcast (the pivot, the column L_kj, the solution
@@ -875,24 +731,47 @@ __global__ __launch_bounds__(kWaveN) void cone_wave_kernel(const float* K, const
 }
 
 
-// Jacobi-preconditioned projected gradient for n <= 64 on four waves: wave v
-// owns rows 16v..16v+15, four lanes per row each hold a quarter of the row
-// of K in fp64 registers; partial dot products meet through quad shuffles,
-// and w is exchanged through LDS (double buffered) with one barrier per step.
-template <int NM>
-__global__ __launch_bounds__(256) void cone_quad_kernel(const float* K, const float* s, const float* t2, int n,
-                                                        int max_iter, float kkt_tol, float* w, float* resid2,
-                                                        int* iters, float* kkt, int* info) {
-  constexpr int Q = NM / 4;   // columns per lane
-  __shared__ __attribute__((aligned(16))) double wb[2][NM];
-  __shared__ double rs[NM];
-  __shared__ double red[4];
+// a double from the lane that a DPP control names (quad_perm, row_ror)
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov_d(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false));
+}
+
+// Jacobi-preconditioned projected gradient for 16 < n <= 256 on NM / 16 waves
+// (n padded to NM, a multiple of 32).  Wave v owns rows 16v .. 16v + 15; a
+// group of L = 4 R lanes holds R of them in registers, C = NM / L columns per
+// lane, in pairs 2 (lane % L) + 2 L c.  The sums meet by DPP moves alone: a
+// lane keeps local row r as row r ^ sel, so that after the exchanges it holds
+// row sel of its group (four lanes per row).  w goes through LDS (double
+// buffered) with one barrier per step.  All sums are fp64; K is kept in fp64
+// registers where they hold it (n <= 192), else in fp32.
+// A step is a chain of latencies up to n ~ 100, then bound by the fp64
+// multiply-adds and by w read from LDS, which R rows per lane share.  R = 1 / 2
+// / 4, us of 200 steps: n = 32: 29 / 31 / 33, 64: 42 / 38 / 40, 96: 63 / 53 /
+// 54, 128: 83 / 64 / 61, 192: 780 (K spilled) / 108 / 95, 256: R = 4: 234.
+// With one row per 4 lanes and branches in the step: n = 32: 39, 64: 49; with
+// K read from memory for n > 128: n = 96: 417, 256: 1730.
+template <int NM, int R>
+__global__ __launch_bounds__(NM * 4) void cone_tile_kernel(const float* K, const float* s, const float* t2, int n,
+                                                           int max_iter, float kkt_tol, float* w, float* resid2,
+                                                           int* iters, float* kkt, int* info) {
+  constexpr int L = 4 * R, C = NM / L, NW = NM / 16;   // lanes and columns of a row group
+  constexpr int A = 4 / R;                              // partial sums per row
+  constexpr bool kWide = NM <= 192;
+  using KT = typename std::conditional<kWide, double, float>::type;
+  __shared__ __attribute__((aligned(16))) double wb[2][NM + 64];   // + a slot per lane that writes nothing
+  __shared__ __attribute__((aligned(16))) double rs[NM];
+  __shared__ double red[2][NW];
+  __shared__ double wl[NW], wsx[NW], fin[2][NW];
   __shared__ int flag;
   const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row = wave * 16 + (lane >> 2), q = lane & 3;
+  const int sel = R == 4 ? lane & 3 : R == 2 ? (lane >> 2) & 1 : 0;   // the lane's row of its group
+  const int row0 = wave * 16 + R * (lane / L), row = row0 + sel, col = 2 * (lane & (L - 1));
   const float* Kp = K + (long long)p * n * n;
   const float* sp = s + (long long)p * n;
   const bool own = row < n;
+  const bool writer = (lane & (R == 4 ? 12 : 3)) == 0;   // one of the four lanes that hold the row's sum
   if (tid == 0) flag = 0;
   if (tid < NM) {
     const float d = tid < n ? Kp[(long long)tid * n + tid] : 0.f;
@@ -900,34 +779,79 @@ __global__ __launch_bounds__(256) void cone_quad_kernel(const float* K, const fl
     wb[0][tid] = 0.0;
   }
   __syncthreads();
-  double kr[Q];
-  bool bad = own && q == 0 && !isfinite(sp[row]);
-  double lrow = 0.0;
+  KT kr[R][C];
+  bool bad = own && writer && !isfinite(sp[row]);
 #pragma unroll
-  for (int c = 0; c < Q; ++c) {
-    const int j = q * Q + c;
-    const float v = (own && j < n) ? Kp[(long long)row * n + j] : 0.f;
-    bad |= !isfinite(v);
-    kr[c] = (double)v;
-    lrow += fabs(kr[c]) * rs[j];
+  for (int r = 0; r < R; ++r) {
+    const int i = row0 + (r ^ sel);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int j = col + 2 * L * (c >> 1) + (c & 1);
+      const float k = Kp[(long long)(i < n ? i : n - 1) * n + (j < n ? j : n - 1)];   // in range: no branch
+      const float v = i < n && j < n ? k : 0.f;
+      bad |= !isfinite(v);
+      kr[r][c] = (KT)v;
+    }
   }
   if (bad) flag = 1;
-  lrow = quad_sum(lrow);
+  // first + the lane's row sum of K times a vector in LDS (abs_k: of |K|);
+  // `first` counts on one lane per row
+  auto row_sum = [&](const double* vec, double first, auto abs_k) {
+    double a[R][A] = {};
+    a[0][0] = first;
+    if constexpr (!kWide) {   // else the widened values are hoisted out of the steps and spill
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < C; ++c) asm volatile("" : "+v"(kr[r][c]));
+    }
+    f64x2 v[C / 2];
+#pragma unroll
+    for (int c = 0; c < C / 2; ++c) v[c] = *reinterpret_cast<const f64x2*>(&vec[col + 2 * L * c]);
+    if constexpr (kWide) __builtin_amdgcn_sched_barrier(0);   // every read in flight before the first product
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const double k = (double)kr[r][c];
+        a[r][c % A] = fma(decltype(abs_k)::value ? fabs(k) : k, v[c / 2][c & 1], a[r][c % A]);
+      }
+    double t[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) t[r] = A == 4 ? (a[r][0] + a[r][1 % A]) + (a[r][2 % A] + a[r][3 % A])
+                                     : A == 2 ? a[r][0] + a[r][1 % A] : a[r][0];
+    if constexpr (R == 4) {
+      t[0] += dpp_mov_d<0xB1>(t[1]);   // lane ^ 1
+      t[2] += dpp_mov_d<0xB1>(t[3]);
+      t[0] += dpp_mov_d<0x4E>(t[2]);   // lane ^ 2
+      t[0] += dpp_mov_d<0x124>(t[0]);  // rotate by 4, by 8
+      return t[0] + dpp_mov_d<0x128>(t[0]);
+    } else {
+      if constexpr (R == 2) t[0] += dpp_mov_d<0x141>(t[1]);   // lane ^ 7
+      t[0] += dpp_mov_d<0xB1>(t[0]);
+      return t[0] + dpp_mov_d<0x4E>(t[0]);
+    }
+  };
+  // maximum over the wave
+  auto row_max = [&](double v) {
+    v = fmax(v, dpp_mov_d<0xB1>(v));
+    v = fmax(v, dpp_mov_d<0x4E>(v));
+    v = fmax(v, dpp_mov_d<0x124>(v));
+    v = fmax(v, dpp_mov_d<0x128>(v));
+    return fmax(fmax(readlane_d(v, 0), readlane_d(v, 16)), fmax(readlane_d(v, 32), readlane_d(v, 48)));
+  };
+  const double lrow = row_sum(rs, 0.0, std::true_type{});
   const double ri = own ? rs[row] : 0.0;
+  const double inv_ri = ri > 0.0 ? 1.0 / ri : 0.0;
   const double si = own ? (double)sp[row] : 0.0;
-  double lmax = own ? lrow * ri : 0.0, smax = own ? fabs(ri * si) : 0.0;
-  for (int off = 32; off > 0; off >>= 1) {
-    lmax = fmax(lmax, __shfl_xor(lmax, off, 64));
-    smax = fmax(smax, __shfl_xor(smax, off, 64));
-  }
-  __shared__ double wl[4], wsx[4];
+  const double lmax = row_max(own ? lrow * ri : 0.0), smax = row_max(own ? fabs(ri * si) : 0.0);
   if (lane == 0) {
     wl[wave] = lmax;
     wsx[wave] = smax;
   }
   __syncthreads();
   if (flag) {
-    if (own && q == 0) w[(long long)p * n + row] = 0.f;
+    if (own && writer) w[(long long)p * n + row] = 0.f;
     if (tid == 0) {
       resid2[p] = t2[p];
       iters[p] = 0;
@@ -936,48 +860,77 @@ __global__ __launch_bounds__(256) void cone_quad_kernel(const float* K, const fl
     }
     return;
   }
-  const double Lhat = fmax(fmax(wl[0], wl[1]), fmax(wl[2], wl[3]));
-  const double den0 = fmax(fmax(wsx[0], wsx[1]), fmax(wsx[2], wsx[3]));
+  double Lhat = 0.0, den0 = 0.0;
+#pragma unroll
+  for (int v = 0; v < NW; ++v) {
+    Lhat = fmax(Lhat, wl[v]);
+    den0 = fmax(den0, wsx[v]);
+  }
   const double den = den0 > 0.0 ? den0 : 2.2250738585072014e-308;
   const double step = ri * ri / (Lhat > 0.0 ? Lhat : 1.0);
   const bool check_each = kkt_tol > 0.f;
 
-  int it = 0, cur = 0;
-  double rho = 0.0, g = 0.0, wi = 0.0;
-  while (true) {
-    double acc = 0.0;
-#pragma unroll
-    for (int c = 0; c < Q; c += 2) {
-      const f64x2 v = *reinterpret_cast<const f64x2*>(&wb[cur][q * Q + c]);
-      acc += kr[c] * v.x;
-      acc += kr[c + 1] * v.y;
-    }
-    acc = quad_sum(acc);
-    g = acc - si;
-    const bool last = it >= max_iter || Lhat == 0.0;
-    if (check_each || last) {
-      double v = (own && q == 0 && ri > 0.0) ? fabs(fmin(wi / ri, ri * g)) : 0.0;
-      for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-      if (lane == 0) red[wave] = v;
-      __syncthreads();
-      rho = fmax(fmax(red[0], red[1]), fmax(red[2], red[3])) / den;
-      __syncthreads();
-      if ((check_each && rho <= (double)kkt_tol) || last) break;
-    }
-    const double nw = wi - step * g;
-    wi = nw > 0.0 ? nw : 0.0;
-    if (q == 0 && row < NM) wb[cur ^ 1][row] = own ? wi : 0.0;
+  const int steps = Lhat == 0.0 ? 0 : max_iter;
+
+  // One step is a chain of latencies (read w, products, exchanges, write w,
+  // barrier), and a taken branch is one of them: the steps without a test run
+  // in a loop of their own, two per turn, and lanes that own no result write
+  // to a slot nobody reads.  Rows past n have step 0 and stay 0.
+  const double neg_s = writer ? -si : 0.0;
+  const int slot = writer ? row : NM + lane;
+  int it = 0;
+  double wi = 0.0;
+  auto gradient = [&](int cur) { return row_sum(wb[cur], neg_s, std::false_type{}); };   // (K w - s)_row
+  auto residual = [&](double g) {   // scaled KKT residual |min(w~_i, g~_i)|, maximum over the wave
+    return row_max(own && ri > 0.0 ? fabs(fmin(wi * inv_ri, ri * g)) : 0.0);
+  };
+  auto advance = [&](int cur) {
+    wi = fmax(wi - step * gradient(cur), 0.0);
+    wb[cur ^ 1][slot] = wi;
     __syncthreads();
-    cur ^= 1;
-    ++it;
+  };
+  if (!check_each) {
+    for (; it + 1 < steps; it += 2) {
+      advance(0);
+      advance(1);
+    }
+    if (it < steps) {
+      advance(0);
+      ++it;
+    }
+  } else {
+    for (; it < steps; ++it) {
+      const double g = gradient(it & 1);
+      const double v = residual(g);
+      if (lane == 0) red[it & 1][wave] = v;
+      const double nw = fmax(wi - step * g, 0.0);
+      wb[(it & 1) ^ 1][slot] = nw;
+      __syncthreads();
+      double rho = 0.0;
+#pragma unroll
+      for (int k = 0; k < NW; ++k) rho = fmax(rho, red[it & 1][k]);
+      if (rho / den <= (double)kkt_tol) break;
+      wi = nw;
+    }
   }
-  double contrib = (own && q == 0) ? wi * g - si * wi : 0.0;
-  for (int off = 32; off > 0; off >>= 1) contrib += __shfl_xor(contrib, off, 64);
-  if (lane == 0) red[wave] = contrib;
+  const double g = gradient(it & 1);
+  const double rmax = residual(g);
+  // resid2 = t2 - s.w + w.(K w - s)
+  const double contrib = wave_sum(own && writer ? wi * g - si * wi : 0.0);
+  if (lane == 0) {
+    fin[0][wave] = rmax;
+    fin[1][wave] = contrib;
+  }
   __syncthreads();
-  if (own && q == 0) w[(long long)p * n + row] = (float)wi;
+  if (own && writer) w[(long long)p * n + row] = (float)wi;
   if (tid == 0) {
-    resid2[p] = (float)((double)t2[p] + ((red[0] + red[1]) + (red[2] + red[3])));
+    double q = 0.0, rho = 0.0;
+    for (int v = 0; v < NW; ++v) {
+      q += fin[1][v];
+      rho = fmax(rho, fin[0][v]);
+    }
+    rho /= den;
+    resid2[p] = (float)((double)t2[p] + q);
     iters[p] = it;
     kkt[p] = (float)rho;
     info[p] = (kkt_tol > 0.f && rho > (double)kkt_tol) ? DR_INFO_NOT_CONVERGED : 0;
@@ -1554,32 +1507,23 @@ extern "C" dr_status dr_project_cone(const float* K, const float* s, const float
                        iters, kkt, info);
     return launch_status();
   }
-  if (n <= kWaveN) {
-    if (n <= 16)
-      hipLaunchKernelGGL(cone_wave_kernel<16>, dim3(P), dim3(kWaveN), 0, hs, K, s, t2, (int)n, max_iter, kkt_tol, w,
-                         resid2, iters, kkt, info);
-    else if (n <= 32)
-      hipLaunchKernelGGL(cone_quad_kernel<32>, dim3(P), dim3(256), 0, hs, K, s, t2, (int)n, max_iter, kkt_tol, w,
-                         resid2, iters, kkt, info);
-    else
-      hipLaunchKernelGGL(cone_quad_kernel<64>, dim3(P), dim3(256), 0, hs, K, s, t2, (int)n, max_iter, kkt_tol, w,
-                         resid2, iters, kkt, info);
+  if (n <= 16) {
+    hipLaunchKernelGGL(cone_wave_kernel<16>, dim3(P), dim3(kWaveN), 0, hs, K, s, t2, (int)n, max_iter, kkt_tol, w,
+                       resid2, iters, kkt, info);
     return launch_status();
   }
-  int npad = 1;
-  while (npad < n) npad <<= 1;
-  int tpr = kConeThreads / npad;
-  if (tpr > 64) tpr = 64;
-  const int cols = (npad + tpr - 1) / tpr;
-  if (cols <= 4)
-    hipLaunchKernelGGL(cone_pg_kernel<4>, dim3(P), dim3(kConeThreads), 0, hs, K, s, t2, (int)n, max_iter, kkt_tol, w,
-                       resid2, iters, kkt, info);
-  else if (cols <= 16)
-    hipLaunchKernelGGL(cone_pg_kernel<16>, dim3(P), dim3(kConeThreads), 0, hs, K, s, t2, (int)n, max_iter, kkt_tol, w,
-                       resid2, iters, kkt, info);
-  else
-    hipLaunchKernelGGL(cone_pg_kernel<0>, dim3(P), dim3(kConeThreads), 0, hs, K, s, t2, (int)n, max_iter, kkt_tol, w,
-                       resid2, iters, kkt, info);
+  // the smallest instance that holds n: both the multiplications and the LDS
+  // reads of a step go with its square (rows per lane: see the kernel)
+#define DR_CONE(NM, R)                                                                                               \
+  case NM / 32:                                                                                                      \
+    hipLaunchKernelGGL((cone_tile_kernel<NM, R>), dim3(P), dim3(NM * 4), 0, hs, K, s, t2, (int)n, max_iter, kkt_tol, \
+                       w, resid2, iters, kkt, info);                                                                 \
+    break;
+  switch ((int)((n + 31) / 32)) {
+    DR_CONE(32, 1) DR_CONE(64, 2) DR_CONE(96, 2) DR_CONE(128, 4)
+    DR_CONE(160, 4) DR_CONE(192, 4) DR_CONE(224, 4) DR_CONE(256, 4)
+  }
+#undef DR_CONE
   return launch_status();
 }
 

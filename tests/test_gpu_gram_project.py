@@ -442,6 +442,54 @@ def test_cone_matches_exact_nnls(n, kappa, iters, tol):
         assert abs(rho - float(kkt[0])) <= 1e-6
 
 
+def cone_steps_ref(K, s, steps):
+    """w and the scaled KKT residual before every step, in fp64: w from 0, step 1 / (largest absolute row sum) on
+    the Jacobi-scaled problem."""
+    r = np.where(np.diag(K) > 0, 1 / np.sqrt(np.where(np.diag(K) > 0, np.diag(K), 1.0)), 0.0)
+    lhat = (r[:, None] * np.abs(K) * r[None, :]).sum(1).max()
+    w, ws, rhos = np.zeros(len(s)), [], []
+    for _ in range(steps + 1):
+        g = K @ w - s
+        v = np.where(r > 0, np.abs(np.minimum(np.divide(w, r, out=np.zeros_like(w), where=r > 0), r * g)), 0.0)
+        ws.append(w)
+        rhos.append(v.max() / np.abs(r * s).max())
+        w = np.maximum(w - r * r * g / lhat, 0.0)
+    return ws, rhos
+
+
+@pytest.mark.parametrize("n", [17, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 224, 225, 256])
+def test_cone_steps_at_the_edges_of_every_size(n):
+    """Both ends of every padded size, for an even, an odd and no step, and stopped by the residual: a full group, one
+    with an all-zero example, one with a value that is not finite."""
+    G = rand((3, n, n + 30), 700 + n, dtype=torch.float64)
+    c = rand((3, n, 1), 800 + n, dtype=torch.float64)
+    G[1, n // 2] = 0
+    K = (G @ G.transpose(1, 2)).float()
+    s = (K.double() @ c)[..., 0].float()
+    K[2, n - 1, 0] = float("inf")
+    t2 = torch.full((3,), 1e7, device=DEV)
+    steps = 40
+    refs = [cone_steps_ref(host64(K[p]), host64(s[p]), steps) for p in range(2)]
+    rhos = refs[0][1]
+    k = next(i for i in range(8, steps) if rhos[i] < min(rhos[:i]))   # a new least residual: the first below tol
+    tol = (rhos[k] * min(rhos[:k])) ** 0.5
+    for it_max, kkt_tol in ((steps, 0.0), (7, 0.0), (0, 0.0), (steps, tol)):
+        w, resid2, it, kkt, info = api.project_cone(K.contiguous(), s.contiguous(), t2, it_max, kkt_tol)
+        torch.cuda.synchronize()
+        for p in range(2):
+            ws, rh = refs[p]
+            q = it_max if kkt_tol == 0 else next((i for i in range(steps) if rh[i] <= np.float32(tol)), steps)
+            assert int(it[p]) == q
+            # fp64 steps on the same fp32 K: the rounding of the result to fp32 is what is left
+            assert np.abs(host64(w[p]) - ws[q]).max() <= 1e-7 * max(np.abs(ws[q]).max(), 1e-30)
+            Kh, sh = host64(K[p]), host64(s[p])
+            r2 = 1e7 - 2 * sh @ ws[q] + ws[q] @ Kh @ ws[q]
+            assert abs(float(resid2[p]) - r2) <= 1e-6 * (1e7 + 2 * abs(sh @ ws[q]))
+            assert abs(float(kkt[p]) - rh[q]) <= 1e-6 * rh[q] + 1e-12
+        assert float(w[1, n // 2]) == 0.0
+        assert int(info[2]) == -3 and int(it[2]) == 0 and float(w[2].abs().max()) == 0.0
+
+
 def test_cone_special_cases(golden_dir):
     import json, os
     fx = json.load(open(os.path.join(golden_dir, "cone_2x2.json")))
