@@ -9,12 +9,11 @@
 //
 // Up to 16 layers go in one launch (blockIdx.z = layer), so that the small
 // per-layer grids fill the chip together.
+//   bp_mfma_kernel   aligned bf16 projectors: both products in one kernel, T
+//                    kept in LDS as three bf16 planes (see the kernel); else:
 //   bp_left_kernel   T = X' P_in   [k_out][d_in] (small, workspace), one
 //                    64-column slice of T per workgroup, fp32 MFMA (16x16x4)
-//                    with both operands staged in LDS; written as fp32, or
-//                    as three bf16 planes for bp_mfma_kernel
-//   bp_mfma_kernel   bf16 projectors: U = P_out^T (T1 + T2 + T3) on bf16 MFMA
-//                    (see the kernel)
+//                    with both operands staged in LDS
 //   bp_right_kernel  U = P_out^T T, one 64 (d_out) x 256 (d_in) tile per
 //                    workgroup: each thread owns 16 rows x 4 columns, so a
 //                    float4 of T read from L2 feeds 64 FMAs; the P_out columns
@@ -52,14 +51,7 @@ struct BpArgs {
 // a < k_out <= 64 (4 row tiles), 4 column tiles: wave w takes column tile w
 // of every row tile.  Rows and columns past k_in / k_out /
 // d_in are zero in LDS.
-// bf16 round to nearest even of a finite fp32 value
-__device__ __forceinline__ unsigned short bf16_rne(float x) {
-  const unsigned u = __float_as_uint(x);
-  return (unsigned short)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
-}
-__device__ __forceinline__ float bf16_val(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
-
-template <typename TP, bool PLANES>
+template <typename TP>
 __global__ __launch_bounds__(256) void bp_left_kernel(BpArgs g) {
   __shared__ __attribute__((aligned(16))) float xs[kBpMaxK * 68];   // X'[a][b], stride 68
   __shared__ __attribute__((aligned(16))) float ps[kBpMaxK * kBpLd];   // P_in[b][c - c0]
@@ -111,21 +103,7 @@ __global__ __launch_bounds__(256) void bp_left_kernel(BpArgs g) {
       const int a = 16 * i + 4 * lq + q, c = c0 + 16 * w + lr;
       if (a >= k_out || c >= d_in) continue;
       const float t = acc[i][q];
-      if constexpr (PLANES) {
-        // T = T1 + T2 + T3 in bf16 planes [3][k_out][d_in] (each the nearest
-        // bf16 to what the previous ones leave; the sum is T to about 2^-24)
-        unsigned short* Tp = reinterpret_cast<unsigned short*>(g.T[l]);
-        const unsigned short h1 = bf16_rne(t);
-        const float r1 = t - bf16_val(h1);
-        const unsigned short h2 = bf16_rne(r1);
-        const unsigned short h3 = bf16_rne(r1 - bf16_val(h2));
-        const long long plane = (long long)k_out * d_in;
-        Tp[(long long)a * d_in + c] = h1;
-        Tp[plane + (long long)a * d_in + c] = h2;
-        Tp[2 * plane + (long long)a * d_in + c] = h3;
-      } else {
-        g.T[l][(long long)a * d_in + c] = t;
-      }
+      g.T[l][(long long)a * d_in + c] = t;
     }
 }
 
@@ -188,106 +166,180 @@ __global__ __launch_bounds__(256) void bp_right_kernel(BpArgs g) {
   }
 }
 
-// bf16 P_out (16-byte aligned, d_in and d_out multiples of 8): U = P_out^T T
-// with T given as three bf16 planes, i.e. sum_{p < 3} P_out^T T_p, as one
-// bf16 MFMA contraction over 3 * k_out rows (each product exact in fp32,
-// fp32 accumulation).  One 128 (d_out) x 128 (d_in) tile per workgroup:
-// P_out[:, o-tile] and the three T[:, c-tile] planes (64 rows of 256 bytes
-// each, 32-byte slots XOR-swizzled per row) are staged in LDS and read as
-// MFMA operands by the gfx950 transposing read (8 consecutive rows a per
-// lane); wave (wr, wc) holds a 64 x 64 quarter.  The finished tile goes back
-// through LDS so that U is written in whole 512-byte rows.
+__device__ __forceinline__ float bf16_val(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
+__device__ __forceinline__ float bf16_lo(unsigned h) { return __uint_as_float(h << 16); }
+__device__ __forceinline__ float bf16_hi(unsigned h) { return __uint_as_float(h & 0xffff0000u); }
+
+// bf16 projectors (16-byte aligned, d_in and d_out multiples of 8), both
+// products in one kernel: a workgroup takes 128 columns of U and `per` tiles
+// of 128 rows.  It makes T = X' P_in of its columns once (fp32 MFMA 16x16x4,
+// k_out x 128, P_in and X' staged in LDS) and leaves it in LDS as three bf16
+// planes T1 + T2 + T3 = T (each the nearest bf16 to what the previous ones
+// leave; the sum is T to about 2^-24).  Then, tile by tile, U = P_out^T (T1 +
+// T2 + T3) is one bf16 MFMA contraction over 3 * k_out rows (each product
+// exact in fp32, fp32 accumulation): P_out[:, o-tile] goes to LDS beside the
+// planes (64 rows of 256 bytes each, 32-byte slots XOR-swizzled per row), all
+// read as MFMA operands by the gfx950 transposing read (8 consecutive rows a
+// per lane); the next tile's P_out is loaded under the products.  Wave (wr,
+// wc) holds a 64 x 64 quarter.  T's columns are the rows of the MFMA tile, so
+// a lane ends up with four neighbouring columns of a row of U; 16 rows at a
+// time go through 4 KB of LDS of the wave's own, so that a store writes whole
+// 256-byte pieces of rows.
+// The d_out x d_in fp32 write is the bound, with the start of a workgroup (P_in
+// and X' from memory, T) before its first store: 8 layers of 2048 x 2048 in 35
+// us and 16 of 4096 x 14336 in 745 us (a fill of U: 21 and 545), 47 and 987
+// with T made by a launch of its own, read back by every tile and results
+// staged through LDS 128 rows at a time.  Stores straight from the registers
+// (64-byte pieces) 39 and 840; one row tile per workgroup 70 and 1700.
 constexpr int kBmTile = 128;
 constexpr int kBmRow = kBmTile * 2;          // bytes of one staged row
 constexpr int kBmSlab = kBpMaxK * kBmRow;    // 16 KB: one operand slab
-constexpr int kBmOutLd = kBmTile + 4;        // output staging stride (floats)
-constexpr int kBmLds = 4 * kBmSlab > kBmTile * kBmOutLd * 4 ? 4 * kBmSlab : kBmTile * kBmOutLd * 4;
+constexpr int kBmXLd = kBpMaxK + 4;          // X' staging stride (floats)
+constexpr int kBmLds = 4 * kBmSlab + 4 * 16 * 64 * 4;   // 80 KB: + 16 x 64 results per wave
+constexpr int kBmGroups = 512;               // workgroups that fill the chip (two per CU)
+constexpr int kBmMaxPer = 32;                // row tiles per workgroup
 
-__global__ __launch_bounds__(256, 2) void bp_mfma_kernel(BpArgs g) {
+__global__ __launch_bounds__(256, 2) void bp_mfma_kernel(BpArgs g, int per) {
+  // slab 0: P_out of the row tile; slabs 1..3: the planes of T.  P_in and X'
+  // lie there first.
   __shared__ __attribute__((aligned(16))) unsigned char lds[kBmLds];
   const int l = blockIdx.z;
-  const int k_out = g.k_out[l], d_out = g.d_out[l], d_in = g.d_in[l];
-  const int o0 = blockIdx.y * kBmTile, c0 = blockIdx.x * kBmTile;
-  if (o0 >= d_out || c0 >= d_in) return;
+  const int k_in = g.k_in[l], k_out = g.k_out[l], d_out = g.d_out[l], d_in = g.d_in[l];
+  const int c0 = blockIdx.x * kBmTile;
+  const int tiles = (d_out + kBmTile - 1) / kBmTile;
+  const int t0 = blockIdx.y * per, t1 = t0 + per < tiles ? t0 + per : tiles;
+  if (t0 >= tiles || c0 >= d_in) return;
   const unsigned short* pg = static_cast<const unsigned short*>(g.p_out[l]);
-  const unsigned short* tg = reinterpret_cast<const unsigned short*>(g.T[l]);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, lr = lane & 15, g4 = lane >> 4;
+  // a 16-byte chunk of the P_out slab per step: row (tid >> 4) + 16 u, columns 8 (tid & 15) ..
+  const int pr = tid >> 4, pc = 8 * (tid & 15);
+  u32x4 pv[4];
+  auto load_p = [&](const unsigned short* src, int k, int x0, int d) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int r = pr + 16 * u;
+      pv[u] = r < k && x0 + pc < d ? *reinterpret_cast<const u32x4*>(src + (long long)r * d + x0 + pc)
+                                   : u32x4{0u, 0u, 0u, 0u};
+    }
+  };
+  // T of these 128 columns
   {
-    // slab 0 = P_out[a][o0 ..], slabs 1..3 = plane p[a][c0 ..]; 16-byte chunks,
-    // every load of the thread in flight before the LDS writes
-    u32x4 v[16];
+    unsigned short* ps = reinterpret_cast<unsigned short*>(lds);        // P_in[b][c - c0], 256 bytes per row
+    float* xs = reinterpret_cast<float*>(lds + kBmSlab);                // X'[a][b]
+    const float* x = g.x[l];
+    float xv[kBpMaxK * kBpMaxK / 256];
+    load_p(static_cast<const unsigned short*>(g.p_in[l]), k_in, c0, d_in);
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + 256 * u, slab = e >> 10, r = (e >> 4) & 63, col = 8 * (e & 15);
-      const bool ok = r < k_out && (slab == 0 ? o0 + col < d_out : c0 + col < d_in);
-      const unsigned short* src = slab == 0 ? pg + (long long)r * d_out + o0 + col
-                                            : tg + ((long long)(slab - 1) * k_out + r) * d_in + c0 + col;
-      v[u] = ok ? *reinterpret_cast<const u32x4*>(src) : u32x4{0u, 0u, 0u, 0u};
+    for (int u = 0; u < kBpMaxK * kBpMaxK / 256; ++u) {
+      const int e = tid + 256 * u, a = e >> 6, b = e & 63;
+      xv[u] = (a < k_out && b < k_in) ? x[a * k_in + b] : 0.f;
     }
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + 256 * u, slab = e >> 10, r = (e >> 4) & 63, ch = e & 15;
-      *reinterpret_cast<u32x4*>(lds + slab * kBmSlab + r * kBmRow + (((ch >> 1) ^ slot_xor(r)) * 32) + (ch & 1) * 16) =
-          v[u];
+    for (int u = 0; u < 4; ++u) *reinterpret_cast<u32x4*>(ps + (pr + 16 * u) * kBmTile + pc) = pv[u];
+#pragma unroll
+    for (int u = 0; u < kBpMaxK * kBpMaxK / 256; ++u) {
+      const int e = tid + 256 * u;
+      xs[(e >> 6) * kBmXLd + (e & 63)] = xv[u];
     }
+    load_p(pg, k_out, t0 * kBmTile, d_out);   // the first row tile, under T
+    __syncthreads();
+    f32x4 t[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) t[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int b1 = 0; b1 < k_in; b1 += 16) {   // rows past k_in are zero
+#pragma unroll
+      for (int b0 = b1; b0 < b1 + 16; b0 += 4) {
+        float av[2], bv[4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) av[i] = bf16_val(ps[(b0 + g4) * kBmTile + 32 * w + 16 * i + lr]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bv[j] = xs[(16 * j + lr) * kBmXLd + b0 + g4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) t[i][j] = mma_f32(av[i], bv[j], t[i][j]);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int a = 16 * j + lr;   // columns 32 w + 16 i + 4 g4 .. + 3 of row a: slot 2 w + i
+        unsigned char* at = lds + kBmSlab + a * kBmRow + ((2 * w + i) ^ slot_xor(a)) * 32 + g4 * 8;
+        f32x4 v = t[i][j];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          const uint2 h = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+          *reinterpret_cast<uint2*>(at + p * kBmSlab) = h;
+          v -= f32x4{bf16_lo(h.x), bf16_hi(h.x), bf16_lo(h.y), bf16_hi(h.y)};
+        }
+      }
   }
-  __syncthreads();
   // fragment reads: lane (g4, q, rr) of the transposing read addresses row
   // 8 g4 + q (+4 for the second half) and 8-byte piece rr of a 16-column
   // block; the block's logical slot is XOR-ed with the row's swizzle
-  const int g4 = lane >> 4, q = (lane >> 2) & 3, rr = lane & 3;
-  const int fx = q | ((g4 & 1) << 2);
+  const int q4 = (lane >> 2) & 3, rr = lane & 3;
+  const int fx = q4 | ((g4 & 1) << 2);
   const int wr = w >> 1, wc = w & 1;
-  const unsigned rbase = (unsigned)((8 * g4 + q) * kBmRow + rr * 8);
-  unsigned offa[4], offb[4];
+  const unsigned rbase = (unsigned)((8 * g4 + q4) * kBmRow + rr * 8);
+  unsigned offp[4], offt[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) offa[i] = rbase + (unsigned)(((4 * wr + i) ^ fx) * 32);
+  for (int j = 0; j < 4; ++j) offp[j] = rbase + (unsigned)(((4 * wr + j) ^ fx) * 32);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) offb[j] = rbase + (unsigned)(((4 * wc + j) ^ fx) * 32);
+  for (int i = 0; i < 4; ++i) offt[i] = rbase + (unsigned)(((4 * wc + i) ^ fx) * 32);
   auto frag = [&](const unsigned char* base) {
     const v4s lo = lds_read_tr16(base);
     const v4s hi = lds_read_tr16(base + 4 * kBmRow);
     return u32x4{__builtin_bit_cast(uint2, lo).x, __builtin_bit_cast(uint2, lo).y, __builtin_bit_cast(uint2, hi).x,
                  __builtin_bit_cast(uint2, hi).y};
   };
-  f32x4 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int nh = k_out > 32 ? 2 : 1;   // 32-row slices of the sketch index a (rows >= k_out are zero)
-  for (int h = 0; h < nh; ++h) {
-    u32x4 fa[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) fa[i] = frag(lds + h * 32 * kBmRow + offa[i]);
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      u32x4 fb[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) fb[j] = frag(lds + (1 + p) * kBmSlab + h * 32 * kBmRow + offb[j]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = mma_bf16(fa[i], fb[j], acc[i][j]);
-    }
-  }
-  __syncthreads();
-  float* outs = reinterpret_cast<float*>(lds);   // [128][kBmOutLd]
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int qq = 0; qq < 4; ++qq)
-        outs[(64 * wr + 16 * i + 4 * g4 + qq) * kBmOutLd + 64 * wc + 16 * j + (lane & 15)] = acc[i][j][qq];
-  __syncthreads();
   float* U = g.U[l];
+  for (int t = t0; t < t1; ++t) {
+    const int o0 = t * kBmTile;
 #pragma unroll
-  for (int u = 0; u < kBmTile * kBmTile / 4 / 256; ++u) {
-    const int e = tid + 256 * u, r = e >> 5, c = 4 * (e & 31);
-    if (o0 + r < d_out && c0 + c < d_in)
-      *reinterpret_cast<float4*>(U + (long long)(o0 + r) * d_in + c0 + c) =
-          *reinterpret_cast<const float4*>(&outs[r * kBmOutLd + c]);
+    for (int u = 0; u < 4; ++u) {
+      const int r = pr + 16 * u, ch = tid & 15;
+      *reinterpret_cast<u32x4*>(lds + r * kBmRow + (((ch >> 1) ^ slot_xor(r)) * 32) + (ch & 1) * 16) = pv[u];
+    }
+    __syncthreads();
+    if (t + 1 < t1) load_p(pg, k_out, o0 + kBmTile, d_out);
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int h = 0; h < nh; ++h) {
+      u32x4 fp[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) fp[j] = frag(lds + h * 32 * kBmRow + offp[j]);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        u32x4 ft[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ft[i] = frag(lds + (1 + p) * kBmSlab + h * 32 * kBmRow + offt[i]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[i][j] = mma_bf16(ft[i], fp[j], acc[i][j]);
+      }
+    }
+    __syncthreads();   // the P_out slab may be replaced
+    float* st = reinterpret_cast<float*>(lds + 4 * kBmSlab + w * 4096);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4*>(st + lr * 64 + (((4 * i + g4) ^ lr) * 4)) = acc[i][j];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = 4 * i + g4, o = o0 + 64 * wr + 16 * j + r, c = c0 + 64 * wc + 4 * lr;
+        const f32x4 v = *reinterpret_cast<const f32x4*>(st + r * 64 + ((lr ^ r) * 4));
+        if (o < d_out && c < d_in) *reinterpret_cast<f32x4*>(U + (long long)o * d_in + c) = v;
+      }
+    }
   }
 }
 
@@ -329,6 +381,7 @@ extern "C" dr_status dr_back_project(const dr_layer* layers, int num_layers, dr_
     int dimax = 1, domax = 1;
     bool mfma = dtype == DR_BF16;
     size_t o = 0;
+    long long tiles = 0;
     for (int j = 0; j < count; ++j) {
       const dr_layer& L = layers[f + j];
       g.p_in[j] = L.p_in;
@@ -336,7 +389,7 @@ extern "C" dr_status dr_back_project(const dr_layer* layers, int num_layers, dr_
       g.x[j] = u + L.col_offset;
       g.T[j] = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + o);
       o = align_up(o + (size_t)L.k_out * (size_t)L.d_in * 6, 256);   // fp32 T or three bf16 planes
-      mfma = mfma && L.d_in % 8 == 0 && L.d_out % 8 == 0 && aligned16(L.p_out);
+      mfma = mfma && L.d_in % 8 == 0 && L.d_out % 8 == 0 && aligned16(L.p_in) && aligned16(L.p_out);
       g.U[j] = U + u_offset[f + j];
       g.k_in[j] = (int)L.k_in;
       g.k_out[j] = (int)L.k_out;
@@ -344,18 +397,26 @@ extern "C" dr_status dr_back_project(const dr_layer* layers, int num_layers, dr_
       g.d_out[j] = (int)L.d_out;
       dimax = g.d_in[j] > dimax ? g.d_in[j] : dimax;
       domax = g.d_out[j] > domax ? g.d_out[j] : domax;
+      tiles += (long long)((g.d_in[j] + kBmTile - 1) / kBmTile) * ((g.d_out[j] + kBmTile - 1) / kBmTile);
     }
     const dim3 gl((dimax + kBpTile - 1) / kBpTile, 1, count);
     const dim3 gr((dimax + kBpCols - 1) / kBpCols, (domax + 4 * kBpRows - 1) / (4 * kBpRows), count);
     if (mfma) {
-      const dim3 gm((dimax + kBmTile - 1) / kBmTile, (domax + kBmTile - 1) / kBmTile, count);
-      hipLaunchKernelGGL((bp_left_kernel<__bf16, true>), gl, dim3(256), 0, hs, g);
-      hipLaunchKernelGGL(bp_mfma_kernel, gm, dim3(256), 0, hs, g);
+      // row tiles per workgroup: as many as leave about two workgroups per CU
+      // (T is made once for all of them), the same for each
+      const int rows = (domax + kBmTile - 1) / kBmTile;
+      const long long want = (tiles + kBmGroups - 1) / kBmGroups;
+      int per = want < kBmMaxPer ? (int)want : kBmMaxPer;
+      per = per < rows ? per : rows;
+      const int parts = (rows + per - 1) / per;
+      per = (rows + parts - 1) / parts;
+      const dim3 gm((dimax + kBmTile - 1) / kBmTile, (rows + per - 1) / per, count);
+      hipLaunchKernelGGL(bp_mfma_kernel, gm, dim3(256), 0, hs, g, per);
     } else if (dtype == DR_BF16) {
-      hipLaunchKernelGGL((bp_left_kernel<__bf16, false>), gl, dim3(256), 0, hs, g);
+      hipLaunchKernelGGL(bp_left_kernel<__bf16>, gl, dim3(256), 0, hs, g);
       hipLaunchKernelGGL(bp_right_kernel<__bf16>, gr, dim3(256), 0, hs, g);
     } else {
-      hipLaunchKernelGGL((bp_left_kernel<float, false>), gl, dim3(256), 0, hs, g);
+      hipLaunchKernelGGL(bp_left_kernel<float>, gl, dim3(256), 0, hs, g);
       hipLaunchKernelGGL(bp_right_kernel<float>, gr, dim3(256), 0, hs, g);
     }
     const dr_status st = launch_status();

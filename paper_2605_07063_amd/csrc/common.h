@@ -91,6 +91,13 @@ __device__ __forceinline__ v4s lds_read_tr16(const unsigned char* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(p));
 }
 
+// two fp32 values as bf16, rounded to nearest even, a in the low half
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+  unsigned r;
+  asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
 // swizzle of the 32-byte slots of a token row: rows that one transposing
 // read touches (q = r & 3 and bit 3 of r) land in distinct bank groups
 __device__ __forceinline__ int slot_xor(int r) { return (r & 3) | (((r >> 3) & 1) << 2); }

@@ -285,12 +285,6 @@ struct Planes8 {
   u32x4 p[3];   // eight values, three bf16 parts
 };
 
-__device__ __forceinline__ unsigned pack_bf16(float a, float b) {   // round to nearest even, a in the low half
-  unsigned r;
-  asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-
 __device__ __forceinline__ void split2(float a, float b, unsigned& p0, unsigned& p1, unsigned& p2) {
   p0 = pack_bf16(a, b);
   const float a1 = a - __uint_as_float(p0 << 16), b1 = b - __uint_as_float(p0 & 0xffff0000u);

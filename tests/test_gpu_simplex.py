@@ -125,6 +125,36 @@ def test_back_projection_matches_oracle(dtype, tol, specs):
         assert rel(host64(got), ref) <= tol
 
 
+@pytest.mark.parametrize("specs,shift", [
+    ([(8, 8, 1, 1), (136, 120, 7, 33), (256, 128, 64, 32)], 0),      # less than a tile, ragged tiles, odd sketch widths
+    ([(2048, 2176, 33, 64), (2056, 2040, 64, 40), (64, 1160, 16, 17)], 0),   # two row tiles per workgroup, the last alone
+    ([(136, 264, 16, 16)], 1),                                       # projectors off a 16-byte boundary: the fp32 path
+])
+def test_back_projection_tiles(specs, shift):
+    """bf16 projectors: both products in one kernel.  T is split to 2^-24 and its 3 k_out products per element are
+    summed in fp32: 1e-6 of the largest |P_out|^T |T|."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(11)
+    layers, off = [], 3
+    for d_in, d_out, k_in, k_out in specs:
+        L = {}
+        for nm, k, d in (("p_in", k_in, d_in), ("p_out", k_out, d_out)):
+            buf = torch.randn(k * d + shift, generator=g, device=DEV).bfloat16()
+            L[nm] = buf[shift:].view(k, d)
+        layers.append(dict(L, col_offset=off))
+        off += k_in * k_out
+    u = torch.randn(off, generator=g, device=DEV)
+    U = api.back_project(layers, u)
+    torch.cuda.synchronize()
+    for got, L in zip(U, layers):
+        k_out, k_in = L["p_out"].shape[0], L["p_in"].shape[0]
+        X = u[L["col_offset"]:L["col_offset"] + k_out * k_in].double().view(k_out, k_in)
+        T = X @ L["p_in"].double()
+        scale = (X.abs() @ L["p_in"].double().abs()).max() * L["p_out"].double().abs().sum(0).max()
+        err = (got.double().view(L["p_out"].shape[1], -1) - L["p_out"].double().t() @ T).abs().max()
+        assert float(err) <= 1e-6 * float(scale)
+
+
 def test_back_projection_of_the_small_block_update():
     """Sketch-space top-k update of the small-block workload (dr_combine) back
     to parameter space: 8 layers of 2048 x 2048 from 64 x 64 sketches."""
