@@ -170,7 +170,7 @@ __device__ __forceinline__ float bf16_val(unsigned short h) { return __uint_as_f
 __device__ __forceinline__ float bf16_lo(unsigned h) { return __uint_as_float(h << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned h) { return __uint_as_float(h & 0xffff0000u); }
 
-// bf16 projectors (16-byte aligned, d_in and d_out multiples of 8), both
+// bf16 projectors (P_out 16-byte aligned, d_in and d_out multiples of 8), both
 // products in one kernel: a workgroup takes 128 columns of U and `per` tiles
 // of 128 rows.  It makes T = X' P_in of its columns once (fp32 MFMA 16x16x4,
 // k_out x 128, P_in and X' staged in LDS) and leaves it in LDS as three bf16
@@ -228,7 +228,20 @@ __global__ __launch_bounds__(256, 2) void bp_mfma_kernel(BpArgs g, int per) {
     float* xs = reinterpret_cast<float*>(lds + kBmSlab);                // X'[a][b]
     const float* x = g.x[l];
     float xv[kBpMaxK * kBpMaxK / 256];
-    load_p(static_cast<const unsigned short*>(g.p_in[l]), k_in, c0, d_in);
+    const unsigned short* pi = static_cast<const unsigned short*>(g.p_in[l]);
+    if ((reinterpret_cast<uintptr_t>(pi) & 15) == 0) {
+      load_p(pi, k_in, c0, d_in);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int r = pr + 16 * u;
+        const bool ok = r < k_in && c0 + pc < d_in;
+        const unsigned short* q = pi + (ok ? (long long)r * d_in + c0 + pc : 0);
+        // (q[0 .. 7] is inside P_in also where it stands for nothing: d_in >= 8)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) pv[u][v] = ok ? q[2 * v] | (unsigned)q[2 * v + 1] << 16 : 0u;
+      }
+    }
 #pragma unroll
     for (int u = 0; u < kBpMaxK * kBpMaxK / 256; ++u) {
       const int e = tid + 256 * u, a = e >> 6, b = e & 63;
@@ -389,7 +402,7 @@ extern "C" dr_status dr_back_project(const dr_layer* layers, int num_layers, dr_
       g.x[j] = u + L.col_offset;
       g.T[j] = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + o);
       o = align_up(o + (size_t)L.k_out * (size_t)L.d_in * 6, 256);   // fp32 T or three bf16 planes
-      mfma = mfma && L.d_in % 8 == 0 && L.d_out % 8 == 0 && aligned16(L.p_in) && aligned16(L.p_out);
+      mfma = mfma && L.d_in % 8 == 0 && L.d_out % 8 == 0 && aligned16(L.p_out);
       g.U[j] = U + u_offset[f + j];
       g.k_in[j] = (int)L.k_in;
       g.k_out[j] = (int)L.k_out;

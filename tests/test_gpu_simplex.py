@@ -126,9 +126,12 @@ def test_back_projection_matches_oracle(dtype, tol, specs):
 
 
 @pytest.mark.parametrize("specs,shift", [
-    ([(8, 8, 1, 1), (136, 120, 7, 33), (256, 128, 64, 32)], 0),      # less than a tile, ragged tiles, odd sketch widths
-    ([(2048, 2176, 33, 64), (2056, 2040, 64, 40), (64, 1160, 16, 17)], 0),   # two row tiles per workgroup, the last alone
-    ([(136, 264, 16, 16)], 1),                                       # projectors off a 16-byte boundary: the fp32 path
+    # less than a tile, ragged tiles, odd sketch widths
+    ([(8, 8, 1, 1), (136, 120, 7, 33), (256, 128, 64, 32)], (0, 0)),
+    # two row tiles per workgroup, the last alone
+    ([(2048, 2176, 33, 64), (2056, 2040, 64, 40), (64, 1160, 16, 17)], (0, 0)),
+    ([(136, 264, 16, 16)], (1, 0)),   # P_in off a 16-byte boundary: read by elements
+    ([(136, 264, 16, 16)], (0, 1)),   # P_out off a 16-byte boundary: the fp32 path
 ])
 def test_back_projection_tiles(specs, shift):
     """bf16 projectors: both products in one kernel.  T is split to 2^-24 and its 3 k_out products per element are
@@ -138,9 +141,9 @@ def test_back_projection_tiles(specs, shift):
     layers, off = [], 3
     for d_in, d_out, k_in, k_out in specs:
         L = {}
-        for nm, k, d in (("p_in", k_in, d_in), ("p_out", k_out, d_out)):
-            buf = torch.randn(k * d + shift, generator=g, device=DEV).bfloat16()
-            L[nm] = buf[shift:].view(k, d)
+        for nm, k, d, sh in (("p_in", k_in, d_in, shift[0]), ("p_out", k_out, d_out, shift[1])):
+            buf = torch.randn(k * d + sh, generator=g, device=DEV).bfloat16()
+            L[nm] = buf[sh:].view(k, d)
         layers.append(dict(L, col_offset=off))
         off += k_in * k_out
     u = torch.randn(off, generator=g, device=DEV)
