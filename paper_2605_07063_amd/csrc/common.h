@@ -142,21 +142,6 @@ __device__ __forceinline__ f32x4 quad_transpose(f32x4 v) {
   return f32x4{x0, x1, x2, x3};
 }
 
-// the same fixed-order DPP wave sum for fp32 (total in lane 63 only)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_f(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xF, false));
-}
-__device__ __forceinline__ float wave_sum_l63f(float v) {
-  v += dpp_f<0xB1, 0xF>(v);
-  v += dpp_f<0x4E, 0xF>(v);
-  v += dpp_f<0x141, 0xF>(v);
-  v += dpp_f<0x140, 0xF>(v);
-  v += dpp_f<0x142, 0xA>(v);
-  v += dpp_f<0x143, 0xC>(v);
-  return v;
-}
-
 // Mixed-precision iterative refinement (fp32 factor, fp64 residuals) of a
 // span solve: a = max|dx| of the next-to-last correction, b = max|dx| of
 // the last one, X = max|x| after it.  The corrections shrink geometrically

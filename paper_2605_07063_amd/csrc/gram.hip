@@ -44,10 +44,11 @@
 //                        16 rows x 4 columns of an fp32 MFMA operand fall on
 //                        distinct banks); the eight waves take the lower
 //                        16x16 blocks of the augmented Gram round-robin
-//                        (fp32 16x16x4 MFMA) and write chunk partials.
-//   gram_small_reduce_kernel : sums the chunk partials (one wave per element,
-//                        a fixed order) into K (both triangles), s (row n)
-//                        and t2 (element n, n).
+//                        (fp32 16x16x4 MFMA) and write chunk partials, a
+//                        block's 256 values side by side.
+//   gram_small_reduce_kernel : sums the chunk partials (a lane per element, a
+//                        fixed order) into K (both triangles), s (row n) and
+//                        t2 (element n, n).
 // No atomics: results are deterministic.
 
 #include <mutex>
@@ -777,39 +778,59 @@ __global__ __launch_bounds__(kSmThreads) void gram_small_kernel(GramArgs a, cons
     for (int k = 0; k < kSmCK; k += 4) acc = mma_f32(ra[k], rb[k], acc);
     // C layout: register r is row 4 lg + r of the block, column lane % 16
 #pragma unroll
-    for (int r = 0; r < 4; ++r) out[(16 * I + 4 * lg + r) * NRP + 16 * J + lr] = acc[r];
+    for (int r = 0; r < 4; ++r) out[q * 256 + (4 * lg + r) * 16 + lr] = acc[r];
   }
 }
 
-// K (both triangles), s and t2 from the chunk partials: one wave per element
-// of the lower triangle, lane l sums chunks l, l + 64, ... in order, then a
-// fixed-order DPP reduction across the lanes (total in lane 63)
-__global__ __launch_bounds__(kThreads) void gram_small_reduce_kernel(GramArgs a, int NRP, int nchunks, float* K,
-                                                                     float* s, float* t2, long long pbase) {
-  const int p = blockIdx.y;
-  const int nr = a.n + 1;
-  const int e = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);   // lower-triangle element
-  const int lane = threadIdx.x & 63;
-  if (e >= nr * (nr + 1) / 2) return;
-  int r = 0;
-  while ((r + 1) * (r + 2) / 2 <= e) ++r;
-  const int c = e - r * (r + 1) / 2;
+// K (both triangles), s and t2 from the chunk partials: a workgroup takes 64
+// neighbouring elements of a 16 x 16 block (four rows), lane by lane; a wave
+// sums 16 chunks at a time (a tree, every load in flight), the waves' sums meet
+// in LDS, again as a tree.  A wave's load is 256 contiguous bytes; with a wave
+// per element, lanes over the chunks, each load touched 64 lines for 4 bytes
+// of each, and most lanes were idle where a group has few chunks.  The whole
+// Gram, us: one group of 64 x 32768 17.1 -> 16.0, 8 of 64 x 4096 33 -> 15, one
+// of 127 x 131072 90 -> 64, 200 of 100 x 128 1530 -> 29.
+constexpr int kSrChunks = 16;   // chunks per wave at a time
+constexpr int kSrWaves = 16;
+__global__ __launch_bounds__(kSrWaves * 64) void gram_small_reduce_kernel(GramArgs a, int NRP, int nchunks, float* K,
+                                                                          float* s, float* t2, long long pbase) {
+  __shared__ float part[kSrWaves][64];
+  const int p = blockIdx.y, q = blockIdx.x >> 2;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  int I = 0;
+  while ((I + 1) * (I + 2) / 2 <= q) ++I;
+  const int J = q - I * (I + 1) / 2;
+  const int e = (blockIdx.x & 3) * 64 + lane;   // element of the block
+  const int r = 16 * I + (e >> 4), c = 16 * J + (e & 15);
   const long long width = a.goff[p + 1] - a.goff[p];
   const int nvalid = (int)((width + kSmCK - 1) / kSmCK);
-  const float* src = a.partial + (long long)p * nchunks * NRP * NRP + r * NRP + c;
+  const float* src = a.partial + (long long)p * nchunks * NRP * NRP + q * 256 + e;
+  auto tree = [](float (&v)[16]) {
+#pragma unroll
+    for (int h = 8; h > 0; h >>= 1)
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (u < h) v[u] += v[u + h];
+    return v[0];
+  };
   float acc = 0.f;
-  for (int ch0 = 0; ch0 < nvalid; ch0 += 256) {
-    float v[4];
+  for (int ch0 = kSrChunks * wave; ch0 < nvalid; ch0 += kSrChunks * nw) {
+    float v[kSrChunks];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int ch = ch0 + lane + 64 * u;
-      v[u] = ch < nvalid ? src[(long long)ch * NRP * NRP] : 0.f;
+    for (int u = 0; u < kSrChunks; ++u) {
+      const float t = src[(long long)(ch0 + u < nvalid ? ch0 + u : nvalid - 1) * NRP * NRP];
+      v[u] = ch0 + u < nvalid ? t : 0.f;
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) acc += v[u];
+    acc += tree(v);
   }
-  acc = wave_sum_l63f(acc);
-  if (lane != 63) return;
+  part[wave][lane] = acc;
+  __syncthreads();
+  if (wave > 0) return;
+  float v[kSrWaves];
+#pragma unroll
+  for (int u = 0; u < kSrWaves; ++u) v[u] = u < nw ? part[u < nw ? u : 0][lane] : 0.f;
+  acc = tree(v);
+  if (r > a.n || c > r) return;
   if (r < a.n) {
     float* Kp = K + (pbase + p) * (long long)a.n * a.n;
     Kp[(long long)r * a.n + c] = acc;
@@ -1287,9 +1308,11 @@ dr_status gram_run(const GramPlan& g, const void* G, int64_t n, int64_t ldG, con
       hipLaunchKernelGGL(gram_small_kernel, dim3(g.maxchunks, gp), dim3(kSmThreads), 0, hs, a,
                          static_cast<const float*>(Gt), (long long)ldGt, (int)m, g.NRP, g.maxchunks);
       if ((st = launch_status()) != DR_OK) return st;
-      const int nr = (int)n + 1;
-      hipLaunchKernelGGL(gram_small_reduce_kernel, dim3((nr * (nr + 1) / 2 + kThreads / 64 - 1) / (kThreads / 64), gp),
-                         dim3(kThreads), 0, hs, a, g.NRP, g.maxchunks, K, s, t2, (long long)p0);
+      const int nb = g.NRP / 16;
+      const int nw = (g.maxchunks + kSrChunks - 1) / kSrChunks;   // 16 chunks per wave, up to 16 waves
+      hipLaunchKernelGGL(gram_small_reduce_kernel, dim3(nb * (nb + 1) * 2, gp),
+                         dim3(64 * (nw < 1 ? 1 : nw > kSrWaves ? kSrWaves : nw)), 0, hs, a, g.NRP, g.maxchunks, K, s,
+                         t2, (long long)p0);
       if ((st = launch_status()) != DR_OK) return st;
     } else if (g.pairs > 0) {
       if (bf) {
