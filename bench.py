@@ -280,8 +280,9 @@ def run_llama(args, api, _lib, workloads, dev, peaks):
             algorithmic_bytes=by, avg_launch_ms=avg_blk, timed_calls=int(blk_ms.size)),
         # fp32 rows, (n(n+1) + 2n + 2 + m) kappa flops on 4 (n + m) kappa bytes:
         # about 61 flops per byte, above the fp32 MFMA ridge (157.3 / 8), so
-        # the Gram is priced against the fp32 MFMA peak
-        "gram_roofline": _roofline("dr_gram (fp32 rows: gram_tile_lds_kernel + reduce + target mean)", "mfma",
+        # the Gram is priced against the fp32 MFMA peak (its fp32 products run
+        # as six bf16 MFMA products of split values)
+        "gram_roofline": _roofline("dr_gram (fp32 rows: gram_split_kernel + gram_reduce_kernel)", "mfma",
                                    _gram_f32_flops(n, m, ktot), stage["gram"], F32_MFMA_PEAK_TFLOPS, "TFLOP/s",
                                    measured_peak=peaks.get("fp32_mfma_TFLOPs") if peaks else None,
                                    algorithmic_flops=_gram_f32_flops(n, m, ktot), algorithmic_bytes=N * ktot * 4.0),
@@ -848,9 +849,8 @@ def time_next_rows(api, layers, lens, n, T, wt, wc, goff, dev, K=None, s=None, r
         u.normal_()
         ms = _event_ms(lambda: api.dr_back_project(layers, u, U, offs, workspace=bws), reps)
         wbytes = 4.0 * sum(sizes)
-        res["back_project"] = {"ms": ms, "roofline": _roofline("dr_back_project (bp_left_kernel + bp_mfma_kernel)",
-                                                               "hbm", wbytes, ms, HBM_PEAK_GBS, "GB/s",
-                                                               algorithmic_bytes=wbytes)}
+        res["back_project"] = {"ms": ms, "roofline": _roofline("dr_back_project (bp_mfma_kernel)", "hbm", wbytes, ms,
+                                                               HBM_PEAK_GBS, "GB/s", algorithmic_bytes=wbytes)}
     return res
 
 

@@ -404,6 +404,30 @@ def test_span_batched_groups_and_hand_fixture(golden_dir):
         assert abs(float(r2[0]) - c["resid2"]) <= 1e-5
 
 
+@pytest.mark.parametrize("n,goff", [
+    (15, [0, 33412]),                  # n + 1 = 16: one block; more than 256 chunks, the last ragged
+    (16, [0, 0, 128, 2052, 35000]),    # a second block of one row; groups of 0, 1, 16 and 258 chunks
+    (63, [0, 2048, 4224]),             # 16 and 17 chunks: one wave full, a second begun
+    (127, [0, 40000]),                 # the largest n
+    (31, [0, 4]),
+])
+def test_gram_small_chunk_sums(n, goff):
+    """The reduction of the chunk partials at the edges of its waves and passes.  An element is a sum of fp32 products
+    per 128 columns and a tree of at most 16 + 16 partials: 128 + 8 + passes roundings of |row| . |row|."""
+    G, Gt = rand((n, goff[-1]), 900 + n), rand((3, goff[-1]), 901 + n)
+    K, s, t2 = api.gram(G, Gt, goff)
+    torch.cuda.synchronize()
+    for p in range(len(goff) - 1):
+        A = G[:, goff[p]:goff[p + 1]].double()
+        b = Gt[:, goff[p]:goff[p + 1]].double().mean(0)
+        R = torch.cat([A, b[None]])
+        ref, lim = R @ R.t(), (128 + 16) * 2.0 ** -24 * (R.abs() @ R.abs().t())
+        got = torch.zeros_like(ref)
+        got[:n, :n], got[n, :n], got[:n, n], got[n, n] = K[p].double(), s[p].double(), s[p].double(), t2[p].double()
+        assert bool(((got - ref).abs() <= lim).all())
+        assert torch.equal(K[p], K[p].t())
+
+
 # --------------------------------------------------------------------------- cone
 
 @pytest.mark.parametrize("n,kappa,iters,tol", [
