@@ -76,7 +76,7 @@ struct GramArgs {
   int P;
   int NT, pairs, CK, maxchunks;
   float* partial;                   // [P][pairs][maxchunks][kTile*kTile]
-  float* K;                         // outputs (gram_tile_lds_kernel writes them itself when
+  float* K;                         // outputs (gram_split_kernel writes them itself when
   float* s;                         // maxchunks == 1); group p of the launch is pbase + p
   float* t2;
   long long pbase;
