@@ -1324,7 +1324,9 @@ dr_status gram_run(const GramPlan& g, const void* G, int64_t n, int64_t ldG, con
       if ((st = launch_status()) != DR_OK) return st;
       if (bf || g.maxchunks > 1) {   // fp32 tiles of a single chunk are written by the tile kernel
         const dim3 rg(g.pairs, gp, kTile * kTile / 256);
-        if (g.maxchunks >= 32)
+        // four threads per element where the blocks alone would not fill the chip (256 rows: 160 blocks; 512
+        // bf16 rows have 576: 45.1 us a Gram with one thread, 46.2 with four)
+        if (g.maxchunks >= 32 && g.pairs * gp * (kTile * kTile / 256) < 512)
           hipLaunchKernelGGL(gram_reduce_kernel<4>, rg, dim3(1024), 0, hs, a, K, s, t2, (long long)p0);
         else
           hipLaunchKernelGGL(gram_reduce_kernel<1>, rg, dim3(256), 0, hs, a, K, s, t2, (long long)p0);
