@@ -20,9 +20,13 @@
 // contiguous in memory (token rows of x / dy, rows of gbar*), staged by
 // buffer->LDS DMA in 64-wide steps in the swizzled 128-byte-row layout.
 // Rows past the last token and columns past a width load as zeros
-// (out-of-range buffer offsets), so padding is never read.  A tile whose rows
-// could lie further apart than a 32-bit offset takes rows of one example
-// only (`packed` = 0: rows t0 .. of example i, blocks of 256 or 128).
+// (out-of-range buffer offsets), so padding is never read.  Rows are addressed
+// by 32-bit offsets from a tile's first example.  A block whose rows lie
+// further apart, over a run of empty examples, is taken in pieces, each from
+// its own first example (PIECES, where the batch is large enough for that: the
+// loop over pieces costs registers that the others need); where full examples
+// already would be too far apart, a tile takes rows of one example only
+// (`packed` = 0: rows t0 .. of example i, blocks of 256 or 128).
 // Partial sums go to fp64 workspace slots and are reduced in a fixed order.
 
 #include "tile256.h"
@@ -113,6 +117,7 @@ struct ScoreArgs {
   int num_layers;
   int T, n, m;
   int packed;                // rows of a tile: packed positions, or one example's tokens
+  int span;                  // packed: examples (empty ones too) that 32-bit offsets reach
   int SB;                    // GIP: 128-row blocks of the target tokens (upper bound)
   const int* len;            // [n + m] or null
   const int* cum;            // [n + 1] token prefix of the general examples, then [m + 1] of the targets
@@ -162,12 +167,20 @@ struct TileRows {
   int tok[ROWS];
 };
 
-// Fills the table for row block rt of `cnt` examples with prefix `cum` (a
-// whole 256-thread workgroup; ends with a barrier) and returns the number of
-// valid rows; e0: the example of the first row, e_last: of the last.
+// position past the last row of row block rt
 template <int ROWS>
+__device__ __forceinline__ int block_end(const int* cum, int cnt, int rt) {
+  const int total = cum[cnt], p0 = rt * ROWS;
+  return total - p0 < ROWS ? total : p0 + ROWS;
+}
+
+// Fills the table for row block rt of `cnt` examples with prefix `cum`, from
+// position p0 of the block on (packed) as far as `span` examples reach: a
+// whole 256-thread workgroup; ends with a barrier.  Returns the number of
+// valid rows; e0: the example of the first row, e_last: of the last.
+template <bool PIECES, int ROWS>
 __device__ __forceinline__ int tile_rows(TileRows<ROWS>& tr, const int* cum, const int* len, int first, int cnt, int T,
-                                         int packed, int rt, int& e0, int& e_last) {
+                                         int packed, int span, int rt, int p0, int& e0, int& e_last) {
   const int tid = threadIdx.x;
   if (!packed) {
     const int TB = (T + ROWS - 1) / ROWS;
@@ -184,15 +197,19 @@ __device__ __forceinline__ int tile_rows(TileRows<ROWS>& tr, const int* cum, con
     __syncthreads();
     return L - t0 < ROWS ? L - t0 : ROWS;
   }
-  const int total = cum[cnt], p0 = rt * ROWS;
-  const int rows = total - p0 < ROWS ? total - p0 : ROWS;
-  int lo = 0, hi = cnt;   // the last example with cum <= p0 (not empty, since p0 < total)
+  int lo = 0, hi = cnt;   // the last example with cum <= p0 (not empty: p0 is below the total)
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (cum[mid] <= p0) lo = mid;
     else hi = mid - 1;
   }
   e0 = lo;
+  int end = block_end<ROWS>(cum, cnt, rt);
+  if (PIECES && e0 + span < cnt) {
+    const int reach = cum[e0 + span];
+    end = reach < end ? reach : end;
+  }
+  const int rows = end - p0;
   // at most ROWS non-empty examples; runs of empty ones can only push an
   // example past the staged prefix, which is then read from memory
   for (int r = tid; r <= ROWS; r += 256) tr.cum[r] = e0 + r <= cnt ? cum[e0 + r] - p0 : 0x7fffffff;
@@ -214,13 +231,13 @@ __device__ __forceinline__ int tile_rows(TileRows<ROWS>& tr, const int* cum, con
 // row sums of a tile (rs[h][row], two column halves) -> one partial per
 // example of the tile, in slot (row block + example) of a column block: the
 // pairs (row block, example) in order step at least one of the two, so the
-// slots are distinct (row block alone when it holds rows of one example)
+// slots are distinct (row block alone when it holds rows of one example);
+// p0: position of the tile's first row
 template <int ROWS>
 __device__ __forceinline__ void tile_example_sums(const TileRows<ROWS>& tr, const double (*rs)[ROWS], const int* cum,
-                                                  int rows, int packed, int rt, int e0, int e_last, double* part,
-                                                  int stride, int col) {
+                                                  int rows, int packed, int rt, int p0, int e0, int e_last,
+                                                  double* part, int stride, int col) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int p0 = rt * ROWS;
   for (int e = e0 + w; e <= e_last; e += 4) {
     const int r = e - e0;
     int lo = r <= ROWS ? tr.cum[r] : cum[e] - p0, hi = r + 1 <= ROWS ? tr.cum[r + 1] : cum[e + 1] - p0;
@@ -244,6 +261,7 @@ __device__ __forceinline__ void tile_example_sums(const TileRows<ROWS>& tr, cons
 // with both parts of gbar* staged (one workgroup of 96 KB per CU, its DMA
 // waited for at every fragment read) took 0.92 ms per layer.  Whole call
 // 8.03 -> 2.55 ms.
+template <bool PIECES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void pip_kernel(ScoreArgs a) {
   // one LDS object: beside a second one the compiler makes every fragment
   // read wait for all DMA in flight (7.9 instead of 1.9 ms on the small block)
@@ -271,8 +289,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int TB = (a.T + kTileRows - 1) / kTileRows, i = rt / TB;
     if ((rt - i * TB) * kTileRows >= clamp_len(a.len, i, a.T)) return;
   }
+  for (int p0 = rt * kTileRows, rows;; p0 += rows) {   // one turn, or one per piece
   int e0, e_last;
-  const int rows = tile_rows(tr, a.cum, a.len, 0, a.n, a.T, a.packed, rt, e0, e_last);
+  rows = tile_rows<PIECES>(tr, a.cum, a.len, 0, a.n, a.T, a.packed, a.span, rt, p0, e0, e_last);
   const int o0 = ob * kTileRows;
   const int d_in = L.d_in, d_out = L.d_out;
 
@@ -359,7 +378,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
   }
   __syncthreads();
-  tile_example_sums(tr, rs, a.cum, rows, a.packed, rt, e0, e_last, L.part, L.OB, ob);
+  tile_example_sums(tr, rs, a.cum, rows, a.packed, rt, p0, e0, e_last, L.part, L.OB, ob);
+  if (!PIECES || p0 + rows >= block_end<kTileRows>(a.cum, a.n, rt)) break;
+  __syncthreads();   // the next piece's table
+  }
 }
 
 // s[l][i] = scale * the sum of the example's partials over its row blocks
@@ -418,6 +440,7 @@ __global__ void split_kernel(const float* g, long long count, __bf16* hi, __bf16
 // follows the valid tokens (with one tile per pair of examples, 64 examples
 // of 32..128 tokens against 8 targets filled 39 % of the products: whole call
 // over eight 2048 x 2048 layers 0.67 -> 0.26 ms, all layers in one launch).
+template <bool PIECES>
 __global__ __launch_bounds__(kSThreads, 2) void gip_kernel(ScoreArgs a) {
   constexpr int kRing = 2 * 2 * kSPanel;
   __shared__ __attribute__((aligned(1024))) unsigned char
@@ -443,9 +466,12 @@ __global__ __launch_bounds__(kSThreads, 2) void gip_kernel(ScoreArgs a) {
     const int i = rt / TB, j = sb / TB;
     if ((rt - i * TB) * kST >= clamp_len(a.len, i, a.T) || (sb - j * TB) * kST >= clamp_len(a.len, a.n + j, a.T)) return;
   }
+  const int* tcum = a.cum + a.n + 1;   // the targets' prefix
+  for (int p0 = rt * kST, rows;; p0 += rows) {   // one turn each, or one per piece
   int e0, e_last, f0, f_last;
-  const int rows = tile_rows(tr, a.cum, a.len, 0, a.n, a.T, a.packed, rt, e0, e_last);
-  const int cols = tile_rows(tc, a.cum + a.n + 1, a.len, a.n, a.m, a.T, a.packed, sb, f0, f_last);
+  rows = tile_rows<PIECES>(tr, a.cum, a.len, 0, a.n, a.T, a.packed, a.span, rt, p0, e0, e_last);
+  for (int c0 = sb * kST, cols;; c0 += cols) {
+  cols = tile_rows<PIECES>(tc, tcum, a.len, a.n, a.m, a.T, a.packed, a.span, sb, c0, f0, f_last);
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = w >> 1, wc = w & 1, lr = lane & 15, lg = lane >> 4;
@@ -492,10 +518,18 @@ __global__ __launch_bounds__(kSThreads, 2) void gip_kernel(ScoreArgs a) {
       v += dpp_d<0x4E, 0xF>(v);
       v += dpp_d<0x141, 0xF>(v);
       v += dpp_d<0x140, 0xF>(v);
-      if (lr == 0) rs[wc][64 * wr + 16 * p + 4 * lg + r] = v;
+      if (lr == 0) {
+        double& sum = rs[wc][64 * wr + 16 * p + 4 * lg + r];
+        sum = !PIECES || c0 == sb * kST ? v : sum + v;
+      }
     }
+  if (!PIECES || c0 + cols >= block_end<kST>(tcum, a.m, sb)) break;
+  }
   __syncthreads();
-  tile_example_sums(tr, rs, a.cum, rows, a.packed, rt, e0, e_last, L.part, a.SB, sb);
+  tile_example_sums(tr, rs, a.cum, rows, a.packed, rt, p0, e0, e_last, L.part, a.SB, sb);
+  if (!PIECES || p0 + rows >= block_end<kST>(a.cum, a.n, rt)) break;
+  __syncthreads();   // the next piece's table
+  }
 }
 
 __global__ void fill_kernel(float* p, long long count, float v) {
@@ -526,18 +560,25 @@ int group_end(const dr_layer* layers, int num_layers, int first, int method) {
   return l;
 }
 
+// examples whose rows a 32-bit offset from the first one reaches
+int64_t score_span(const dr_layer* layers, int num_layers, int64_t T) {
+  int64_t span = (int64_t)1 << 24;
+  for (int l = 0; l < num_layers && T > 0; ++l) {
+    const int64_t ld = layers[l].ldx > layers[l].lddy ? layers[l].ldx : layers[l].lddy;
+    const int64_t e = ((int64_t)kOobOffset - 64) / (T * ld * 2);
+    span = e < span ? e : span;
+  }
+  return span;
+}
+
 // Packed tiles address a tile's rows from its first example with 32-bit
-// offsets, and positions are 32-bit: possible when the examples that one
-// tile can hold span less than 4 GiB.
+// offsets, and positions are 32-bit: possible when the full examples that one
+// tile can hold span less than 4 GiB (with empty ones between them the tile is
+// taken in pieces).
 bool score_packed(const dr_layer* layers, int num_layers, int64_t n, int64_t m, int64_t T, int64_t rows) {
   const int64_t most = n > m ? n : m;
-  const int64_t span = (most < rows ? most : rows) * T;
   if (most * T >= ((int64_t)1 << 31) - 2 * rows) return false;
-  for (int l = 0; l < num_layers; ++l) {
-    const int64_t ld = layers[l].ldx > layers[l].lddy ? layers[l].ldx : layers[l].lddy;
-    if ((uint64_t)span * (uint64_t)ld * 2 >= (uint64_t)kOobOffset - 64) return false;
-  }
-  return true;
+  return score_span(layers, num_layers, T) >= (most < rows ? most : rows);
 }
 
 // 128-token column blocks of the m targets (upper bound)
@@ -689,6 +730,7 @@ extern "C" dr_status dr_score_exact(const dr_layer* layers, int num_layers, int6
     a.n = (int)n;
     a.m = (int)m;
     a.packed = score_packed(layers + l0, cnt, n, m, T, rows);
+    a.span = (int)score_span(layers + l0, cnt, T);
     a.SB = (int)gip_cols(m, T, a.packed);
     a.len = len;
     a.cum = cum;
@@ -720,14 +762,17 @@ extern "C" dr_status dr_score_exact(const dr_layer* layers, int num_layers, int6
     // valid tokens return at once
     const int64_t R = a.packed ? (n * T + rows - 1) / rows : n * ((T + rows - 1) / rows);
     const unsigned grid = (unsigned)((R * cols + 255) / 256 * 256);
+    const bool pieces = a.packed && (n > m ? n : m) > a.span;
     const dim3 rgrid((unsigned)((n + 3) / 4), (unsigned)cnt);
     if (method == DR_SCORE_PIP) {
       hipLaunchKernelGGL(split_kernel, dim3((unsigned)((goff[cnt] + 255) / 256)), dim3(256), 0, hs,
                          (const float*)gstar, (long long)goff[cnt], hi, lo);
-      if (grid > 0) hipLaunchKernelGGL(pip_kernel, dim3(grid), dim3(256), 0, hs, a);
+      if (grid > 0)
+        hipLaunchKernelGGL(pieces ? pip_kernel<true> : pip_kernel<false>, dim3(grid), dim3(256), 0, hs, a);
       hipLaunchKernelGGL((score_reduce_kernel<kTileRows, true>), rgrid, dim3(256), 0, hs, a, sl, 1.0);
     } else {
-      if (grid > 0) hipLaunchKernelGGL(gip_kernel, dim3(grid), dim3(kSThreads), 0, hs, a);
+      if (grid > 0)
+        hipLaunchKernelGGL(pieces ? gip_kernel<true> : gip_kernel<false>, dim3(grid), dim3(kSThreads), 0, hs, a);
       hipLaunchKernelGGL((score_reduce_kernel<kST, false>), rgrid, dim3(256), 0, hs, a, sl, 1.0 / (double)m);
     }
     if ((st = launch_status()) != DR_OK) return st;

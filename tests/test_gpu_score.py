@@ -134,6 +134,22 @@ def test_rows_further_apart_than_a_tile_can_address():
     check_all(layers, n, m, lens, ["gip", "pip"])
 
 
+def test_empty_examples_between_the_rows_of_a_tile():
+    """Runs of empty examples inside one tile (general rows, and targets) over which the examples lie more than 4 GiB
+    apart, although as many examples as a tile has rows do not.  What 32-bit offsets would wrap to is padding (NaN)."""
+    n, m, T, ld = 700, 600, 8, 524288      # 8 MiB an example: 512 of them reach 4 GiB
+    lens = torch.zeros(n + m, dtype=torch.int32)
+    for i, L in ((0, 8), (2, 3), (514, 5), (600, 8), (601, 1), (699, 7), (n, 8), (n + 1, 2), (n + 520, 8), (n + 599, 4)):
+        lens[i] = L
+    lens[603:640] = 8                      # a second tile of 128 rows
+    lens = lens.to(DEV)
+    layers = make([(72, 136)], n + m, T, lens, seed=8)
+    wide = torch.empty((n + m) * T * ld, dtype=torch.bfloat16, device=DEV).view(n + m, T, ld)
+    wide[:, :, :72] = layers[0]["x"]
+    layers[0]["x"] = wide[:, :, :72]
+    check_all(layers, n, m, lens, ["gip", "pip"])
+
+
 def test_layer_groups():
     """More layers than one group holds, of different widths."""
     n, m, T = 3, 2, 20
