@@ -375,6 +375,7 @@ struct PackArgs {
   int xcd;              // 1: number workgroups XCD by XCD (all layers of the launch alike)
   int out_vec4;         // 1: S rows and every layer's column offset are 16-byte aligned
   int max_tiles;        // WL * KS: tile slots per layer
+  int span;             // examples (empty ones too) that 32-bit offsets reach
   const int* cum;       // [N + 2]: exclusive prefix of the clamped lengths, then R
   const int* tile_ex;   // [max_tiles] example holding the first position of each tile, -1 if empty
   float* S;
@@ -455,7 +456,11 @@ __device__ __forceinline__ uint2 split_pack(float a, float b) {
   return make_uint2((ua >> 16) | (ub & 0xffff0000u), (__float_as_uint(ra) >> 16) | (__float_as_uint(rb) & 0xffff0000u));
 }
 
-template <bool BF16, int KIN, int KOUT>
+// Rows are addressed by 32-bit offsets from a tile's first example.  PIECES
+// (batches of more than a.span examples): a tile whose rows lie further apart,
+// over a run of empty examples, is taken in pieces, each from its own first
+// example.
+template <bool BF16, int KIN, int KOUT, bool PIECES>
 __global__ __launch_bounds__(kThreads, 2) void sketch_packed_kernel(PackArgs a) {
   using E = Tr<BF16>;
   constexpr int NSUB = 2;                   // MFMA operand vectors per row per step
@@ -494,11 +499,28 @@ __global__ __launch_bounds__(kThreads, 2) void sketch_packed_kernel(PackArgs a) 
   const LayerArg& L = a.L[li];
   const int* cum = a.cum;
   for (int kt = 0; kt < a.KS; ++kt) {
-  const int p0 = r_lo + kt * kTokTile;
-  const int pend = p0 + kTokTile < r_hi ? p0 + kTokTile : r_hi;   // this tile's positions: [p0, pend)
-  if (p0 >= pend) break;
+  const int t0 = r_lo + kt * kTokTile;
+  const int tend = t0 + kTokTile < r_hi ? t0 + kTokTile : r_hi;   // this tile's positions: [t0, tend)
+  if (t0 >= tend) break;
   const int tile = wg * a.KS + kt;
-  const int e0 = a.tile_ex[tile];
+  const int tile_e0 = a.tile_ex[tile];
+  for (int p0 = t0, pend;; p0 = pend) {   // the tile's rows: [p0, pend), all of it or a piece
+  int e0 = tile_e0;
+  pend = tend;
+  if constexpr (PIECES) {
+    if (p0 > t0) {   // the last example with cum <= p0
+      int hi = a.N;
+      while (e0 < hi) {
+        const int mid = (e0 + hi + 1) >> 1;
+        if (cum[mid] <= p0) e0 = mid;
+        else hi = mid - 1;
+      }
+    }
+    if (e0 + a.span < a.N) {
+      const int reach = cum[e0 + a.span];
+      pend = reach < pend ? reach : pend;
+    }
+  }
   // cum[e0 .. e0 + 128] staged once in LDS.  A tile holds at most 128
   // non-empty examples; runs of empty ones in between can only push an
   // example past the staged range, which then reads cum from memory.
@@ -715,9 +737,9 @@ __global__ __launch_bounds__(kThreads, 2) void sketch_packed_kernel(PackArgs a) 
     }
     }
     DR_LDS_SYNC();
-    const bool inside = ce >= p0 && ce1 <= pend;
+    const bool inside = ce >= t0 && ce1 <= tend;
     float* out = inside ? a.S + (long long)e * a.ldS + L.col_offset
-                        : a.partial + (((long long)li * a.max_tiles + tile) * 2 + (e == e0 ? 0 : 1)) * SW;
+                        : a.partial + (((long long)li * a.max_tiles + tile) * 2 + (e == tile_e0 ? 0 : 1)) * SW;
     if (!inside || a.out_vec4) {
       // four consecutive lanes' entries are four consecutive columns of one
       // output row: float4 reads of the four regions and one float4 store
@@ -744,6 +766,8 @@ __global__ __launch_bounds__(kThreads, 2) void sketch_packed_kernel(PackArgs a) 
     }
     DR_LDS_SYNC();
   }
+  if (!PIECES || pend == tend) break;
+  }   // pieces of this tile
   }   // tiles of this workgroup
 }
 
@@ -867,17 +891,26 @@ int resident_slots() {
 
 int64_t packed_tiles(int64_t N, int64_t T) { return (N * T + kTokTile - 1) / kTokTile; }
 
+// examples whose rows a 32-bit offset from the first one reaches (with room
+// for one tile more)
+int64_t packed_span(const dr_layer* layers, int first, int count, int64_t T, dr_dtype dtype) {
+  const int64_t es = dtype == DR_BF16 ? 2 : 4;
+  int64_t span = (int64_t)1 << 24;
+  for (int j = first; j < first + count && T > 0; ++j) {
+    const int64_t ld = layers[j].ldx > layers[j].lddy ? layers[j].ldx : layers[j].lddy;
+    const int64_t e = (((int64_t)kOobOffset - 1) / (ld * es) - kTokTile) / T;
+    span = e < span ? e : span;
+  }
+  return span;
+}
+
+// packed tiles: full operand steps only, and the full examples that a tile can
+// hold within reach (with empty ones between them it is taken in pieces)
 bool packed_ok(const dr_layer* layers, int first, int count, int64_t N, int64_t T, dr_dtype dtype) {
   const int64_t kc = dtype == DR_BF16 ? 64 : 32;
-  const int64_t es = dtype == DR_BF16 ? 2 : 4;
-  const int64_t span = (N < kTokTile ? N : kTokTile) * T + kTokTile;
-  for (int j = first; j < first + count; ++j) {
-    const dr_layer& L = layers[j];
-    if (L.d_in % kc || L.d_out % kc) return false;
-    const int64_t ld = L.ldx > L.lddy ? L.ldx : L.lddy;
-    if ((uint64_t)span * (uint64_t)ld * (uint64_t)es >= (uint64_t)kOobOffset) return false;
-  }
-  return true;
+  for (int j = first; j < first + count; ++j)
+    if (layers[j].d_in % kc || layers[j].d_out % kc) return false;
+  return packed_span(layers, first, count, T, dtype) >= (N < kTokTile ? N : kTokTile);
 }
 
 Plan plan(const dr_layer* layers, int num_layers, int64_t N, int64_t T, dr_dtype dtype, Launch* out) {
@@ -960,8 +993,14 @@ Plan plan(const dr_layer* layers, int num_layers, int64_t N, int64_t T, dr_dtype
 template <bool BF16, int KIN, int KOUT>
 void launch_t(const Launch& l, const SketchArgs& a, const PackArgs& pa, hipStream_t st) {
   if (l.packed) {
-    if (pa.max_tiles > 0)
-      hipLaunchKernelGGL((sketch_packed_kernel<BF16, KIN, KOUT>), dim3(l.count * pa.WL), dim3(kThreads), 0, st, pa);
+    if (pa.max_tiles > 0) {
+      if (pa.N > pa.span)
+        hipLaunchKernelGGL((sketch_packed_kernel<BF16, KIN, KOUT, true>), dim3(l.count * pa.WL), dim3(kThreads), 0, st,
+                           pa);
+      else
+        hipLaunchKernelGGL((sketch_packed_kernel<BF16, KIN, KOUT, false>), dim3(l.count * pa.WL), dim3(kThreads), 0,
+                           st, pa);
+    }
     hipLaunchKernelGGL((sketch_packed_reduce_kernel<KIN, KOUT>), dim3(l.count * pa.N * kPackReduceWGs<KIN, KOUT>), dim3(kThreads),
                        0, st, pa);
     return;
@@ -1085,6 +1124,7 @@ extern "C" dr_status dr_sketch_grads(const dr_layer* layers, int num_layers, int
       pa.WL = pl.WL;
       pa.KS = pl.KS;
       pa.max_tiles = pl.max_tiles;
+      pa.span = (int)packed_span(layers, l.first, l.count, T, dtype);
       pa.cum = reinterpret_cast<const int*>(ws + pl.off_cum);
       pa.tile_ex = reinterpret_cast<const int*>(ws + pl.off_tiles);
       pa.partial = reinterpret_cast<float*>(ws + pl.off_partial);

@@ -197,3 +197,20 @@ def test_unaligned_output_layout_matches_aligned():
         torch.cuda.synchronize()
         assert torch.equal(S[:, 3:3 + tot], S_ref)
         assert torch.isnan(S[:, :3]).all() and torch.isnan(S[:, 3 + tot:]).all()
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.bfloat16, TOL_SKETCH_BF16), (torch.float32, TOL_SKETCH_F32)])
+def test_empty_examples_between_the_rows_of_a_tile(dtype, tol):
+    """A run of empty examples inside one tile over which the examples lie more than 4 GiB apart, although as many
+    examples as a tile has rows do not.  What 32-bit offsets would wrap to is padding (NaN)."""
+    N, T, ld = 700, 8, 524288 if dtype == torch.bfloat16 else 262144   # 8 MiB an example: 512 of them reach 4 GiB
+    lens = torch.zeros(N, dtype=torch.int32)
+    for i, L in ((0, 8), (2, 3), (514, 5), (600, 8), (601, 1), (699, 7)):
+        lens[i] = L
+    lens[603:640] = 8
+    lens = lens.to(DEV)
+    layers = custom_layers([(128, 64, 16, 32)], N, T, dtype, lens, nan_padding=True, seed=9)
+    wide = torch.empty(N * T * ld, dtype=dtype, device=DEV).view(N, T, ld)
+    wide[:, :, :128] = layers[0]["x"]
+    layers[0]["x"] = wide[:, :, :128]
+    run_case(layers, lens, N, T, tol)
