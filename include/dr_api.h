@@ -416,7 +416,8 @@ size_t dr_update_workspace_size(const dr_layer* layers, int num_layers, int64_t 
  * groups of up to 16 whose gbar* hold at most 32 Mi elements together (or of
  * one layer); the workspace holds one group's gbar*.
  * Requirements as for dr_assemble_update; one layer's gbar* rows and one
- * example's rows must span less than 4 GiB (else DR_ERR_UNSUPPORTED).
+ * example's rows must span less than 4 GiB, and a group's tiles (at T tokens
+ * an example) number at most 65535 * 2^22 (else DR_ERR_UNSUPPORTED).
  * ------------------------------------------------------------------------- */
 dr_status dr_score_exact(const dr_layer* layers, int num_layers, int64_t n, int64_t m, int64_t T,
                          const int32_t* len, dr_dtype dtype, dr_score_method method, float* s,

@@ -123,6 +123,15 @@ struct ScoreArgs {
   const int* cum;            // [n + 1] token prefix of the general examples, then [m + 1] of the targets
 };
 
+// Tile of this workgroup: workgroup b (of a grid of kGridX columns) runs on
+// XCD b % 8, which takes runs of 32 tiles.
+constexpr int64_t kGridX = (int64_t)1 << 22;    // a launch takes fewer than 2^32 threads per dimension,
+constexpr int64_t kGridY = 65535;               // and as many rows
+__device__ __forceinline__ long long tile_index() {
+  const long long sl = (long long)blockIdx.y * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  return ((sl >> 5) * 8 + (blockIdx.x & 7)) * 32 + (sl & 31);
+}
+
 // exclusive prefixes of the clamped lengths: block 0 the n general examples,
 // block 1 the m targets
 __global__ __launch_bounds__(1024) void score_plan_kernel(const int* len, int n, int m, int T, int* cum) {
@@ -270,10 +279,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   double (*rs)[kTileRows] = reinterpret_cast<double (*)[kTileRows]>(lds + kTileRing);
   TileRows<kTileRows>& tr = *reinterpret_cast<TileRows<kTileRows>*>(lds + kTileRing + 2 * kTileRows * sizeof(double));
   const int R = a.packed ? (a.cum[a.n] + kTileRows - 1) / kTileRows : a.n * ((a.T + kTileRows - 1) / kTileRows);
-  // Workgroup b runs on XCD b % 8; each XCD takes runs of 32 tiles: eight
-  // column blocks of four row blocks, whose panels its L2 then holds.
-  const int x = blockIdx.x & 7, sl = blockIdx.x >> 3;
-  long long q = ((long long)(sl >> 5) * 8 + x) * 32 + (sl & 31);
+  // each XCD takes runs of 32 tiles: eight column blocks of four row blocks,
+  // whose panels its L2 then holds
+  long long q = tile_index();
   int li = 0;
   while (li < a.num_layers && q >= (long long)R * a.L[li].OB) {
     q -= (long long)R * a.L[li].OB;
@@ -451,10 +459,8 @@ __global__ __launch_bounds__(kSThreads, 2) void gip_kernel(ScoreArgs a) {
   const int TB = (a.T + kST - 1) / kST;
   const int R = a.packed ? (a.cum[a.n] + kST - 1) / kST : a.n * TB;
   const int C = a.packed ? (a.cum[a.n + 1 + a.m] + kST - 1) / kST : a.m * TB;
-  // XCD b % 8 takes runs of 32 tiles, the column blocks of a row block next
-  // to each other
-  const int x = blockIdx.x & 7, sl = blockIdx.x >> 3;
-  long long q = ((long long)(sl >> 5) * 8 + x) * 32 + (sl & 31);
+  // (the column blocks of a row block next to each other)
+  long long q = tile_index();
   const long long per = (long long)R * C;
   if (per == 0) return;
   const int li = (int)(q / per);
@@ -540,6 +546,7 @@ __global__ void fill_kernel(float* p, long long count, float v) {
 // ---------------------------------------------------------------- host
 
 struct ScorePlan {
+  double tiles;   // of the largest launch (upper bound)
   size_t off_wm, off_g, off_upd, off_hi, off_lo, off_cum, off_part, off_direct, bytes;
 };
 
@@ -586,9 +593,14 @@ int64_t gip_cols(int64_t m, int64_t T, bool packed) {
   return packed ? (m * T + kST - 1) / kST : m * ((T + kST - 1) / kST);
 }
 
-// row blocks of ROWS tokens over n examples: (row block, example) slots
+// row blocks over n examples (the most that the lengths allow)
+int64_t row_blocks(int64_t n, int64_t T, int64_t rows, bool packed) {
+  return packed ? (n * T + rows - 1) / rows : n * ((T + rows - 1) / rows);
+}
+
+// (row block, example) slots
 int64_t score_slots(int64_t n, int64_t T, int64_t rows, bool packed) {
-  return packed ? (n * T + rows - 1) / rows + n : n * ((T + rows - 1) / rows);
+  return row_blocks(n, T, rows, packed) + (packed ? n : 0);
 }
 
 dr_layer target_layer(const dr_layer& L, int64_t n, int64_t T) {
@@ -600,6 +612,7 @@ dr_layer target_layer(const dr_layer& L, int64_t n, int64_t T) {
 
 ScorePlan score_plan(const dr_layer* layers, int num_layers, int64_t n, int64_t m, int64_t T, int method) {
   int64_t gmax = 1, partmax = 1;
+  double tiles = 0.0;
   size_t updmax = 0, dirmax = 0;
   const int64_t rows = method == DR_SCORE_PIP ? kTileRows : kST;
   dr_layer t[kMaxScoreLayers];
@@ -607,15 +620,17 @@ ScorePlan score_plan(const dr_layer* layers, int num_layers, int64_t n, int64_t 
     const int l1 = group_end(layers, num_layers, l0, method);
     const bool packed = score_packed(layers + l0, l1 - l0, n, m, T, rows);
     const int64_t slots = score_slots(n, T, rows, packed);
-    int64_t g = 0, part = 0;
+    int64_t g = 0, cols = 0;
     for (int l = l0; l < l1; ++l) {
       g += layers[l].d_out * layers[l].d_in;
       t[l - l0] = target_layer(layers[l], n, T);
-      part += slots * (method == DR_SCORE_PIP ? (layers[l].d_out + kTileRows - 1) / kTileRows
-                                              : gip_cols(m, T, packed));
+      cols += method == DR_SCORE_PIP ? (layers[l].d_out + kTileRows - 1) / kTileRows : gip_cols(m, T, packed);
     }
+    const int64_t part = slots * cols;
     gmax = g > gmax ? g : gmax;
     partmax = part > partmax ? part : partmax;
+    const double nt = (double)row_blocks(n, T, rows, packed) * cols;
+    if (method != DR_SCORE_DIRECT) tiles = nt > tiles ? nt : tiles;
     if (method != DR_SCORE_GIP) {
       const size_t u = dr_update_workspace_size(t, l1 - l0, m, T, DR_BF16);
       updmax = u > updmax ? u : updmax;
@@ -629,6 +644,7 @@ ScorePlan score_plan(const dr_layer* layers, int num_layers, int64_t n, int64_t 
     l0 = l1;
   }
   ScorePlan p;
+  p.tiles = tiles;
   size_t o = 0;
   p.off_wm = o;     o = align_up(o + (size_t)(m > 0 ? m : 1) * 4, 256);
   p.off_g = o;      if (method != DR_SCORE_GIP) o = align_up(o + (size_t)gmax * 4, 256);
@@ -681,6 +697,7 @@ extern "C" dr_status dr_score_exact(const dr_layer* layers, int num_layers, int6
   dr_status st = validate_score(layers, num_layers, n, m, T, dtype, (int)method, s);
   if (st != DR_OK) return st;
   const ScorePlan pl = score_plan(layers, num_layers, n, m, T, (int)method);
+  if (pl.tiles > (double)(kGridX * kGridY)) return DR_ERR_UNSUPPORTED;
   if (!workspace || ws_bytes < pl.bytes) return DR_ERR_WORKSPACE;
   if (n == 0) return DR_OK;
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
@@ -760,19 +777,19 @@ extern "C" dr_status dr_score_exact(const dr_layer* layers, int num_layers, int6
     }
     // tiles over the most row blocks the lengths allow; workgroups past the
     // valid tokens return at once
-    const int64_t R = a.packed ? (n * T + rows - 1) / rows : n * ((T + rows - 1) / rows);
-    const unsigned grid = (unsigned)((R * cols + 255) / 256 * 256);
+    const int64_t nt = (row_blocks(n, T, rows, a.packed) * cols + 255) / 256 * 256;
+    const dim3 grid((unsigned)(nt < kGridX ? nt : kGridX), (unsigned)((nt + kGridX - 1) / kGridX));
     const bool pieces = a.packed && (n > m ? n : m) > a.span;
     const dim3 rgrid((unsigned)((n + 3) / 4), (unsigned)cnt);
     if (method == DR_SCORE_PIP) {
       hipLaunchKernelGGL(split_kernel, dim3((unsigned)((goff[cnt] + 255) / 256)), dim3(256), 0, hs,
                          (const float*)gstar, (long long)goff[cnt], hi, lo);
-      if (grid > 0)
-        hipLaunchKernelGGL(pieces ? pip_kernel<true> : pip_kernel<false>, dim3(grid), dim3(256), 0, hs, a);
+      if (nt > 0)
+        hipLaunchKernelGGL(pieces ? pip_kernel<true> : pip_kernel<false>, grid, dim3(256), 0, hs, a);
       hipLaunchKernelGGL((score_reduce_kernel<kTileRows, true>), rgrid, dim3(256), 0, hs, a, sl, 1.0);
     } else {
-      if (grid > 0)
-        hipLaunchKernelGGL(pieces ? gip_kernel<true> : gip_kernel<false>, dim3(grid), dim3(kSThreads), 0, hs, a);
+      if (nt > 0)
+        hipLaunchKernelGGL(pieces ? gip_kernel<true> : gip_kernel<false>, grid, dim3(kSThreads), 0, hs, a);
       hipLaunchKernelGGL((score_reduce_kernel<kST, false>), rgrid, dim3(256), 0, hs, a, sl, 1.0 / (double)m);
     }
     if ((st = launch_status()) != DR_OK) return st;

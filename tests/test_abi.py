@@ -235,6 +235,8 @@ def test_score_argument_errors(lib):
         ws = lib.dr_score_workspace_size(arr, 1, 4, 2, 8, E.DR_BF16, meth)
         assert ws > 0
         assert call(method=meth, ws=FAKE, wsb=ws - 1) == E.DR_ERR_WORKSPACE
+    # more tiles than a grid holds: an error, not a truncated grid
+    assert call(method=E.DR_SCORE_GIP, n=1 << 13, m=1 << 13, T=1 << 13, ws=FAKE, wsb=1 << 62) == E.DR_ERR_UNSUPPORTED
 
 
 def test_simplex_and_backprojection_argument_errors(lib):

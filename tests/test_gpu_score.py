@@ -150,6 +150,22 @@ def test_empty_examples_between_the_rows_of_a_tile():
     check_all(layers, n, m, lens, ["gip", "pip"])
 
 
+def test_more_tiles_than_one_grid_dimension_takes():
+    """2^24 tiles of 256 threads (by T, not by the lengths): a launch takes fewer than 2^32 threads per dimension."""
+    n, m, T, count = 512, 32, 1024, 16
+    assert (n * T // 128) * (m * T // 128) * count * 256 >= 1 << 32
+    g = torch.Generator().manual_seed(9)
+    lens = torch.randint(0, 4, (n + m,), generator=g, dtype=torch.int32)
+    lens[n - 1], lens[n + m - 1] = 300, 200
+    lens = lens.to(DEV)
+    layers = make([(8, 16)], n + m, T, lens, seed=9)
+    (ref,) = reference(layers, n, m, lens)
+    s = api.score_exact(layers * count, n, m, lens, method="gip")
+    torch.cuda.synchronize()
+    for l in range(count):
+        assert rel(host64(s[l]), ref) <= TOL_SCORE
+
+
 def test_layer_groups():
     """More layers than one group holds, of different widths."""
     n, m, T = 3, 2, 20
