@@ -159,22 +159,27 @@ __global__ __launch_bounds__(1024) void update_plan_kernel(const float* w, long 
   if (tid == 0) const_cast<int*>(a.cnt)[list] = base_s;
 }
 
+// Sort key of a weight: |w| as bits, which orders every value, NaNs last (a
+// comparison of floats ranks a NaN beside another entry and leaves a hole in
+// the list)
+__device__ __forceinline__ unsigned weight_key(float w) { return __float_as_uint(w) & 0x7fffffffu; }
+
 // entry i of a list goes to position #{j : (|w_j|, ex_j) < (|w_i|, ex_i)}
 __global__ __launch_bounds__(256) void update_sort_kernel(UpdArgs a) {
-  __shared__ float kw[256];
+  __shared__ unsigned kw[256];
   __shared__ int ki[256];
   const int list = blockIdx.y;
   const int cnt = a.cnt[list];
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (blockIdx.x * 256 >= cnt) return;
   const long long base = (long long)list * a.n;
-  const float wi = i < cnt ? fabsf(a.uw[base + i]) : 0.f;
+  const unsigned wi = i < cnt ? weight_key(a.uw[base + i]) : 0u;
   const int xi = i < cnt ? a.uex[base + i] : 0;
   int rank = 0;
   for (int j0 = 0; j0 < cnt; j0 += 256) {
     __syncthreads();
     const int j = j0 + threadIdx.x;
-    kw[threadIdx.x] = j < cnt ? fabsf(a.uw[base + j]) : 0.f;
+    kw[threadIdx.x] = j < cnt ? weight_key(a.uw[base + j]) : 0u;
     ki[threadIdx.x] = j < cnt ? a.uex[base + j] : 0;
     __syncthreads();
     const int m = cnt - j0 < 256 ? cnt - j0 : 256;
@@ -322,7 +327,7 @@ __global__ __launch_bounds__(1024) void update_steps_kernel(UpdArgs a, int modes
 __global__ __launch_bounds__(1024) void update_list_kernel(const float* w, long long ldw, UpdArgs a, const int* len,
                                                            int T, int list0, RowSel rs, int modes) {
   __shared__ int wsum[16];
-  __shared__ float kw[1024];
+  __shared__ unsigned kw[1024];
   __shared__ int ki[1024];
   const int list = list0 + blockIdx.x;
   const float* wr = w + (long long)rs.r[blockIdx.x] * ldw;
@@ -345,12 +350,12 @@ __global__ __launch_bounds__(1024) void update_list_kernel(const float* w, long 
     cnt += wsum[v];
   }
   if (keep) {
-    kw[at] = fabsf(wi);
+    kw[at] = weight_key(wi);
     ki[at] = tid;
   }
   __syncthreads();
   if (keep) {   // to position #{j : (|w_j|, j) < (|w|, i)}
-    const float aw = fabsf(wi);
+    const unsigned aw = weight_key(wi);
     int rank = 0;
     for (int j = 0; j < cnt; ++j) rank += (kw[j] < aw || (kw[j] == aw && ki[j] < tid)) ? 1 : 0;
     const_cast<int*>(a.ex)[base + rank] = tid;

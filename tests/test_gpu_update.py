@@ -293,3 +293,27 @@ def test_equal_weights_rows_further_apart_than_a_step_can_address():
     layers[0]["x"] = wide[:, :, :2048]
     picks = sample(2048, [0, 2047])
     check(layers, equal_weights(n), n, lens, rows=picks, cols=picks)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n", [6, 1100])    # one kernel makes the lists, or three
+def test_nan_weight_reaches_every_element(n, dtype):
+    """A NaN among the weights, in every order of its neighbours: each entry of the list has a place of its own, whatever
+    an earlier call left in the workspace, and U is NaN."""
+    T, d = 5, 64
+    lens = torch.full((n,), T, dtype=torch.int32, device=DEV)
+    layers = make_layers([(d, d)], n, T, dtype, lens, seed=16)
+    ws = torch.empty(api.dr_update_workspace_size(layers, n, T, dtype), dtype=torch.uint8, device=DEV)
+    ws.fill_(0)
+    U = torch.empty(d * d, device=DEV)
+    for at in (0, 1, n - 1):
+        for sign in (1.0, -1.0):
+            w = torch.arange(1, n + 1, device=DEV, dtype=torch.float32).flip(0)
+            w[at] = float("nan") * sign
+            api.dr_assemble_update(layers, n, T, lens, w, U, [0], workspace=ws)
+            torch.cuda.synchronize()
+            assert bool(torch.isnan(U).all())
+            w[at] = 0.0                     # skipped: the others alone
+            api.dr_assemble_update(layers, n, T, lens, w, U, [0], workspace=ws)
+            torch.cuda.synchronize()
+            assert bool(torch.isfinite(U).all())
