@@ -158,8 +158,8 @@ size_t dr_sketch_workspace_size(const dr_layer* layers, int num_layers, int64_t 
  * Arithmetic: fp32 inputs -> fp32 products with fp32 accumulation (n < 128:
  * fp32 MFMA; n >= 128: each value as three bf16 parts, which hold it to
  * 2^-25, and each product as six bf16 MFMA products, exact in fp32; fp32 MFMA
- * from the first value of 2^50 or more on); bf16 inputs -> bf16 MFMA with fp32
- * accumulation.
+ * from the first columns on that hold a value of 2^50 or more, or a nonzero one
+ * below 2^-109); bf16 inputs -> bf16 MFMA with fp32 accumulation.
  * Requirements: ldG, ldGt and every goff[p] multiples of 4 (f32) or 8 (bf16);
  * G and Gt 16-byte aligned.
  * ------------------------------------------------------------------------- */

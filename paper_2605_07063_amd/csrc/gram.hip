@@ -268,10 +268,12 @@ __device__ __forceinline__ void big_store_block_fast(float* Kp, int n, int R, in
 // the products of step t, and the split of step t + 1 (loaded a step ago)
 // followed by the loads of step t + 2.
 //
-// From a step that holds a value of 2^50 or more on (an infinity, or one whose
-// partial products could overflow) the chunk is taken on fp32 MFMA straight
+// From a step that holds a value of 2^50 or more (an infinity, or one whose
+// partial products could overflow) or a nonzero one below 2^-109 (whose third
+// part is below the smallest bf16) on, the chunk is taken on fp32 MFMA straight
 // from memory by the same waves: there inf and overflow come out as in fp32
-// arithmetic.
+// arithmetic, and tiny values count in full (rows of 1e-36 against targets of
+// order one: scores off by 2.5e-5 by their parts, 3e-7 on fp32 MFMA).
 constexpr int kPC = 32;                       // fp32 columns per step
 constexpr int kPThreads = 512;
 constexpr int kPRows = 256, kPCols = 128;     // rows of tile I, rows of an off-diagonal tile's column half
@@ -279,6 +281,7 @@ constexpr int kPDiagBlocks = 17, kPOffBlocks = 24;   // 16-row blocks of a stage
 constexpr int kPStageMax = 3 * kPOffBlocks * 1024;
 constexpr int kPWin = 56;                     // steps whose target mean is in LDS at a time (two windows)
 constexpr float kPBig = 1125899906842624.f;   // 2^50
+constexpr float kPTiny = 0x1p-109f;           // three parts of eight bits end at 2^-133, the smallest bf16
 
 __device__ const float kZeros4[4] = {0.f, 0.f, 0.f, 0.f};   // read in place of columns past a chunk
 
@@ -312,6 +315,21 @@ __device__ __forceinline__ float abs_max8(f32x4 a, f32x4 b, float m) {   // NaNs
   asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(b.x), "v"(b.y));
   asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(b.z), "v"(b.w));
   return m;
+}
+
+__device__ __forceinline__ float abs_min8(f32x4 a, f32x4 b, float m) {
+  asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(a.x), "v"(a.y));
+  asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(a.z), "v"(a.w));
+  asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(b.x), "v"(b.y));
+  asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(b.z), "v"(b.w));
+  return m;
+}
+
+__device__ __forceinline__ bool has_tiny(f32x4 a, f32x4 b) {   // a nonzero value below kPTiny
+  bool t = false;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) t |= (a[e] != 0.f && fabsf(a[e]) < kPTiny) || (b[e] != 0.f && fabsf(b[e]) < kPTiny);
+  return t;
 }
 
 // c[j] += A B_j^T over one step for NJ blocks: the six part pairs, the smallest
@@ -409,12 +427,13 @@ __device__ __forceinline__ void gram_split_tile(const GramArgs& a, unsigned char
   };
   auto stage = [&](int t, const f32x4 (&v)[NI][2]) {
     unsigned char* sb = lds + (t & 1) * kStage;
-    float m = 0.f;
+    float m = 0.f, lo = 1.f;
     auto put8 = [&](int b, f32x4 x, f32x4 y) {
       const Planes8 q = split8(x, y);
 #pragma unroll
       for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x4*>(sb + (k * NB + b) * 1024 + lane * 16) = q.p[k];
       m = abs_max8(x, y, m);
+      lo = abs_min8(x, y, lo);
     };
 #pragma unroll
     for (int u = 0; u < NI; ++u)
@@ -423,7 +442,17 @@ __device__ __forceinline__ void gram_split_tile(const GramArgs& a, unsigned char
       const f32x4* g = reinterpret_cast<const f32x4*>(gm_at(t) + 8 * lg);
       put8(16, g[0], g[1]);
     }
-    if (__any(m >= kPBig) && lane == 0) big[t & 1] = t + 1;
+    bool odd = m >= kPBig;
+    if (__any(lo < kPTiny)) {   // zeros (columns past a chunk, empty rows) or tiny values: look closely
+#pragma unroll
+      for (int u = 0; u < NI; ++u)
+        if (live16[u]) odd |= has_tiny(v[u][0], v[u][1]);
+      if (mean_wave) {
+        const f32x4* g = reinterpret_cast<const f32x4*>(gm_at(t) + 8 * lg);
+        odd |= has_tiny(g[0], g[1]);
+      }
+    }
+    if (__any(odd) && lane == 0) big[t & 1] = t + 1;
   };
   auto frag = [&](const unsigned char* sb, int b, u32x4 (&f)[3]) {
 #pragma unroll

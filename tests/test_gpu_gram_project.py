@@ -700,11 +700,29 @@ def test_gram_fp32_infinities_and_large_values(n, col):
     assert np.allclose(host64(K[n - 1, ok]), big, rtol=1e-5)
 
 
-def test_gram_fp32_tiny_values():
-    """Values whose lower bf16 parts are subnormal."""
-    G = rand((130, 512), 11) * 1e-37
-    Gt = rand((2, 512), 12) * 1e30
-    K, s, t2 = api.gram(G, Gt, [0, 512])
-    torch.cuda.synchronize()
-    ref = G.double() @ Gt.double().mean(0)
-    assert rel(host64(s[0]), host64(ref)) <= TOL_GRAM
+@pytest.mark.parametrize("n", [130, 300])
+@pytest.mark.parametrize("scale", [1e-30, 1e-33, 1e-34, 1e-36, 1e-38])
+def test_gram_fp32_tiny_values(n, scale):
+    """Values whose lower bf16 parts would be subnormal or below: rows of that size against targets of order one, all
+    of them, or one row and one value in a later step beside rows of order one and rows of zeros.  fp32 products of 512
+    terms with fp32 sums: 2e-6 of a row's sum of sizes covers sqrt(512) roundings of 2^-24."""
+    Gt = rand((2, 512), 12)
+    for some in (False, True):
+        G = rand((n, 512), 11)
+        if some:
+            G[7] *= scale
+            G[n - 1, 0:400] *= scale
+            G[n - 1, 400:] = 0.0
+            G[20:30] = 0.0
+        else:
+            G *= scale
+        K, s, t2 = api.gram(G, Gt, [0, 512])
+        torch.cuda.synchronize()
+        g, b = G.double(), Gt.double().mean(0).float().double()
+        ref, size = g @ b, g.abs() @ b.abs()
+        assert bool(((s[0].double() - ref).abs() <= 2e-6 * size + 1e-45).all())
+        if some:
+            ref, size = g @ g.t(), g.abs() @ g.abs().t()
+            # (products below the smallest normal fp32 number are left out)
+            ok = size > 1e-36
+            assert bool(((K[0].double() - ref).abs() <= 2e-6 * size)[ok].all())
