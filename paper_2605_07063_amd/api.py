@@ -475,9 +475,10 @@ def combine(G, w, goff=None, stream=None):
     # the call writes every column of [goff[0], goff[-1]): zeros are only needed before it
     u = (torch.zeros if goff[0] else torch.empty)(goff[-1], dtype=torch.float32, device=w.device)
     _keep(stream, u)
-    ts = _side_stream(stream, u.device) if goff[0] else None
+    ts = _side_stream(stream, u.device)
     if ts is not None:
-        # the zero fill runs on the current stream: order the combine after it
+        # the zero fill runs on the current stream, and so may work on a freed tensor whose memory u was given: order
+        # the combine after both
         ts.wait_stream(torch.cuda.current_stream(u.device))
     dr_combine(G, goff, w, u, stream=stream)
     return u

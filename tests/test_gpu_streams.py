@@ -44,20 +44,29 @@ def test_side_stream_blocked_span_keeps_its_workspace():
     assert rel(host64(w[0]), w_ref) <= TOL_SOLVE
 
 
-def test_side_stream_raw_handle_and_combine_order():
+@pytest.mark.parametrize("first", [0, 64])
+def test_side_stream_raw_handle_and_combine_order(first):
     """A raw stream handle (int) works like a torch stream, and the
-    allocating combine orders its zero fill before the side-stream kernel."""
+    allocating combine is ordered after the current stream: after its zero
+    fill (columns before the first group), and after work still queued there
+    on a freed tensor whose memory it was given.  The current stream is held
+    back, so that a side-stream kernel that does not wait runs first."""
     n, kappa = 64, 4096
     g = torch.Generator(device=DEV)
     g.manual_seed(5)
     G = torch.randn(n, kappa, generator=g, device=DEV)
     w = torch.randn(1, n, generator=g, device=DEV)
+    ref = np.zeros(kappa)
+    ref[first:] = oracle.combine_ref(host64(G[:, first:]), host64(w[0]))
     side = torch.cuda.Stream()
-    side.wait_stream(torch.cuda.current_stream())
-    with torch.cuda.stream(side):
-        torch.cuda._sleep(20_000_000)
-    u = api.combine(G, w, stream=side.cuda_stream)
     torch.cuda.synchronize()
-    ref = oracle.combine_ref(host64(G), host64(w[0]))
+    freed = torch.empty(kappa, device=DEV)
+    at = freed.data_ptr()
+    torch.cuda._sleep(50_000_000)
+    freed.fill_(1e30)
+    del freed
+    u = api.combine(G, w, [first, kappa], stream=side.cuda_stream)
+    assert u.data_ptr() == at                  # (else the test holds nothing back)
+    torch.cuda.synchronize()
     assert rel(host64(u), ref) <= TOL_SOLVE
-    assert np.isfinite(host64(u)).all()
+    assert np.isfinite(host64(u)).all() and bool((u[:first] == 0).all())
