@@ -413,8 +413,9 @@ size_t dr_update_workspace_size(const dr_layer* layers, int num_layers, int64_t 
  *   workspace at least dr_score_workspace_size() bytes.
  * Arithmetic: bf16 MFMA with fp32 accumulation, partial sums in fp64; PIP
  * multiplies by gbar* as a bf16 hi + lo pair.  Layers are processed in
- * groups of up to 16 whose gbar* hold at most 32 Mi elements together (or of
- * one layer); the workspace holds one group's gbar*.
+ * groups of up to 16 whose gbar* (DIRECT, PIP) or partial sums (GIP) hold at
+ * most 32 Mi elements together (or of one layer); the workspace holds one
+ * group's gbar* and partial sums.
  * Requirements as for dr_assemble_update; one layer's gbar* rows and one
  * example's rows must span less than 4 GiB, and a group's tiles (at T tokens
  * an example) number at most 65535 * 2^22 (else DR_ERR_UNSUPPORTED).

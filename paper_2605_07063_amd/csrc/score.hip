@@ -550,17 +550,44 @@ struct ScorePlan {
   size_t off_wm, off_g, off_upd, off_hi, off_lo, off_cum, off_part, off_direct, bytes;
 };
 
+// 128-token column blocks of the m targets (upper bound)
+int64_t gip_cols(int64_t m, int64_t T, bool packed) {
+  return packed ? (m * T + kST - 1) / kST : m * ((T + kST - 1) / kST);
+}
+
+// row blocks over n examples (the most that the lengths allow)
+int64_t row_blocks(int64_t n, int64_t T, int64_t rows, bool packed) {
+  return packed ? (n * T + rows - 1) / rows : n * ((T + rows - 1) / rows);
+}
+
+// (row block, example) slots
+int64_t score_slots(int64_t n, int64_t T, int64_t rows, bool packed) {
+  return row_blocks(n, T, rows, packed) + (packed ? n : 0);
+}
+
 // Layers are taken in groups of at most kMaxScoreLayers consecutive ones: a
 // group's gbar* are assembled in one call and its tiles share one launch, so
 // that the last round of tiles is a small part of it (eight 2048 x 2048
 // layers one at a time: 2.4 rounds of the chip each).  A group's gbar* hold
-// at most kGroupElems elements (256 MiB of workspace for PIP), or one layer.
-constexpr int64_t kGroupElems = (int64_t)32 << 20;
+// at most kGroupElems elements (256 MiB of workspace for PIP), its GIP
+// partials, which go with the tokens of both sides, kGroupPartials (256 MiB
+// again); or it is one layer.
+constexpr int64_t kGroupElems = (int64_t)32 << 20, kGroupPartials = (int64_t)32 << 20;
 
-int group_end(const dr_layer* layers, int num_layers, int first, int method) {
+int group_end(const dr_layer* layers, int num_layers, int first, int64_t n, int64_t m, int64_t T, int method) {
   int64_t g = 0;
+  int most = kMaxScoreLayers;
+  if (method == DR_SCORE_GIP) {
+    double part = 1.0;   // of a layer
+    for (int packed = 0; packed < 2; ++packed) {
+      const double p = (double)score_slots(n, T, kST, packed) * (double)gip_cols(m, T, packed);
+      part = p > part ? p : part;
+    }
+    const double fit = (double)kGroupPartials / part;
+    most = fit >= most ? most : (fit < 1.0 ? 1 : (int)fit);
+  }
   int l = first;
-  for (; l < num_layers && l - first < kMaxScoreLayers; ++l) {
+  for (; l < num_layers && l - first < most; ++l) {
     g += layers[l].d_out * layers[l].d_in;
     if (method != DR_SCORE_GIP && l > first && g > kGroupElems) break;
   }
@@ -588,21 +615,6 @@ bool score_packed(const dr_layer* layers, int num_layers, int64_t n, int64_t m, 
   return score_span(layers, num_layers, T) >= (most < rows ? most : rows);
 }
 
-// 128-token column blocks of the m targets (upper bound)
-int64_t gip_cols(int64_t m, int64_t T, bool packed) {
-  return packed ? (m * T + kST - 1) / kST : m * ((T + kST - 1) / kST);
-}
-
-// row blocks over n examples (the most that the lengths allow)
-int64_t row_blocks(int64_t n, int64_t T, int64_t rows, bool packed) {
-  return packed ? (n * T + rows - 1) / rows : n * ((T + rows - 1) / rows);
-}
-
-// (row block, example) slots
-int64_t score_slots(int64_t n, int64_t T, int64_t rows, bool packed) {
-  return row_blocks(n, T, rows, packed) + (packed ? n : 0);
-}
-
 dr_layer target_layer(const dr_layer& L, int64_t n, int64_t T) {
   dr_layer t = L;
   t.x = static_cast<const unsigned char*>(L.x) + n * T * L.ldx * 2;
@@ -617,7 +629,7 @@ ScorePlan score_plan(const dr_layer* layers, int num_layers, int64_t n, int64_t 
   const int64_t rows = method == DR_SCORE_PIP ? kTileRows : kST;
   dr_layer t[kMaxScoreLayers];
   for (int l0 = 0; l0 < num_layers;) {
-    const int l1 = group_end(layers, num_layers, l0, method);
+    const int l1 = group_end(layers, num_layers, l0, n, m, T, method);
     const bool packed = score_packed(layers + l0, l1 - l0, n, m, T, rows);
     const int64_t slots = score_slots(n, T, rows, packed);
     int64_t g = 0, cols = 0;
@@ -715,7 +727,7 @@ extern "C" dr_status dr_score_exact(const dr_layer* layers, int num_layers, int6
     if ((st = launch_status()) != DR_OK) return st;
   }
   for (int l0 = 0; l0 < num_layers;) {
-    const int l1 = group_end(layers, num_layers, l0, (int)method), cnt = l1 - l0;
+    const int l1 = group_end(layers, num_layers, l0, n, m, T, (int)method), cnt = l1 - l0;
     float* sl = s + (int64_t)l0 * n;
     int64_t goff[kMaxScoreLayers + 1] = {0};
     for (int j = 0; j < cnt; ++j) goff[j + 1] = goff[j] + layers[l0 + j].d_out * layers[l0 + j].d_in;

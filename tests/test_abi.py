@@ -235,6 +235,11 @@ def test_score_argument_errors(lib):
         ws = lib.dr_score_workspace_size(arr, 1, 4, 2, 8, E.DR_BF16, meth)
         assert ws > 0
         assert call(method=meth, ws=FAKE, wsb=ws - 1) == E.DR_ERR_WORKSPACE
+    # the partial sums of a group of GIP layers stay within 256 MiB, or are one layer's
+    many = (_lib.DrLayer * 16)(*[layer(ldx=256, lddy=256) for _ in range(16)])
+    size = lambda count, n, m, T: lib.dr_score_workspace_size(many, count, n, m, T, E.DR_BF16, E.DR_SCORE_GIP)
+    assert size(1, 1024, 64, 4096) > 256 << 20 and size(16, 1024, 64, 4096) == size(1, 1024, 64, 4096)
+    assert size(1, 256, 32, 2048) < size(16, 256, 32, 2048) < 257 << 20
     # more tiles than a grid holds: an error, not a truncated grid
     assert call(method=E.DR_SCORE_GIP, n=1 << 13, m=1 << 13, T=1 << 13, ws=FAKE, wsb=1 << 62) == E.DR_ERR_UNSUPPORTED
 
