@@ -813,17 +813,19 @@ __global__ __launch_bounds__(kSmThreads) void gram_small_kernel(GramArgs a, cons
 
 // K (both triangles), s and t2 from the chunk partials: a workgroup takes 64
 // neighbouring elements of a 16 x 16 block (four rows), lane by lane; a wave
-// sums 16 chunks at a time (a tree, every load in flight), the waves' sums meet
-// in LDS, again as a tree.  A wave's load is 256 contiguous bytes; with a wave
-// per element, lanes over the chunks, each load touched 64 lines for 4 bytes
-// of each, and most lanes were idle where a group has few chunks.  The whole
-// Gram, us: one group of 64 x 32768 17.1 -> 16.0, 8 of 64 x 4096 33 -> 15, one
-// of 127 x 131072 90 -> 64, 200 of 100 x 128 1530 -> 29.
+// sums 16 chunks at a time (a tree in fp64, every load in flight), the waves'
+// sums meet in LDS, again as a tree.  A wave's load is 256 contiguous bytes;
+// with a wave per element, lanes over the chunks, each load touched 64 lines
+// for 4 bytes of each, and most lanes were idle where a group has few chunks.
+// The whole Gram, us: one group of 64 x 32768 16.7 -> 12.3, 8 of 64 x 4096 33
+// -> 12, one of 127 x 131072 89 -> 52, 200 of 100 x 128 1540 -> 30.  In fp64
+// what is left is the error of the chunks' own sums: 64 x 32768 3.1e-8 against
+// 64 bits, 4.6e-8 with an fp32 tree, 5.3e-8 with fp32 sums along lanes.
 constexpr int kSrChunks = 16;   // chunks per wave at a time
 constexpr int kSrWaves = 16;
 __global__ __launch_bounds__(kSrWaves * 64) void gram_small_reduce_kernel(GramArgs a, int NRP, int nchunks, float* K,
                                                                           float* s, float* t2, long long pbase) {
-  __shared__ float part[kSrWaves][64];
+  __shared__ double part[kSrWaves][64];
   const int p = blockIdx.y, q = blockIdx.x >> 2;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   int I = 0;
@@ -834,7 +836,7 @@ __global__ __launch_bounds__(kSrWaves * 64) void gram_small_reduce_kernel(GramAr
   const long long width = a.goff[p + 1] - a.goff[p];
   const int nvalid = (int)((width + kSmCK - 1) / kSmCK);
   const float* src = a.partial + (long long)p * nchunks * NRP * NRP + q * 256 + e;
-  auto tree = [](float (&v)[16]) {
+  auto tree = [](double (&v)[16]) {
 #pragma unroll
     for (int h = 8; h > 0; h >>= 1)
 #pragma unroll
@@ -842,23 +844,23 @@ __global__ __launch_bounds__(kSrWaves * 64) void gram_small_reduce_kernel(GramAr
         if (u < h) v[u] += v[u + h];
     return v[0];
   };
-  float acc = 0.f;
+  double sum = 0.0;
   for (int ch0 = kSrChunks * wave; ch0 < nvalid; ch0 += kSrChunks * nw) {
-    float v[kSrChunks];
+    float t[kSrChunks];
 #pragma unroll
-    for (int u = 0; u < kSrChunks; ++u) {
-      const float t = src[(long long)(ch0 + u < nvalid ? ch0 + u : nvalid - 1) * NRP * NRP];
-      v[u] = ch0 + u < nvalid ? t : 0.f;
-    }
-    acc += tree(v);
+    for (int u = 0; u < kSrChunks; ++u) t[u] = src[(long long)(ch0 + u < nvalid ? ch0 + u : nvalid - 1) * NRP * NRP];
+    double v[kSrChunks];
+#pragma unroll
+    for (int u = 0; u < kSrChunks; ++u) v[u] = ch0 + u < nvalid ? (double)t[u] : 0.0;
+    sum += tree(v);
   }
-  part[wave][lane] = acc;
+  part[wave][lane] = sum;
   __syncthreads();
   if (wave > 0) return;
-  float v[kSrWaves];
+  double v[kSrWaves];
 #pragma unroll
-  for (int u = 0; u < kSrWaves; ++u) v[u] = u < nw ? part[u < nw ? u : 0][lane] : 0.f;
-  acc = tree(v);
+  for (int u = 0; u < kSrWaves; ++u) v[u] = u < nw ? part[u < nw ? u : 0][lane] : 0.0;
+  const float acc = (float)tree(v);
   if (r > a.n || c > r) return;
   if (r < a.n) {
     float* Kp = K + (pbase + p) * (long long)a.n * a.n;

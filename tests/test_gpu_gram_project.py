@@ -413,7 +413,7 @@ def test_span_batched_groups_and_hand_fixture(golden_dir):
 ])
 def test_gram_small_chunk_sums(n, goff):
     """The reduction of the chunk partials at the edges of its waves and passes.  An element is a sum of fp32 products
-    per 128 columns and a tree of at most 16 + 16 partials: 128 + 8 + passes roundings of |row| . |row|."""
+    per 128 columns, the chunks' sums added in fp64: at most 128 roundings of |row| . |row| and one of the result."""
     G, Gt = rand((n, goff[-1]), 900 + n), rand((3, goff[-1]), 901 + n)
     K, s, t2 = api.gram(G, Gt, goff)
     torch.cuda.synchronize()
