@@ -821,17 +821,24 @@ __global__ __launch_bounds__(kSmThreads) void gram_small_kernel(GramArgs a, cons
 // -> 12, one of 127 x 131072 89 -> 52, 200 of 100 x 128 1540 -> 30.  In fp64
 // what is left is the error of the chunks' own sums: 64 x 32768 3.1e-8 against
 // 64 bits, 4.6e-8 with an fp32 tree, 5.3e-8 with fp32 sums along lanes.
-constexpr int kSrChunks = 16;   // chunks per wave at a time
+// EL = 16 elements per workgroup, each lane group of 16 on chunks of its own,
+// where a launch would have at most 24 blocks and there are 64 chunks or more:
+// one group of 16 x 65536 11.6 -> 9.8 us (a wave per element took 10.6), of 32
+// x 229376 38 -> 31.  Four groups of 16 x 16384, 48 blocks: 9.2 as it is, 9.6
+// with 16 elements.
+constexpr int kSrChunks = 16;   // chunks per lane at a time
 constexpr int kSrWaves = 16;
+template <int EL>
 __global__ __launch_bounds__(kSrWaves * 64) void gram_small_reduce_kernel(GramArgs a, int NRP, int nchunks, float* K,
                                                                           float* s, float* t2, long long pbase) {
+  constexpr int S = 64 / EL;   // chunk slots of a wave
   __shared__ double part[kSrWaves][64];
-  const int p = blockIdx.y, q = blockIdx.x >> 2;
+  const int p = blockIdx.y, q = blockIdx.x / (256 / EL);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   int I = 0;
   while ((I + 1) * (I + 2) / 2 <= q) ++I;
   const int J = q - I * (I + 1) / 2;
-  const int e = (blockIdx.x & 3) * 64 + lane;   // element of the block
+  const int e = blockIdx.x % (256 / EL) * EL + lane % EL;   // element of the block
   const int r = 16 * I + (e >> 4), c = 16 * J + (e & 15);
   const long long width = a.goff[p + 1] - a.goff[p];
   const int nvalid = (int)((width + kSmCK - 1) / kSmCK);
@@ -845,7 +852,7 @@ __global__ __launch_bounds__(kSrWaves * 64) void gram_small_reduce_kernel(GramAr
     return v[0];
   };
   double sum = 0.0;
-  for (int ch0 = kSrChunks * wave; ch0 < nvalid; ch0 += kSrChunks * nw) {
+  for (int ch0 = kSrChunks * (S * wave + lane / EL); ch0 < nvalid; ch0 += kSrChunks * S * nw) {
     float t[kSrChunks];
 #pragma unroll
     for (int u = 0; u < kSrChunks; ++u) t[u] = src[(long long)(ch0 + u < nvalid ? ch0 + u : nvalid - 1) * NRP * NRP];
@@ -860,7 +867,11 @@ __global__ __launch_bounds__(kSrWaves * 64) void gram_small_reduce_kernel(GramAr
   double v[kSrWaves];
 #pragma unroll
   for (int u = 0; u < kSrWaves; ++u) v[u] = u < nw ? part[u < nw ? u : 0][lane] : 0.0;
-  const float acc = (float)tree(v);
+  sum = tree(v);
+#pragma unroll
+  for (int o = EL; o < 64; o *= 2) sum += __shfl_xor(sum, o, 64);
+  if (lane >= EL) return;
+  const float acc = (float)sum;
   if (r > a.n || c > r) return;
   if (r < a.n) {
     float* Kp = K + (pbase + p) * (long long)a.n * a.n;
@@ -1340,8 +1351,11 @@ dr_status gram_run(const GramPlan& g, const void* G, int64_t n, int64_t ldG, con
                          static_cast<const float*>(Gt), (long long)ldGt, (int)m, g.NRP, g.maxchunks);
       if ((st = launch_status()) != DR_OK) return st;
       const int nb = g.NRP / 16;
-      const int nw = (g.maxchunks + kSrChunks - 1) / kSrChunks;   // 16 chunks per wave, up to 16 waves
-      hipLaunchKernelGGL(gram_small_reduce_kernel, dim3(nb * (nb + 1) * 2, gp),
+      const bool wide = nb * (nb + 1) * 2 * gp <= 24 && g.maxchunks >= 64;   // (few blocks, many chunks)
+      const int el = wide ? 16 : 64, per = kSrChunks * 64 / el;
+      const int nw = (g.maxchunks + per - 1) / per;   // 16 chunks per lane, up to 16 waves
+      hipLaunchKernelGGL(wide ? gram_small_reduce_kernel<16> : gram_small_reduce_kernel<64>,
+                         dim3(nb * (nb + 1) / 2 * (256 / el), gp),
                          dim3(64 * (nw < 1 ? 1 : nw > kSrWaves ? kSrWaves : nw)), 0, hs, a, g.NRP, g.maxchunks, K, s,
                          t2, (long long)p0);
       if ((st = launch_status()) != DR_OK) return st;

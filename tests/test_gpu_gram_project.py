@@ -410,6 +410,8 @@ def test_span_batched_groups_and_hand_fixture(golden_dir):
     (63, [0, 2048, 4224]),             # 16 and 17 chunks: one wave full, a second begun
     (127, [0, 40000]),                 # the largest n
     (31, [0, 4]),
+    (16, [0, 140004]),                 # few blocks, many chunks: 1024 chunks at a time, and a second pass
+    (40, [0, 8068]),                   # 64 chunks, the fewest that are split over a wave
 ])
 def test_gram_small_chunk_sums(n, goff):
     """The reduction of the chunk partials at the edges of its waves and passes.  An element is a sum of fp32 products
