@@ -1010,51 +1010,65 @@ bool gram_use_big(int64_t n, int P, dr_dtype dtype) {
   return T * (T + 1) / 2 * gp >= kBigMinTiles;
 }
 
-// One 16 x 16 block of a 64 x 64 tile per workgroup: sums the chunk partials in
-// fp64 (each of NP threads per element a run of the chunks, then the runs in
-// order) and writes K (lower triangle and its mirror, the latter through LDS
-// so that it too goes out along rows) and, for fp32 rows, s and t2 from the
-// upper triangle of the diagonal tiles (where gram_split_kernel puts them).
-// Four threads per element when there are many chunks to read (256 of them
-// for 256 x 229376, 42 MB: 14 us with one).
-template <int NP>
+// ROWS x 256 / ROWS elements of a 64 x 64 tile per workgroup: sums the chunk
+// partials in fp64 (each of NP threads per element a run of the chunks, then
+// the runs in order) and writes K (lower triangle and its mirror, the latter
+// through LDS so that it too goes out in pieces of rows) and, for fp32 rows, s
+// and t2 from the upper triangle of the diagonal tiles (where the fp32 tile
+// kernels put them).
+template <int ROWS, int NP>
 __global__ __launch_bounds__(256 * NP) void gram_reduce_kernel(GramArgs a, float* K, float* s, float* t2,
                                                                long long pbase) {
-  __shared__ double red[NP][256];
-  __shared__ float tile[16][17];
-  const int q = blockIdx.x, p = blockIdx.y, bi = blockIdx.z >> 2, bj = blockIdx.z & 3;
+  constexpr int COLS = 256 / ROWS, CB = kTile / COLS;
+  __shared__ double red[NP][NP > 1 ? 256 : 1];
+  __shared__ float tile[ROWS][COLS + 1];
+  const int q = blockIdx.x, p = blockIdx.y;
   const int e = threadIdx.x & 255, part = threadIdx.x >> 8;
-  const long long width = a.goff[p + 1] - a.goff[p];
-  const int nvalid = (int)((width + a.CK - 1) / a.CK);
+  const long long width = a.goff[p + 1] - a.goff[p], up = width + a.CK - 1;
+  // (a 64-bit division is as long as the sum of a few chunks)
+  const int nvalid = a.maxchunks == 1 ? width > 0 : (int)(up >> 32 ? up / a.CK : (unsigned)up / (unsigned)a.CK);
   int I, J;
   pair_to_tiles(q, I, J);
-  const bool diag = I == J, upper = diag && bj > bi;
-  // upper blocks of a diagonal tile hold the scores (two rows of them) and t2
-  if (upper && !(a.rows > a.n && (bi == 0 || (bi == 1 && bj >= 2)))) return;
-  const int tr = 16 * bi + (e >> 4), tc = 16 * bj + (e & 15);
+  const int r0 = ROWS * ((int)blockIdx.z / CB), c0 = COLS * ((int)blockIdx.z % CB);
+  if (I * kTile + r0 >= a.n) return;   // no rows (nor, below them, scores)
+  if (I == J && c0 >= r0 + ROWS && !(a.rows > a.n && r0 % 16 == 0 && r0 <= 16)) return;   // above the diagonal
+  const int tr = r0 + e / COLS, tc = c0 + e % COLS;
   const int r = I * kTile + tr, c = J * kTile + tc;
-  const bool need = upper ? (e >> 4) == 0 : r < a.n;
+  const bool lower = c <= r && r < a.n;
+  // upper triangle of a diagonal tile: the scores (two rows of them) and t2
+  int srow = -1;
+  if (a.rows > a.n && I == J && c > r) {
+    if ((tr == 0 || tr == 16) && tc >= 32) srow = I * kTile + 2 * tr + (tc - 32);
+    if (srow >= a.n) srow = -1;
+  }
+  const bool t2_here = a.rows > a.n && q == 0 && tr == 0 && tc == 16;
+  const bool need = lower || srow >= 0 || t2_here;
   double sum = 0.0;
   if (need) {
-    const float* src =
-        a.partial + ((long long)p * a.pairs + q) * a.maxchunks * (kTile * kTile) + tr * kTile + tc;
     int ch = (int)((long long)nvalid * part / NP);
     const int ce = (int)((long long)nvalid * (part + 1) / NP);
-    for (; ch + 16 <= ce; ch += 16) {
-      float v[16];
+    const float* src =
+        a.partial + (((long long)p * a.pairs + q) * a.maxchunks + ch) * (kTile * kTile) + tr * kTile + tc;
+    // every load of a batch in flight before the first addition; the last
+    // batch is the smallest that holds what is left
+    auto batch = [&](auto count, auto full) {
+      constexpr int N = decltype(count)::value;
+      constexpr bool FULL = decltype(full)::value;
+      float v[N];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = src[(long long)(ch + u) * (kTile * kTile)];
+      for (int u = 0; u < N; ++u) v[u] = src[(FULL || ch + u < ce ? u : 0) * (kTile * kTile)];
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < 16; ++u) sum += (double)v[u];
-    }
-    for (; ch + 4 <= ce; ch += 4) {
-      float v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = src[(long long)(ch + u) * (kTile * kTile)];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) sum += (double)v[u];
-    }
-    for (; ch < ce; ++ch) sum += (double)src[(long long)ch * (kTile * kTile)];
+      for (int u = 0; u < N; ++u) sum += FULL || ch + u < ce ? (double)v[u] : 0.0;
+      ch += N;
+      src += N * (kTile * kTile);
+    };
+    while (ch + 32 <= ce) batch(std::integral_constant<int, 32>{}, std::true_type{});
+    if (ch + 16 < ce) batch(std::integral_constant<int, 32>{}, std::false_type{});
+    else if (ch + 8 < ce) batch(std::integral_constant<int, 16>{}, std::false_type{});
+    else if (ch + 4 < ce) batch(std::integral_constant<int, 8>{}, std::false_type{});
+    else if (ch + 1 < ce) batch(std::integral_constant<int, 4>{}, std::false_type{});
+    else if (ch < ce) batch(std::integral_constant<int, 1>{}, std::true_type{});
   }
   if (NP > 1) {
     red[part][e] = sum;
@@ -1065,26 +1079,17 @@ __global__ __launch_bounds__(256 * NP) void gram_reduce_kernel(GramArgs a, float
     }
   }
   const float acc = (float)sum;
-  if (upper) {
-    if (part == 0 && need) {
-      const int srow = I * kTile + 2 * tr + (tc - 32);
-      if (bj >= 2) {
-        if (srow < a.n) s[(pbase + p) * (long long)a.n + srow] = acc;
-      } else if (I == 0 && tc == 16) {
-        t2[pbase + p] = acc;
-      }
-    }
-    return;
-  }
   float* Kp = K + (pbase + p) * (long long)a.n * a.n;
   if (part == 0) {
-    tile[e >> 4][e & 15] = acc;
-    if (need && c <= r) Kp[(long long)r * a.n + c] = acc;
+    tile[e / COLS][e % COLS] = acc;
+    if (lower) Kp[(long long)r * a.n + c] = acc;
+    if (srow >= 0) s[(pbase + p) * (long long)a.n + srow] = acc;
+    if (t2_here) t2[pbase + p] = acc;
   }
   __syncthreads();
-  if (part == 0) {   // element (e & 15, e >> 4) of the block, mirrored
-    const int mr = I * kTile + 16 * bi + (e & 15), mc = J * kTile + 16 * bj + (e >> 4);
-    if (mr < a.n && mc <= mr) Kp[(long long)mc * a.n + mr] = tile[e & 15][e >> 4];
+  if (part == 0) {   // mirrored
+    const int mr = I * kTile + r0 + e % ROWS, mc = J * kTile + c0 + e / ROWS;
+    if (mr < a.n && mc <= mr) Kp[(long long)mc * a.n + mr] = tile[e % ROWS][e / ROWS];
   }
 }
 
@@ -1369,12 +1374,20 @@ dr_status gram_run(const GramPlan& g, const void* G, int64_t n, int64_t ldG, con
       if ((st = launch_status()) != DR_OK) return st;
       if (bf || g.maxchunks > 1) {   // fp32 tiles of a single chunk are written by the tile kernel
         const dim3 rg(g.pairs, gp, kTile * kTile / 256);
-        // four threads per element where the blocks alone would not fill the chip (256 rows: 160 blocks; 512
-        // bf16 rows have 576: 45.1 us a Gram with one thread, 46.2 with four)
-        if (g.maxchunks >= 32 && g.pairs * gp * (kTile * kTile / 256) < 512)
-          hipLaunchKernelGGL(gram_reduce_kernel<4>, rg, dim3(1024), 0, hs, a, K, s, t2, (long long)p0);
+        // Rows of 64 where the workgroups are few: a wave's load is then one
+        // piece of 256 bytes (one bf16 group of 512 x 4096: 29.5 us, with 16 x
+        // 16 blocks 34.0), in four parts where the chunks are many (256 fp32
+        // rows x 229376 columns, 256 chunks: 14 us with one).  Where there are
+        // many, and few chunks, the writes weigh more: 16 x 16 blocks, whose
+        // mirror goes out in pieces of 64 bytes, not 16 (64 groups of 512 x 64:
+        // 86 us, 98 in rows).  Up to 16 rows are one such block.
+        const int64_t blocks = (int64_t)g.pairs * gp * (kTile * kTile / 256);
+        if (g.maxchunks >= 32 && blocks < 512)
+          hipLaunchKernelGGL((gram_reduce_kernel<4, 4>), rg, dim3(1024), 0, hs, a, K, s, t2, (long long)p0);
+        else if (blocks < 2048 && n > 16)
+          hipLaunchKernelGGL((gram_reduce_kernel<4, 1>), rg, dim3(256), 0, hs, a, K, s, t2, (long long)p0);
         else
-          hipLaunchKernelGGL(gram_reduce_kernel<1>, rg, dim3(256), 0, hs, a, K, s, t2, (long long)p0);
+          hipLaunchKernelGGL((gram_reduce_kernel<16, 1>), rg, dim3(256), 0, hs, a, K, s, t2, (long long)p0);
         if ((st = launch_status()) != DR_OK) return st;
       }
     }
