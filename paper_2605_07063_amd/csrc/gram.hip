@@ -1023,7 +1023,7 @@ __global__ __launch_bounds__(256 * NP) void gram_reduce_kernel(GramArgs a, float
   __shared__ double red[NP][NP > 1 ? 256 : 1];
   __shared__ float tile[ROWS][COLS + 1];
   const int q = blockIdx.x, p = blockIdx.y;
-  const int e = threadIdx.x & 255, part = threadIdx.x >> 8;
+  const int e = threadIdx.x & 255, part = NP == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
   const long long width = a.goff[p + 1] - a.goff[p], up = width + a.CK - 1;
   // (a 64-bit division is as long as the sum of a few chunks)
   const int nvalid = a.maxchunks == 1 ? width > 0 : (int)(up >> 32 ? up / a.CK : (unsigned)up / (unsigned)a.CK);
@@ -1047,8 +1047,8 @@ __global__ __launch_bounds__(256 * NP) void gram_reduce_kernel(GramArgs a, float
   if (need) {
     int ch = (int)((long long)nvalid * part / NP);
     const int ce = (int)((long long)nvalid * (part + 1) / NP);
-    const float* src =
-        a.partial + (((long long)p * a.pairs + q) * a.maxchunks + ch) * (kTile * kTile) + tr * kTile + tc;
+    const float* src = a.partial + (((long long)p * a.pairs + q) * a.maxchunks + ch) * (kTile * kTile);
+    const unsigned at = tr * kTile + tc;   // (the chunk's address is scalar)
     // every load of a batch in flight before the first addition; the last
     // batch is the smallest that holds what is left
     auto batch = [&](auto count, auto full) {
@@ -1056,19 +1056,25 @@ __global__ __launch_bounds__(256 * NP) void gram_reduce_kernel(GramArgs a, float
       constexpr bool FULL = decltype(full)::value;
       float v[N];
 #pragma unroll
-      for (int u = 0; u < N; ++u) v[u] = src[(FULL || ch + u < ce ? u : 0) * (kTile * kTile)];
+      for (int u = 0; u < N; ++u) v[u] = (src + (FULL || ch + u < ce ? u : 0) * (kTile * kTile))[at];
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < N; ++u) sum += FULL || ch + u < ce ? (double)v[u] : 0.0;
       ch += N;
       src += N * (kTile * kTile);
     };
-    while (ch + 32 <= ce) batch(std::integral_constant<int, 32>{}, std::true_type{});
-    if (ch + 16 < ce) batch(std::integral_constant<int, 32>{}, std::false_type{});
-    else if (ch + 8 < ce) batch(std::integral_constant<int, 16>{}, std::false_type{});
-    else if (ch + 4 < ce) batch(std::integral_constant<int, 8>{}, std::false_type{});
-    else if (ch + 1 < ce) batch(std::integral_constant<int, 4>{}, std::false_type{});
-    else if (ch < ce) batch(std::integral_constant<int, 1>{}, std::true_type{});
+    if constexpr (ROWS == 16) {   // few chunks: little code
+      while (ch + 16 <= ce) batch(std::integral_constant<int, 16>{}, std::true_type{});
+      while (ch + 4 <= ce) batch(std::integral_constant<int, 4>{}, std::true_type{});
+      while (ch < ce) batch(std::integral_constant<int, 1>{}, std::true_type{});
+    } else {
+      while (ch + 32 <= ce) batch(std::integral_constant<int, 32>{}, std::true_type{});
+      if (ch + 16 < ce) batch(std::integral_constant<int, 32>{}, std::false_type{});
+      else if (ch + 8 < ce) batch(std::integral_constant<int, 16>{}, std::false_type{});
+      else if (ch + 4 < ce) batch(std::integral_constant<int, 8>{}, std::false_type{});
+      else if (ch + 1 < ce) batch(std::integral_constant<int, 4>{}, std::false_type{});
+      else if (ch < ce) batch(std::integral_constant<int, 1>{}, std::true_type{});
+    }
   }
   if (NP > 1) {
     red[part][e] = sum;
