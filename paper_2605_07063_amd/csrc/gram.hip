@@ -11,7 +11,11 @@
 //                        the group's columns (lower-triangle tile pairs only),
 //                        bf16 16x16x32 MFMA, fp32 accumulate; operands stream
 //                        from memory straight into registers.
-//   gram_split_kernel  : fp32 rows: 256-row tiles of K_p over one chunk of the
+//   gram_tile_lds_kernel : fp32 rows, the same tiles and chunks on fp32 MFMA,
+//                        operands staged through LDS; the target mean joins
+//                        the diagonal tiles as a further row, so s_p and t2_p
+//                        come out of the same pass.
+//   gram_split_kernel  : fp32 rows, larger problems: 256-row tiles of K_p over one chunk of the
 //                        group's columns, each value split into three bf16
 //                        parts and each product taken as six bf16 MFMAs.  A
 //                        diagonal tile also forms the target mean of its
@@ -51,6 +55,7 @@
 //                        t2 (element n, n).
 // No atomics: results are deterministic.
 
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 
@@ -63,6 +68,7 @@ constexpr int kThreads = 256;
 constexpr int kTile = 64;
 constexpr int kMaxGroups = 256;   // groups per launch (more groups -> more launches)
 constexpr int kTargetWGs = 1024;
+constexpr int kLdsSlots = 256 * 3;   // gram_tile_lds_kernel workgroups resident at once: 256 CUs x 3 (48 KB of LDS each)
 constexpr int kSplitSlots = 256;     // gram_split_kernel workgroups resident at once (one per CU)
 constexpr int64_t kSplitPartials = (int64_t)44 << 20;   // bytes of its chunk partials
 
@@ -76,8 +82,8 @@ struct GramArgs {
   int P;
   int NT, pairs, CK, maxchunks;
   float* partial;                   // [P][pairs][maxchunks][kTile*kTile]
-  float* K;                         // outputs (gram_split_kernel writes them itself when
-  float* s;                         // maxchunks == 1); group p of the launch is pbase + p
+  float* K;                         // outputs (the fp32 tile kernels write them themselves
+  float* s;                         // when maxchunks == 1); group p of the launch is pbase + p
   float* t2;
   long long pbase;
   int vec4;                         // rows of K start 16-byte aligned
@@ -234,6 +240,247 @@ __device__ __forceinline__ void big_store_block_fast(float* Kp, int n, int R, in
     if (c & 2) { x0 = r02; x1 = r13; } else { x2 = r02; x3 = r13; }
   }
   __builtin_nontemporal_store(f32x4{x0, x1, x2, x3}, reinterpret_cast<f32x4*>(Kp + (long long)(R + 4 * lg + c) * n + C + 4 * m));
+}
+
+// fp32 rows, n + 1 > 128, where the 256-row tiles below would leave the chip
+// idle or spend themselves on a short last tile (lds_tiles_time): 64 x 64
+// tile pairs over the n general rows, with the operands staged through LDS.  Per step of 32 columns the workgroup's
+// rows are loaded once into registers (16-byte segments), written to a
+// three-stage LDS ring in the conflict-free operand layout, and read by the
+// four waves as fp32 MFMA fragments; loads run two steps ahead of their LDS
+// writes, and the LDS writes one step ahead of the products.  A step's
+// products are summed from zero and then added (one chain of MFMAs over a
+// chunk had errors of 1.9e-7 to 5.1e-7 against 64 bits).
+//   off-diagonal pair (I > J): tile I's 64 rows, then tile J's 64 rows;
+//   diagonal pair (I = J): tile I's 64 rows once (they are both operands),
+//     then the target mean as a 16-row block whose other rows are zero.
+//     Waves (0, 0), (1, 0) and (1, 1) take the tile's lower triangle; wave
+//     (0, 1), whose quadrant lies above the diagonal, takes the target mean
+//     against the 64 rows (the scores s), and in tile 0 wave (0, 0) also
+//     takes the target mean against itself (t2).  Both land in the partial
+//     tile's upper triangle, which holds nothing else: s of tile row
+//     16 b + l at (16 (b / 2), 32 + 16 (b % 2) + l), t2 at (0, 16).
+constexpr int kLS = 32;                          // fp32 columns per step (128-byte rows)
+constexpr int kLNS = 3;                          // ring stages
+constexpr int kLStage = 2 * kTile * kLS * 4;     // 128 rows of 128 bytes
+constexpr int kLMeanRow = kTile;                 // diagonal pairs: the target mean's stage row
+constexpr int kKindS = 16, kKindT2 = 17;         // wave tasks beyond the block masks 0..15
+
+__global__ __launch_bounds__(kThreads, 2) void gram_tile_lds_kernel(GramArgs a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[kLNS * kLStage];
+  const int chunk = blockIdx.x, q = blockIdx.y, p = blockIdx.z;
+  const long long g0 = a.goff[p], g1 = a.goff[p + 1];
+  const long long c0 = g0 + (long long)chunk * a.CK;
+  // with one chunk per group the tile is final and written here, so an
+  // empty group still writes its zeros (no steps)
+  const bool direct = a.maxchunks == 1;
+  if (c0 >= g1 && !direct) return;
+  const long long c1 = c0 + a.CK < g1 ? c0 + a.CK : g1;
+  const int nsteps = c1 > c0 ? (int)((c1 - c0 + kLS - 1) / kLS) : 0;
+  int I, J;
+  pair_to_tiles(q, I, J);
+  const bool diag = I == J;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int lr = lane & 15, lg = lane >> 4;
+  const int wr = w >> 1, wc = w & 1;
+  // loader: segment e = tid + 256 u of a stage is stage row e / 8, segment
+  // e % 8 (an off-diagonal pair loads u = 0..3, a diagonal one u = 0..2).
+  // An entry outside the problem reads the target mean's first 16 bytes
+  // instead and is zeroed at the LDS write, so the loads are unconditional
+  // and their waits counted.
+  const unsigned char* mean = reinterpret_cast<const unsigned char*>(a.gbar);   // by absolute column
+  const unsigned char* src[4];
+  bool rok[4];
+  int sseg[4];
+  unsigned loff[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int e = tid + kThreads * u, R = e >> 3, sg = e & 7;
+    if (R < kTile || !diag) {
+      const int grow = R < kTile ? I * kTile + R : J * kTile + (R - kTile);
+      rok[u] = grow < a.n;
+      src[u] = rok[u] ? a.G + (long long)grow * a.ldG * 4 : mean;
+    } else {
+      rok[u] = R == kLMeanRow;
+      src[u] = mean;
+    }
+    sseg[u] = sg;
+    loff[u] = (unsigned)(R * 128 + ((sg ^ ((R >> 1) & 7)) * 16));
+  }
+  auto seg_ok = [&](int t, int u) { return rok[u] && c0 + (long long)t * kLS + sseg[u] * 4 < c1; };
+  // the zeroing happens at the LDS write, so nothing waits for the loads
+  // until then
+  auto gload = [&](int t, u32x4 (&v)[4], auto nu) {
+#pragma unroll
+    for (int u = 0; u < decltype(nu)::value; ++u) {
+      const long long c = c0 + (long long)t * kLS + sseg[u] * 4;
+      v[u] = *reinterpret_cast<const u32x4*>(seg_ok(t, u) ? src[u] + c * 4 : mean);
+    }
+  };
+  auto lstore = [&](int t, const u32x4 (&v)[4], auto nu) {
+    unsigned char* sb = lds + (t % kLNS) * kLStage;
+#pragma unroll
+    for (int u = 0; u < decltype(nu)::value; ++u)
+      *reinterpret_cast<u32x4*>(sb + loff[u]) = seg_ok(t, u) ? v[u] : u32x4{0u, 0u, 0u, 0u};
+  };
+  f32x4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // the wave's products of step t.  Kind 0..15: the 16 x 16 blocks (i, j)
+  // whose bit i * 2 + j is set (A block i against B block j); kKindT2: mask
+  // 13 plus the target mean against itself into acc[0][1]; kKindS: the
+  // target mean against the tile's four 16-row blocks into acc[b / 2][b % 2]
+  auto compute = [&](int t, auto kind, auto dg) {
+    constexpr int KD = decltype(kind)::value;
+    constexpr bool DG = decltype(dg)::value;
+    if constexpr (KD != 0) {
+      const unsigned char* sb = lds + (t % kLNS) * kLStage;
+      const unsigned char* bb = sb + (DG ? 0 : kTile * 128);   // B operand rows
+      f32x4 sum[2][2];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kh = 0; kh < 2; ++kh) {
+        const int sg = 4 * kh + lg;
+        if constexpr (KD == kKindS) {
+          const u32x4 fm = swz_read(sb + kLMeanRow * 128, lr, sg);
+          u32x4 fb[4];
+#pragma unroll
+          for (int b = 0; b < 4; ++b) fb[b] = swz_read(sb + 16 * b * 128, lr, sg);
+          sum[0][0] = mma_v<false>(fm, fb[0], sum[0][0]);
+          sum[0][1] = mma_v<false>(fm, fb[1], sum[0][1]);
+          sum[1][0] = mma_v<false>(fm, fb[2], sum[1][0]);
+          sum[1][1] = mma_v<false>(fm, fb[3], sum[1][1]);
+        } else {
+          constexpr int M = KD == kKindT2 ? 13 : KD;
+          constexpr bool ra0 = (M & 3) != 0, ra1 = (M & 12) != 0, rb0 = (M & 5) != 0, rb1 = (M & 10) != 0;
+          u32x4 fa[2], fb[2];
+          if constexpr (ra0) fa[0] = swz_read(sb + (wr * 32) * 128, lr, sg);
+          if constexpr (ra1) fa[1] = swz_read(sb + (wr * 32 + 16) * 128, lr, sg);
+          if constexpr (rb0) fb[0] = swz_read(bb + (wc * 32) * 128, lr, sg);
+          if constexpr (rb1) fb[1] = swz_read(bb + (wc * 32 + 16) * 128, lr, sg);
+          if constexpr ((M & 1) != 0) sum[0][0] = mma_v<false>(fa[0], fb[0], sum[0][0]);
+          if constexpr ((M & 2) != 0) sum[0][1] = mma_v<false>(fa[0], fb[1], sum[0][1]);
+          if constexpr ((M & 4) != 0) sum[1][0] = mma_v<false>(fa[1], fb[0], sum[1][0]);
+          if constexpr ((M & 8) != 0) sum[1][1] = mma_v<false>(fa[1], fb[1], sum[1][1]);
+          if constexpr (KD == kKindT2) {
+            const u32x4 fm = swz_read(sb + kLMeanRow * 128, lr, sg);
+            sum[0][1] = mma_v<false>(fm, fm, sum[0][1]);
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] += sum[i >> 1][i & 1];
+    }
+  };
+  // step t: products from stage t % 3; the data of step t + 2 (loaded two
+  // steps ago) into stage (t + 2) % 3, last read at step t - 1; the loads of
+  // step t + 4; one barrier
+  auto run = [&](auto dg, auto kind) {
+    constexpr bool DG = decltype(dg)::value;
+    const std::integral_constant<int, DG ? 3 : 4> nu;
+    u32x4 va[4], vb[4];
+    gload(0, va, nu);
+    gload(1, vb, nu);
+    lstore(0, va, nu);
+    lstore(1, vb, nu);
+    gload(2, va, nu);
+    gload(3, vb, nu);
+    __syncthreads();
+    for (int t = 0; t < nsteps; t += 2) {
+      compute(t, kind, dg);
+      lstore(t + 2, va, nu);
+      __builtin_amdgcn_sched_barrier(0);
+      gload(t + 4, va, nu);
+      __builtin_amdgcn_sched_barrier(0);
+      DR_LDS_SYNC();
+      compute(t + 1, kind, dg);   // past the last step its stage holds zeros: the products add 0
+      lstore(t + 3, vb, nu);
+      __builtin_amdgcn_sched_barrier(0);
+      gload(t + 5, vb, nu);
+      __builtin_amdgcn_sched_barrier(0);
+      DR_LDS_SYNC();
+    }
+  };
+  // Blocks the reduction never reads take no products and keep zero
+  // accumulators: A rows wholly past row n - 1 (I >= J, so these are the
+  // last tile's), and on a diagonal tile the blocks wholly above the
+  // diagonal.  The mask is uniform over the wave and is rounded up to the
+  // smallest loop variant that contains it (extra products are harmless).
+  int live = 0;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int rb = I * kTile + wr * 32 + 16 * i, cb = J * kTile + wc * 32 + 16 * j;
+      if (rb < a.n && cb <= rb + 15) live |= 1 << (i * 2 + j);
+    }
+  using F = std::false_type;
+  using T = std::true_type;
+  if (!diag) {
+    // J < I: every B block lies below the A rows, so live is 0, 3 or 15
+    if (live == 0)
+      run(F{}, std::integral_constant<int, 0>{});
+    else if ((live & ~3) == 0)
+      run(F{}, std::integral_constant<int, 3>{});
+    else
+      run(F{}, std::integral_constant<int, 15>{});
+  } else if (wr == 0 && wc == 1) {
+    run(T{}, std::integral_constant<int, kKindS>{});
+  } else if (I == 0 && wr == 0 && wc == 0) {
+    run(T{}, std::integral_constant<int, kKindT2>{});   // its live blocks are within mask 13
+  } else if (live == 0) {
+    run(T{}, std::integral_constant<int, 0>{});
+  } else if ((live & ~1) == 0) {
+    run(T{}, std::integral_constant<int, 1>{});
+  } else if ((live & ~3) == 0) {
+    run(T{}, std::integral_constant<int, 3>{});
+  } else if ((live & ~13) == 0) {
+    run(T{}, std::integral_constant<int, 13>{});
+  } else {
+    run(T{}, std::integral_constant<int, 15>{});
+  }
+
+  if (direct) {
+    // the reduction's writes for a single chunk: K's lower triangle and
+    // mirror, and from a diagonal tile the scores and t2 in its upper
+    // triangle
+    float* Kp = a.K + (a.pbase + p) * (long long)a.n * a.n;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int tr = wr * 32 + i * 16 + lg * 4 + r, tc = wc * 32 + j * 16 + lr;
+          const int row = I * kTile + tr, col = J * kTile + tc;
+          const float v = acc[i][j][r];
+          if (col <= row) {
+            if (row < a.n) {
+              Kp[(long long)row * a.n + col] = v;
+              Kp[(long long)col * a.n + row] = v;
+            }
+          } else if (diag) {
+            if ((tr == 0 || tr == 16) && tc >= 32) {
+              const int srow = I * kTile + 2 * tr + (tc - 32);
+              if (srow < a.n) a.s[(a.pbase + p) * (long long)a.n + srow] = v;
+            } else if (I == 0 && tr == 0 && tc == 16) {
+              a.t2[a.pbase + p] = v;
+            }
+          }
+        }
+    return;
+  }
+  float* out = a.partial + (((long long)p * a.pairs + q) * a.maxchunks + chunk) * (kTile * kTile);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        out[(wr * 32 + i * 16 + lg * 4 + r) * kTile + wc * 32 + j * 16 + lr] = acc[i][j][r];
 }
 
 // fp32 rows, n + 1 > 128: 256-row tiles on bf16 MFMA.  Each value is split
@@ -1176,17 +1423,66 @@ struct GramPlan {
   int NT, pairs, CK, maxchunks;
   size_t gbar_bytes, partial_bytes;
   size_t bytes;     // workspace of the call: gbar and the partial tiles, or more (see gram_plan)
+  bool lds_tiles;   // fp32 rows: gram_tile_lds_kernel, not gram_split_kernel
   bool small;       // gram_small_kernel path
   int NRP;          // its padded row count
 };
 
 bool gram_use_small(int64_t n, dr_dtype dtype) { return dtype == DR_F32 && n >= 1 && n + 1 <= kSmMaxRows; }
 
-// Chunk length: a multiple of 256 columns; for bf16 tiles shrunk until a
-// launch has about kTargetWGs workgroups, for fp32 tiles sized to two
-// rounds of kLdsSlots; identical for every launch of a call.
+// Chunk of gram_tile_lds_kernel: the multiple of 256 columns that keeps the
+// launch just within two rounds of kLdsSlots, so that the second round is
+// nearly full (the fixed count keeps the chunking, and with it the summation
+// order, the same on every device)
+int64_t lds_tile_chunk(int64_t maxw, int64_t pairs, int64_t groups) {
+  const int64_t all = align_up((size_t)(maxw > 0 ? maxw : 1), 256);
+  const int64_t c = align_up((size_t)((maxw * pairs * groups + 2 * kLdsSlots - 1) / (2 * kLdsSlots)), 256);
+  return c < 256 ? 256 : (c < all ? c : all);
+}
+
+// The fp32 tile kernels' times in us, to within 6.5 % (64 x 64 tiles) and 9.5 %
+// (split tiles), fitted to 650 shapes of 128 to 1100 rows, 1 to 224 groups and
+// 32 to 229376 columns; the call takes the lesser (the split tiles on a near
+// tie), within 0.3 % of the better one on average.  Few columns, few rows and
+// short last row tiles leave the split tiles' 256 workgroups idle: one group of
+// 256 x 4096 24.5 us split and 18.3 in 64 x 64 tiles, 224 groups of 257 x 256
+// 180 and 88, one of 512 x 1024 23.3 and 17.4; but one of 256 x 65536 47 and 71.
+// K's own writes count where it is large, and the chunk partials, written and
+// read again.
+double lds_tiles_time(int64_t n, int64_t pairs, int64_t groups, int64_t maxw) {
+  const int64_t ck = lds_tile_chunk(maxw, pairs, groups), chunks = maxw > 0 ? (maxw + ck - 1) / ck : 1;
+  const double wgs = (double)(pairs * groups * chunks), rounds = wgs / kLdsSlots;
+  const double cols = (double)(ck < maxw ? ck : maxw) * 1e-3;
+  double t = 8.5 + cols * (52.0 * (rounds > 1.0 / 3 ? rounds : 1.0 / 3) + 5.1 * std::ceil(rounds));
+  t += 0.34 * 4e-6 * (double)(n * n * groups);
+  if (chunks > 1) t += 1.5 + 0.63 * 1e-6 * wgs * (kTile * kTile * 4);
+  return t;
+}
+
+double split_tiles_time(int64_t n, int64_t pairs, int64_t groups, int64_t steps, int64_t chunks) {
+  const int64_t T = (n + kPRows - 1) / kPRows;
+  // Workgroups are dealt to the eight XCDs in turn: with a multiple of eight
+  // per group each XCD gets one kind of tile, and the chip waits for whole
+  // rounds of the longest; otherwise short tiles make room for others.
+  double rounds = (double)(T * T * groups * chunks) / kSplitSlots;
+  rounds = T == 1 || T * T * chunks % 8 == 0 ? std::ceil(rounds) : (rounds > 1.0 ? rounds : 1.0);
+  const double rows = n < kPRows ? (double)n / kPRows : 1.0, out = 4e-6 * (double)(n * n * groups);
+  double t = 5.6 + rounds * ((double)((steps + chunks - 1) / chunks) * (1.12 + 1.42 * rows) + 1.4 + 5.3 * rows);
+  t += 0.16 * out;
+  if (chunks > 1) {
+    t += 0.45 * 1e-6 * (double)(pairs * groups * chunks * (kTile * kTile * 4)) - 1.1;
+  } else if (T > 1) {   // written by elements: a broken 64-row block, rows off 16 bytes
+    if (n % 64 && (n - 1) % kPRows >= 64) t += 0.25 * out;
+    if (n % 4) t += 0.14 * out;
+  }
+  return t;
+}
+
+// Chunk length: bf16 tiles, a multiple of 256 columns, shrunk until a launch
+// has about kTargetWGs workgroups; fp32 tiles, see the two rules; identical for
+// every launch of a call.
 GramPlan gram_plan(int64_t n, const int64_t* goff, int P, dr_dtype dtype) {
-  GramPlan g;
+  GramPlan g = {};
   // fp32 sketches: gbar joins as row n, so s and t2 come out of the same
   // pass (the tiles cover the n general rows; the diagonal tiles carry gbar)
   const int64_t rows = dtype == DR_F32 ? n + 1 : n;
@@ -1217,19 +1513,23 @@ GramPlan gram_plan(int64_t n, const int64_t* goff, int P, dr_dtype dtype) {
     }
     ck = (steps + chunks - 1) / chunks * kPC;
     if (ck < kPC) ck = kPC;
+    g.lds_tiles = n > 0 &&
+                  lds_tiles_time(n, g.pairs, gp, maxw) < 0.95 * split_tiles_time(n, g.pairs, gp, steps, chunks);
+    if (g.lds_tiles) ck = lds_tile_chunk(maxw, g.pairs, gp);
   } else {
     while (ck > 256 && (int64_t)g.pairs * gp * ((maxw + ck - 1) / ck) < kTargetWGs) ck = align_up((size_t)(ck / 2), 256);
   }
   g.CK = (int)ck;
   g.maxchunks = (int)((maxw + ck - 1) / ck);
   if (g.maxchunks < 1) g.maxchunks = 1;
-  // fp32 rows: the kernels form gbar in LDS (with n = 0 it is the whole work)
-  const int64_t gcols = dtype == DR_F32 && n > 0 ? 0 : goff[P];
+  g.small = gram_use_small(n, dtype);
+  if (g.small) g.lds_tiles = false;
+  // fp32 rows: the kernels form gbar in LDS, but for the 64 x 64 tiles (with n = 0 it is the whole work)
+  const int64_t gcols = dtype == DR_F32 && n > 0 && !g.lds_tiles ? 0 : goff[P];
   g.gbar_bytes = align_up((size_t)(gcols > 0 ? gcols : 1) * sizeof(float), 256);
   g.partial_bytes = (size_t)gp * g.pairs * g.maxchunks * kTile * kTile * sizeof(float);
   if (rows == 0 || gram_use_big(n, P, dtype) || (dtype == DR_F32 && g.maxchunks == 1)) g.partial_bytes = 0;
   g.rows = rows;
-  g.small = gram_use_small(n, dtype);
   g.NRP = (int)((n + 1 + 15) / 16 * 16);
   if (g.small) {
     g.maxchunks = (int)((maxw + kSmCK - 1) / kSmCK);
@@ -1239,17 +1539,14 @@ GramPlan gram_plan(int64_t n, const int64_t* goff, int P, dr_dtype dtype) {
   g.bytes = g.gbar_bytes + g.partial_bytes;
   if (dtype == DR_F32 && n > 0) {
     // The size asked for does not fall below gbar over all columns and, for
-    // tiled rows, the chunk partials of 64 x 64 tiles at two rounds of 768
-    // workgroups: dr_gram_noalloc's limit is stated in it, so that which
-    // problems that call refuses does not depend on how the tiles are cut.
+    // tiled rows, the chunk partials of gram_tile_lds_kernel: dr_gram_noalloc's
+    // limit is stated in it, so that which problems that call refuses does not
+    // depend on how the tiles are cut.
     size_t floor = align_up((size_t)(goff[P] > 0 ? goff[P] : 1) * sizeof(float), 256);
     if (g.small) {
       floor += g.partial_bytes;
     } else {
-      const int64_t all = align_up((size_t)(maxw > 0 ? maxw : 1), 256), slots = 2 * 768;
-      int64_t c = align_up((size_t)((maxw * g.pairs * gp + slots - 1) / slots), 256);
-      if (c < 256) c = 256;
-      if (c > all) c = all;
+      const int64_t c = lds_tile_chunk(maxw, g.pairs, gp);
       floor += (size_t)gp * g.pairs * (maxw > 0 ? (maxw + c - 1) / c : 1) * kTile * kTile * sizeof(float);
     }
     if (floor > g.bytes) g.bytes = floor;
@@ -1309,7 +1606,7 @@ dr_status gram_run(const GramPlan& g, const void* G, int64_t n, int64_t ldG, con
   float* partial = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + g.gbar_bytes);
 
   const long long c_lo = goff[0], c_hi = goff[P];
-  if (c_hi > c_lo && (bf || n == 0)) {   // the fp32 kernels form gbar inside their chunks
+  if (c_hi > c_lo && (bf || n == 0 || g.lds_tiles)) {   // the other fp32 kernels form gbar inside their chunks
     const int blocks = (int)((c_hi - c_lo + kThreads - 1) / kThreads);
     if (bf)
       hipLaunchKernelGGL(target_mean_kernel<true>, dim3(blocks), dim3(kThreads), 0, hs,
@@ -1373,6 +1670,8 @@ dr_status gram_run(const GramPlan& g, const void* G, int64_t n, int64_t ldG, con
     } else if (g.pairs > 0) {
       if (bf) {
         hipLaunchKernelGGL(gram_tile_kernel, dim3(g.maxchunks, g.pairs, gp), dim3(kThreads), 0, hs, a);
+      } else if (g.lds_tiles) {
+        hipLaunchKernelGGL(gram_tile_lds_kernel, dim3(g.maxchunks, g.pairs, gp), dim3(kThreads), 0, hs, a);
       } else {
         const int T = (int)((n + kPRows - 1) / kPRows);
         hipLaunchKernelGGL(gram_split_kernel, dim3(g.maxchunks, T * T, gp), dim3(kPThreads), 0, hs, a);

@@ -663,33 +663,68 @@ def test_gram_fp32_split_tiles_against_fp64(n, goff, m):
     of its terms' sizes (one part split, 2^-25, per operand; the truncated sum
     of a 32-column step; the additions of the steps, whose errors grow at most
     with the square root of their number and not in one direction)."""
+    check_fp32_tiles(n, goff, m, 6 * 2.0 ** -24)
+
+
+def check_fp32_tiles(n, goff, m, tol):
     rows = rand((n + m, goff[-1]), 3 * n + m, scale=1.0) + 0.5
     G, Gt = rows[:n].contiguous(), rows[n:].contiguous()
     K, s, t2 = api.gram(G, Gt, goff)
     torch.cuda.synchronize()
     for p, (a, b) in enumerate(zip(goff, goff[1:])):
         g, gbar = G[:, a:b].double(), Gt[:, a:b].double().mean(0).float().double()
-        tol = 6 * 2.0 ** -24
         assert ((K[p].double() - g @ g.t()).abs() <= tol * (g.abs() @ g.abs().t())).all()
         assert ((s[p].double() - g @ gbar).abs() <= tol * (g.abs() @ gbar.abs())).all()
         assert abs(float(t2[p]) - float(gbar @ gbar)) <= tol * float(gbar @ gbar)
         assert torch.equal(K[p], K[p].t())
 
 
-@pytest.mark.parametrize("n", [130, 300])
+def ragged(count, most, *some):
+    """Offsets of `count` groups, the widths `some` among groups of `most` columns."""
+    widths = [most] * count
+    for k, w in enumerate(some):
+        widths[(3 * k + 1) % count] = w
+    return [int(v) for v in np.concatenate([[0], np.cumsum(widths)])]
+
+
+@pytest.mark.parametrize("n,goff,m", [
+    (128, ragged(150, 1024, 32, 0, 4), 1),          # one row tile
+    (255, ragged(40, 2012, 36, 0, 1984), 17),       # ragged steps, an empty group, windows of the target mean
+    (256, ragged(3, 65536, 8200), 3),
+    (300, ragged(64, 1000, 4, 996), 2),             # one chunk: K, s and t2 from the tiles themselves
+    (301, ragged(64, 1000, 0, 60), 2),              # the same with rows of K off 16 bytes
+    (320, ragged(9, 2800, 2796), 5),
+    (449, ragged(9, 2400, 0, 1200), 33),            # 449 = 256 + 193: a last tile with one row in its fourth block
+    (512, ragged(9, 260, 4, 256), 2),
+])
+def test_gram_fp32_split_tiles_of_many_groups(n, goff, m):
+    """As above, with as many groups or columns as the split tiles are taken for (some of the shapes above are too small
+    for them).  A chunk of up to 64 steps has 64 additions of at most 2^-24 of the sum so far, which grows evenly: a
+    standard deviation of 2.7 * 2^-24 of the whole, of which the 6 million entries of a case see 5, and 2 * 2^-24 for
+    the parts and the sums inside a step."""
+    check_fp32_tiles(n, goff, m, 16 * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("n,groups", [(130, 1), (300, 1), (420, 8)])   # the last on split tiles, both kinds of them
 @pytest.mark.parametrize("col", [3, 70, 1900])
-def test_gram_fp32_infinities_and_large_values(n, col):
+def test_gram_fp32_infinities_and_large_values(n, groups, col):
     """An infinity, and values whose products overflow fp32, come out as fp32
     arithmetic gives them (not as NaN from their bf16 parts), from the first
     step or a later one, and leave the other rows alone."""
     cols, m = 2000, 2
-    G, Gt = rand((n, cols), n + col).abs() + 0.5, rand((m, cols), n + col + 1).abs() + 0.5
+    at = (groups // 2) * cols
+    G, Gt = rand((n, groups * cols), n + col).abs() + 0.5, rand((m, groups * cols), n + col + 1).abs() + 0.5
+    col += at
     G[5, col] = float("inf")
     G[n - 1, col] = 3e38
     G[n - 2, col] = float("nan")
-    K, s, t2 = api.gram(G, Gt, [0, cols])
+    K, s, t2 = api.gram(G, Gt, [cols * p for p in range(groups + 1)])
     torch.cuda.synchronize()
-    K, s = K[0], s[0]
+    for p in range(groups):
+        if p != groups // 2:
+            assert bool(torch.isfinite(K[p]).all() and torch.isfinite(s[p]).all())
+    K, s = K[groups // 2], s[groups // 2]
+    G, Gt = G[:, at:at + cols], Gt[:, at:at + cols]
     ok = torch.ones(n, dtype=torch.bool, device=DEV)
     ok[[5, n - 1, n - 2]] = False
     assert torch.isinf(K[5, ok]).all() and torch.isinf(s[5]) and (K[5, ok] > 0).all()
@@ -702,13 +737,14 @@ def test_gram_fp32_infinities_and_large_values(n, col):
     assert np.allclose(host64(K[n - 1, ok]), big, rtol=1e-5)
 
 
-@pytest.mark.parametrize("n", [130, 300])
+@pytest.mark.parametrize("n,groups", [(130, 1), (300, 1), (420, 20)])   # the last on split tiles, both kinds of them
 @pytest.mark.parametrize("scale", [1e-30, 1e-33, 1e-34, 1e-36, 1e-38])
-def test_gram_fp32_tiny_values(n, scale):
+def test_gram_fp32_tiny_values(n, groups, scale):
     """Values whose lower bf16 parts would be subnormal or below: rows of that size against targets of order one, all
     of them, or one row and one value in a later step beside rows of order one and rows of zeros.  fp32 products of 512
     terms with fp32 sums: 2e-6 of a row's sum of sizes covers sqrt(512) roundings of 2^-24."""
     Gt = rand((2, 512), 12)
+    goff = [512 * p for p in range(groups + 1)]
     for some in (False, True):
         G = rand((n, 512), 11)
         if some:
@@ -718,8 +754,9 @@ def test_gram_fp32_tiny_values(n, scale):
             G[20:30] = 0.0
         else:
             G *= scale
-        K, s, t2 = api.gram(G, Gt, [0, 512])
+        K, s, t2 = api.gram(G.repeat(1, groups), Gt.repeat(1, groups), goff)
         torch.cuda.synchronize()
+        assert all(torch.equal(K[p], K[0]) and torch.equal(s[p], s[0]) for p in range(groups))
         g, b = G.double(), Gt.double().mean(0).float().double()
         ref, size = g @ b, g.abs() @ b.abs()
         assert bool(((s[0].double() - ref).abs() <= 2e-6 * size + 1e-45).all())
