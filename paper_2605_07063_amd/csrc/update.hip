@@ -1198,11 +1198,13 @@ extern "C" dr_status dr_assemble_update(const dr_layer* layers, int num_layers, 
   auto packed = [&](const dr_layer& L) {
     return n * T * (L.ldx > L.lddy ? L.ldx : L.lddy) * es < (int64_t)kOobOffset - 64;
   };
-  // Calls of up to kSmallFlops products leave every list to update_bf16_kernel:
-  // the second tile kernel's launch costs more than its faster loop saves (two
-  // layers 640 x 640, 5 examples of up to 159 tokens, 1.3 GFLOP: 28 us, 35 with
-  // both; three layers, 0.1 TFLOP: 247 us, 174 with both).
-  constexpr double kSmallFlops = 1.5e10;
+  // Calls of up to kSmallFlops leave every list to update_bf16_kernel: the
+  // second tile kernel's launch, the step tables and the fill of its longer
+  // pipeline cost more than its faster loop saves (32 to 64 examples of equal
+  // weight, all and half of them: 17 GFLOP 2 to 30 % slower with both, 34 GFLOP
+  // 4 %, 69 GFLOP 3 % faster, 137 GFLOP 12 %, 275 GFLOP 19 %, medians of 20 to
+  // 56 shapes each).
+  constexpr double kSmallFlops = 5e10;
   double flops = 0.0;
   for (int l = 0; l < num_layers; ++l) flops += 2.0 * (double)(n * T) * (double)(layers[l].d_in * layers[l].d_out);
   int modes = 0;

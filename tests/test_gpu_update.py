@@ -237,8 +237,8 @@ def sample(d, edges):
     return torch.unique(torch.cat([torch.randint(0, d, (60,), generator=g), torch.tensor(edges)])).to(DEV)
 
 
-# wide layers: calls of less than 1.5e10 products leave every list to the
-# kernel for several weights
+# (calls of this size leave every list to the kernel for several weights; the
+# same lists in larger calls are below)
 @pytest.mark.parametrize("T,d_in,d_out,lens", [
     (100, 2312, 2568, [16, 15, 17, 16, 16, 31, 32, 33, 1, 100, 47, 16, 0, 99]),   # up to three examples in a step
     (15, 6008, 6016, [15, 1, 8, 14, 15, 0, 15, 3, 7, 15, 15, 2, 9, 11]),          # all below the packing length
@@ -317,3 +317,59 @@ def test_nan_weight_reaches_every_element(n, dtype):
             api.dr_assemble_update(layers, n, T, lens, w, U, [0], workspace=ws)
             torch.cuda.synchronize()
             assert bool(torch.isfinite(U).all())
+
+
+def products(layers, n, T):
+    return 2.0 * n * T * sum(L["x"].shape[2] * L["dy"].shape[2] for L in layers)
+
+
+# above this many products lists of equal weights take a tile kernel of their own
+TILE_PRODUCTS = 5e10
+
+
+@pytest.mark.parametrize("T,d_in,d_out,lens", [
+    (100, 4104, 4624, [16, 15, 17, 16, 16, 31, 32, 33, 1, 100, 47, 16, 0, 99]),   # up to three examples in a step
+    (15, 10760, 11528, [15, 1, 8, 14, 15, 0, 15, 3, 7, 15, 15, 2, 9, 11]),        # all below the packing length
+    (64, 5384, 5520, [64] * 14),                                                  # whole steps only
+    (40, 6664, 6920, [40] * 14),                                                  # every example ends inside a step
+])
+def test_equal_weights_packed_steps_of_large_calls(T, d_in, d_out, lens):
+    n = len(lens)
+    lens = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    layers = make_layers([(d_in, d_out)], n, T, torch.bfloat16, lens, seed=21, nan_rows=(4, 5))
+    assert products(layers, n, T) > TILE_PRODUCTS
+    check(layers, equal_weights(n, skip=(4, 5)), n, lens, rows=sample(d_out, [0, 255, 256, d_out - 1]),
+          cols=sample(d_in, [0, 255, 256, d_in - 1]))
+
+
+def test_equal_and_mixed_weight_rows_in_one_large_call():
+    n, T = 9, 270
+    lens = torch.tensor([270, 3, 64, 20, 33, 270, 16, 69, 150], dtype=torch.int32, device=DEV)
+    layers = make_layers([(2312, 264), (136, 2600), (64, 64), (3400, 3400)], n, T, torch.bfloat16, lens, seed=23)
+    assert products(layers, n, T) > TILE_PRODUCTS
+    w = torch.stack([equal_weights(n, skip=(1,)), mixed_weights(n, 3), torch.zeros(n, device=DEV)])
+    picks = torch.tensor([0, 1, 40, 63], device=DEV)
+    check(layers, w, n, lens, group_of_layer=[0, 1, 2, 0], rows=picks, cols=picks)
+
+
+def test_more_examples_than_one_workgroup_sorts_in_a_large_call():
+    n, T = 1100, 12
+    g = torch.Generator().manual_seed(6)
+    lens = torch.randint(0, T + 1, (n,), generator=g, dtype=torch.int32).to(DEV)
+    layers = make_layers([(1400, 1400), (264, 264)], n, T, torch.bfloat16, lens, seed=25)
+    assert products(layers, n, T) > TILE_PRODUCTS
+    picks = torch.tensor([0, 100, 255, 263], device=DEV)
+    check(layers, equal_weights(n, skip=range(0, n, 3)), n, lens, rows=picks, cols=picks)
+    check(layers, mixed_weights(n, 6), n, lens, rows=picks, cols=picks)
+
+
+def test_equal_weights_rows_further_apart_in_a_large_call():
+    n, T, ld = 6, 300, 1_500_000
+    lens = torch.tensor([300, 0, 257, 17, 299, 33], dtype=torch.int32, device=DEV)
+    layers = make_layers([(3968, 3600)], n, T, torch.bfloat16, lens, seed=24)
+    assert products(layers, n, T) > TILE_PRODUCTS
+    wide = torch.empty(n * T * ld, dtype=torch.bfloat16, device=DEV).view(n, T, ld)
+    wide[:, :, :3968] = layers[0]["x"]
+    layers[0]["x"] = wide[:, :, :3968]
+    picks = sample(3600, [0, 3599])
+    check(layers, equal_weights(n), n, lens, rows=picks, cols=picks)
