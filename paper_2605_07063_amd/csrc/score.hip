@@ -61,11 +61,13 @@ __device__ __forceinline__ void issue_panel(__amdgpu_buffer_rsrc_t rs, const Pan
   }
 }
 
-// acc[i][j] += A[64 wr + 16 i + .][k] B[64 wc + 16 j + .][k] over k < K, A
-// and B given as row panels
+// acc[i][j] += A[64 wr + 16 i + .][k] B[64 wc + 16 j + .][k] over k < K for
+// NB B panels (summed), A and B given as row panels
+template <int NB>
 __device__ __forceinline__ void panel_gemm(unsigned char* lds, __amdgpu_buffer_rsrc_t ra, const PanelRows& pa,
-                                           __amdgpu_buffer_rsrc_t rb, const PanelRows& pb, int K, f32x4 (&acc)[4][4]) {
-  constexpr int kStage = 2 * kSPanel;
+                                           const __amdgpu_buffer_rsrc_t (&rb)[NB], const PanelRows& pb, int K,
+                                           f32x4 (&acc)[4][4]) {
+  constexpr int kStage = (1 + NB) * kSPanel;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = w >> 1, wc = w & 1, lr = lane & 15, lg = lane >> 4;
@@ -73,7 +75,8 @@ __device__ __forceinline__ void panel_gemm(unsigned char* lds, __amdgpu_buffer_r
   auto issue = [&](int t, int st) {
     unsigned char* sb = lds + st * kStage;
     issue_panel(ra, pa, sb, w, t * kSK, K);
-    issue_panel(rb, pb, sb + kSPanel, w, t * kSK, K);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) issue_panel(rb[b], pb, sb + (1 + b) * kSPanel, w, t * kSK, K);
   };
   issue(0, 0);
   for (int t = 0; t < nk; ++t) {
@@ -84,15 +87,19 @@ __device__ __forceinline__ void panel_gemm(unsigned char* lds, __amdgpu_buffer_r
 #pragma unroll
     for (int kh = 0; kh < 2; ++kh) {
       const int seg = 4 * kh + lg;
-      u32x4 fa[4], fb[4];
+      u32x4 fa[4], fb[NB][4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) fa[i] = swz_read(sa + (4 * wr + i) * 2048, lr, seg);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) fb[j] = swz_read(sa + kSPanel + (4 * wc + j) * 2048, lr, seg);
+      for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < 4; ++j) fb[b][j] = swz_read(sa + (1 + b) * kSPanel + (4 * wc + j) * 2048, lr, seg);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = mma_bf16(fa[i], fb[j], acc[i][j]);
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[i][j] = mma_bf16(fa[i], fb[b][j], acc[i][j]);
     }
   }
   DR_LDS_SYNC();   // the ring is free for the next use
@@ -109,7 +116,7 @@ struct ScoreLayer {
   const unsigned char* glo;
   double* part;              // partial sums of this layer
   int d_in, d_out;
-  int OB;                    // PIP: 256-column blocks of d_out
+  int OB;                    // PIP: 256-column blocks of d_out (128 in pip_small_kernel)
 };
 
 struct ScoreArgs {
@@ -392,6 +399,90 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
 }
 
+// row panel of a tile's token rows
+__device__ __forceinline__ PanelRows token_panel(const TileRows<kST>& t, long long ex, long long ld) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  PanelRows p;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int hb = w + 4 * u;
+    const int r = 8 * hb + (lane >> 3);
+    p.seg[u] = swz_seg_of_lane(lane, hb & 1);
+    const int rel = t.rel[r];
+    p.off[u] = rel >= 0 ? (unsigned)(rel * ex + t.tok[r] * ld * 2) : kOobOffset;
+  }
+  return p;
+}
+
+// The same in tiles of 128 rows of one example x 128 outputs, both parts of
+// gbar* staged beside the tokens, where there are too few tiles of either size
+// to fill the chip: a tile's own time then counts, and one of 256 x 256 takes
+// longer (the whole call, one layer 1024 x 1024, 16 examples of 128 tokens: 61
+// us, 92 in 256 x 256 tiles; one of 4096 x 4096, one example of 512: 147, 239).
+__global__ __launch_bounds__(kSThreads) void pip_small_kernel(ScoreArgs a) {
+  constexpr int kRing = 2 * 3 * kSPanel;
+  __shared__ __attribute__((aligned(1024))) unsigned char
+      lds[kRing + 2 * kST * sizeof(double) + sizeof(TileRows<kST>)];   // one LDS object, as in pip_kernel
+  double (*rs)[kST] = reinterpret_cast<double (*)[kST]>(lds + kRing);
+  TileRows<kST>& tr = *reinterpret_cast<TileRows<kST>*>(lds + kRing + 2 * kST * sizeof(double));
+  const int TB = (a.T + kST - 1) / kST, R = a.n * TB;
+  int q = blockIdx.x, li = 0;
+  while (li < a.num_layers && q >= R * a.L[li].OB) {
+    q -= R * a.L[li].OB;
+    ++li;
+  }
+  if (li == a.num_layers) return;
+  const ScoreLayer& L = a.L[li];
+  const int rt = q / L.OB, ob = q - rt * L.OB, o0 = ob * kST;
+  if ((rt % TB) * kST >= clamp_len(a.len, rt / TB, a.T)) return;
+  int e0, e_last;
+  const int rows = tile_rows<false>(tr, a.cum, a.len, 0, a.n, a.T, 0, a.span, rt, 0, e0, e_last);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr = w >> 1, wc = w & 1, lr = lane & 15, lg = lane >> 4;
+  const __amdgpu_buffer_rsrc_t ra = make_rsrc(L.x + (long long)e0 * L.exx, kOobOffset);
+  const __amdgpu_buffer_rsrc_t rb[2] = {make_rsrc(L.ghi + (long long)o0 * L.d_in * 2, kOobOffset),
+                                        make_rsrc(L.glo + (long long)o0 * L.d_in * 2, kOobOffset)};
+  PanelRows pb;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int hb = w + 4 * u, r = 8 * hb + (lane >> 3);
+    pb.seg[u] = swz_seg_of_lane(lane, hb & 1);
+    pb.off[u] = o0 + r < L.d_out ? (unsigned)((long long)r * L.d_in * 2) : kOobOffset;
+  }
+  f32x4 acc[4][4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[p][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  panel_gemm<2>(lds, ra, token_panel(tr, L.exx, L.ldx), rb, pb, L.d_in, acc);
+  // dot with the dy rows of the tile (valid tokens and outputs only)
+  const __bf16* dyb = reinterpret_cast<const __bf16*>(L.dy + (long long)e0 * L.exdy) + o0;
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 64 * wr + 16 * p + 4 * lg + r;
+      float d = 0.f;
+      if (row < rows) {
+        const __bf16* dyr = dyb + (long long)tr.tok[row] * L.lddy;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int o = 64 * wc + 16 * j + lr;
+          if (o0 + o < L.d_out) d = fmaf(acc[p][j][r], (float)dyr[o], d);
+        }
+      }
+      double v = (double)d;
+      v += dpp_d<0xB1, 0xF>(v);
+      v += dpp_d<0x4E, 0xF>(v);
+      v += dpp_d<0x141, 0xF>(v);
+      v += dpp_d<0x140, 0xF>(v);
+      if (lr == 0) rs[wc][row] = v;
+    }
+  __syncthreads();
+  tile_example_sums(tr, rs, a.cum, rows, 0, rt, 0, e0, e_last, L.part, L.OB, ob);
+}
+
 // s[l][i] = scale * the sum of the example's partials over its row blocks
 // (in order) and the nc column blocks of each, one wave per (layer, example);
 // OBS: the layer's own column count
@@ -481,18 +572,6 @@ __global__ __launch_bounds__(kSThreads, 2) void gip_kernel(ScoreArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = w >> 1, wc = w & 1, lr = lane & 15, lg = lane >> 4;
-  auto panel = [&](const TileRows<kST>& t, long long ex, long long ld) {
-    PanelRows p;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int hb = w + 4 * u;
-      const int r = 8 * hb + (lane >> 3);
-      p.seg[u] = swz_seg_of_lane(lane, hb & 1);
-      const int rel = t.rel[r];
-      p.off[u] = rel >= 0 ? (unsigned)(rel * ex + t.tok[r] * ld * 2) : kOobOffset;
-    }
-    return p;
-  };
   f32x4 dd[4][4], xx[4][4];
 #pragma unroll
   for (int p = 0; p < 4; ++p)
@@ -503,13 +582,13 @@ __global__ __launch_bounds__(kSThreads, 2) void gip_kernel(ScoreArgs a) {
     }
   {
     const __amdgpu_buffer_rsrc_t ra = make_rsrc(L.dy + (long long)e0 * L.exdy, kOobOffset);
-    const __amdgpu_buffer_rsrc_t rb = make_rsrc(L.dy + (long long)(a.n + f0) * L.exdy, kOobOffset);
-    panel_gemm(lds, ra, panel(tr, L.exdy, L.lddy), rb, panel(tc, L.exdy, L.lddy), L.d_out, dd);
+    const __amdgpu_buffer_rsrc_t rb[1] = {make_rsrc(L.dy + (long long)(a.n + f0) * L.exdy, kOobOffset)};
+    panel_gemm<1>(lds, ra, token_panel(tr, L.exdy, L.lddy), rb, token_panel(tc, L.exdy, L.lddy), L.d_out, dd);
   }
   {
     const __amdgpu_buffer_rsrc_t ra = make_rsrc(L.x + (long long)e0 * L.exx, kOobOffset);
-    const __amdgpu_buffer_rsrc_t rb = make_rsrc(L.x + (long long)(a.n + f0) * L.exx, kOobOffset);
-    panel_gemm(lds, ra, panel(tr, L.exx, L.ldx), rb, panel(tc, L.exx, L.ldx), L.d_in, xx);
+    const __amdgpu_buffer_rsrc_t rb[1] = {make_rsrc(L.x + (long long)(a.n + f0) * L.exx, kOobOffset)};
+    panel_gemm<1>(lds, ra, token_panel(tr, L.exx, L.ldx), rb, token_panel(tc, L.exx, L.ldx), L.d_in, xx);
   }
 #pragma unroll
   for (int p = 0; p < 4; ++p)
@@ -549,6 +628,24 @@ struct ScorePlan {
   double tiles;   // of the largest launch (upper bound)
   size_t off_wm, off_g, off_upd, off_hi, off_lo, off_cum, off_part, off_direct, bytes;
 };
+
+// Few tiles: with one round of workgroups, and each on rows of one example,
+// there is nothing to gain from packing the tokens (nor a prefix to form), and
+// PIP takes the smaller tiles: up to one 128 x 128 tile per CU, at T tokens an
+// example.  (GIP of 512 tiles, two per CU, gains from packing ragged lengths:
+// one layer 4096 x 14336, 4 x 2 examples of T = 1024, 193 us packed, 221 not.)
+constexpr double kSmallTiles = 256.0;
+bool score_small(const dr_layer* layers, int num_layers, int64_t n, int64_t m, int64_t T, int method) {
+  if (method == DR_SCORE_DIRECT) return false;
+  const double TB = (double)((T + kST - 1) / kST);
+  double tiles = 0.0;
+  for (int l = 0; l < num_layers; ++l)
+    tiles += (double)n * TB * (method == DR_SCORE_PIP ? (double)((layers[l].d_out + kST - 1) / kST) : (double)m * TB);
+  return tiles <= kSmallTiles;
+}
+
+// rows of a tile
+int64_t score_rows(int method, bool small) { return method == DR_SCORE_PIP && !small ? kTileRows : kST; }
 
 // 128-token column blocks of the m targets (upper bound)
 int64_t gip_cols(int64_t m, int64_t T, bool packed) {
@@ -626,17 +723,18 @@ ScorePlan score_plan(const dr_layer* layers, int num_layers, int64_t n, int64_t 
   int64_t gmax = 1, partmax = 1;
   double tiles = 0.0;
   size_t updmax = 0, dirmax = 0;
-  const int64_t rows = method == DR_SCORE_PIP ? kTileRows : kST;
   dr_layer t[kMaxScoreLayers];
   for (int l0 = 0; l0 < num_layers;) {
     const int l1 = group_end(layers, num_layers, l0, n, m, T, method);
-    const bool packed = score_packed(layers + l0, l1 - l0, n, m, T, rows);
+    const bool small = score_small(layers + l0, l1 - l0, n, m, T, method);
+    const int64_t rows = score_rows(method, small);
+    const bool packed = !small && score_packed(layers + l0, l1 - l0, n, m, T, rows);
     const int64_t slots = score_slots(n, T, rows, packed);
     int64_t g = 0, cols = 0;
     for (int l = l0; l < l1; ++l) {
       g += layers[l].d_out * layers[l].d_in;
       t[l - l0] = target_layer(layers[l], n, T);
-      cols += method == DR_SCORE_PIP ? (layers[l].d_out + kTileRows - 1) / kTileRows : gip_cols(m, T, packed);
+      cols += method == DR_SCORE_PIP ? (layers[l].d_out + rows - 1) / rows : gip_cols(m, T, packed);
     }
     const int64_t part = slots * cols;
     gmax = g > gmax ? g : gmax;
@@ -722,10 +820,7 @@ extern "C" dr_status dr_score_exact(const dr_layer* layers, int num_layers, int6
     if ((st = launch_status()) != DR_OK) return st;
   }
   int* cum = reinterpret_cast<int*>(ws + pl.off_cum);
-  if (method != DR_SCORE_DIRECT) {
-    hipLaunchKernelGGL(score_plan_kernel, dim3(2), dim3(1024), 0, hs, len, (int)n, (int)m, (int)T, cum);
-    if ((st = launch_status()) != DR_OK) return st;
-  }
+  bool planned = false;
   for (int l0 = 0; l0 < num_layers;) {
     const int l1 = group_end(layers, num_layers, l0, n, m, T, (int)method), cnt = l1 - l0;
     float* sl = s + (int64_t)l0 * n;
@@ -752,13 +847,19 @@ extern "C" dr_status dr_score_exact(const dr_layer* layers, int num_layers, int6
       l0 = l1;
       continue;
     }
-    const int64_t rows = method == DR_SCORE_PIP ? kTileRows : kST;
+    const bool small = score_small(layers + l0, cnt, n, m, T, (int)method);
+    const int64_t rows = score_rows((int)method, small);
     ScoreArgs a = {};
     a.num_layers = cnt;
     a.T = (int)T;
     a.n = (int)n;
     a.m = (int)m;
-    a.packed = score_packed(layers + l0, cnt, n, m, T, rows);
+    a.packed = !small && score_packed(layers + l0, cnt, n, m, T, rows);
+    if (a.packed && !planned) {
+      hipLaunchKernelGGL(score_plan_kernel, dim3(2), dim3(1024), 0, hs, len, (int)n, (int)m, (int)T, cum);
+      if ((st = launch_status()) != DR_OK) return st;
+      planned = true;
+    }
     a.span = (int)score_span(layers + l0, cnt, T);
     a.SB = (int)gip_cols(m, T, a.packed);
     a.len = len;
@@ -779,7 +880,7 @@ extern "C" dr_status dr_score_exact(const dr_layer* layers, int num_layers, int6
       b.exdy = T * L.lddy * 2;
       b.d_in = (int)L.d_in;
       b.d_out = (int)L.d_out;
-      b.OB = (int)((L.d_out + kTileRows - 1) / kTileRows);
+      b.OB = (int)((L.d_out + rows - 1) / rows);
       b.ghi = reinterpret_cast<const unsigned char*>(hi + goff[j]);
       b.glo = reinterpret_cast<const unsigned char*>(lo + goff[j]);
       b.part = part;
@@ -796,9 +897,12 @@ extern "C" dr_status dr_score_exact(const dr_layer* layers, int num_layers, int6
     if (method == DR_SCORE_PIP) {
       hipLaunchKernelGGL(split_kernel, dim3((unsigned)((goff[cnt] + 255) / 256)), dim3(256), 0, hs,
                          (const float*)gstar, (long long)goff[cnt], hi, lo);
-      if (nt > 0)
+      if (nt > 0 && small)
+        hipLaunchKernelGGL(pip_small_kernel, grid, dim3(kSThreads), 0, hs, a);
+      else if (nt > 0)
         hipLaunchKernelGGL(pieces ? pip_kernel<true> : pip_kernel<false>, grid, dim3(256), 0, hs, a);
-      hipLaunchKernelGGL((score_reduce_kernel<kTileRows, true>), rgrid, dim3(256), 0, hs, a, sl, 1.0);
+      hipLaunchKernelGGL((small ? score_reduce_kernel<kST, true> : score_reduce_kernel<kTileRows, true>), rgrid,
+                         dim3(256), 0, hs, a, sl, 1.0);
     } else {
       if (nt > 0)
         hipLaunchKernelGGL(pieces ? gip_kernel<true> : gip_kernel<false>, grid, dim3(kSThreads), 0, hs, a);

@@ -172,3 +172,40 @@ def test_layer_groups():
     lens = torch.tensor([20, 7, 16, 20, 3], dtype=torch.int32, device=DEV)
     specs = [(64 + 8 * (l % 5), 40 + 72 * (l % 4)) for l in range(18)]
     check_all(make(specs, n + m, T, lens, seed=7), n, m, lens, METHODS)
+
+
+# Calls of up to 256 tiles of 128 x 128 (at T tokens an example) take rows of one example to a tile; larger ones pack
+# the tokens.
+
+@pytest.mark.parametrize("length", [255, 256, 257])
+def test_packed_tile_edges_of_larger_calls(length):
+    n, m, T = 3, 2, 257
+    lens = torch.tensor([length, 1, length, length, 128], dtype=torch.int32, device=DEV)
+    check_all(make([(64, 3720)], n + m, T, lens, seed=5), n, m, lens, ["pip"])
+    check_all(make([(64, 264)] * 10, n + m, T, lens, seed=5), n, m, lens, ["gip"])
+
+
+def test_rows_further_apart_in_a_larger_call():
+    n, m, T, ld = 5, 2, 300, 1_500_000
+    lens = torch.tensor([300, 0, 257, 128, 1, 300, 129], dtype=torch.int32, device=DEV)
+    layers = make([(72, 2200)], n + m, T, lens, seed=6)
+    wide = torch.empty((n + m) * T * ld, dtype=torch.bfloat16, device=DEV).view(n + m, T, ld)
+    wide[:, :, :72] = layers[0]["x"]
+    layers[0]["x"] = wide[:, :, :72]
+    check_all(layers, n, m, lens, ["pip"])
+
+
+def test_layer_groups_of_packed_tiles():
+    n, m, T = 30, 10, 20
+    g = torch.Generator().manual_seed(10)
+    lens = torch.randint(0, T + 1, (n + m,), generator=g, dtype=torch.int32).to(DEV)
+    specs = [(64 + 8 * (l % 5), 40 + 72 * (l % 4)) for l in range(18)]
+    check_all(make(specs, n + m, T, lens, seed=7), n, m, lens, METHODS)
+
+
+@pytest.mark.parametrize("d_in,d_out", [(8, 8), (64, 128), (72, 136), (200, 1000)])
+@pytest.mark.parametrize("T", [1, 127, 128, 129])
+def test_small_calls_at_the_edges_of_a_tile(T, d_in, d_out):
+    n, m = 5, 2
+    lens = torch.tensor([T, 0, 1, max(1, T - 1), T, T, 1], dtype=torch.int32, device=DEV)
+    check_all(make([(d_in, d_out)], n + m, T, lens, seed=11), n, m, lens, ["gip", "pip"])
