@@ -346,12 +346,16 @@ __global__ __launch_bounds__(256, 2) void bp_mfma_kernel(BpArgs g, int per) {
     for (int j = 0; j < 4; ++j) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4*>(st + lr * 64 + (((4 * i + g4) ^ lr) * 4)) = acc[i][j];
+      // other lanes of the wave read what this one wrote, and write there next
+      // (LDS keeps a wave's order; this keeps the compiler to it)
+      asm volatile("" ::: "memory");
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int r = 4 * i + g4, o = o0 + 64 * wr + 16 * j + r, c = c0 + 64 * wc + 4 * lr;
         const f32x4 v = *reinterpret_cast<const f32x4*>(st + r * 64 + ((lr ^ r) * 4));
         if (o < d_out && c < d_in) *reinterpret_cast<f32x4*>(U + (long long)o * d_in + c) = v;
       }
+      asm volatile("" ::: "memory");
     }
   }
 }

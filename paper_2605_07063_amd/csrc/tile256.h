@@ -31,6 +31,17 @@ __device__ __forceinline__ void tile256_clear(f32x4 (&acc)[8][8]) {
     }
 }
 
+// The last products' results are read next: wait states after an MFMA that the
+// compiler does not see inside the asm.  Every accumulator then passes through
+// an asm, so that no read of it can be scheduled before the wait.
+__device__ __forceinline__ void tile256_settle(f32x4 (&acc)[8][8]) {
+  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) asm volatile("" : "+a"(acc[i][j]));
+}
+
 // acc[i][j] (i over A's 16-row blocks of this wave, j over B's) += the
 // products of nk steps.  dma1(t, st, q), q = 0..15: one DMA of step t into
 // stage st (zeros for t >= nk).  rd1(fa, fb, stage, kh, q): fragment read q
@@ -79,9 +90,7 @@ __device__ __forceinline__ void tile256_loop(unsigned char* lds, int nk, Dma&& d
       for (int m = 4 * q; m < 4 * q + 4; ++m) mma(m & 7, m >> 3, fa1, fb1);
     }
   }
-  // the last products' results are read next: wait states after an MFMA that
-  // the compiler does not see inside the asm
-  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+  tile256_settle(acc);
 }
 
 }  // namespace dr

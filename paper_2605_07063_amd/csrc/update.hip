@@ -769,9 +769,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     run_step(t, fa0, fb0, fa1, fb1);
     run_step(t + 1, fa1, fb1, fa0, fb0);   // (past the last step: zeros)
   }
-  // the last products' results are read next: wait states after an MFMA that
-  // the compiler does not see inside the asm
-  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+  tile256_settle(acc);
   DR_WAIT_VM(0);
   const float wgt = nk > 0 ? a.exw[(long long)Lr.list * a.n] : 0.f;
 
