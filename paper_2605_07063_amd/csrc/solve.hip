@@ -1446,8 +1446,8 @@ __global__ void empty_group_kernel(const float* t2, int P, float* lam_eff, float
 }  // namespace dr
 
 extern "C" size_t dr_span_workspace_size(int64_t n, int P) {
-  if (n <= dr::kSpanMaxN || n > dr::kSpanLargeMaxN || P < 1) return 0;
-  return dr::span_large_workspace(n, P);
+  if (n <= dr::kSpanMaxN || n > dr::kSpanLargeMaxN) return 0;
+  return dr::span_large_workspace(n, P > 1 ? P : 1);
 }
 
 extern "C" size_t dr_cone_workspace_size(int64_t n, int P) {
