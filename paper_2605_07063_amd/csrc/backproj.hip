@@ -366,12 +366,13 @@ __global__ __launch_bounds__(256, 2) void bp_mfma_kernel(BpArgs g, int per) {
 extern "C" size_t dr_backproject_workspace_size(const dr_layer* layers, int num_layers) {
   if (!layers || num_layers < 1) return 0;
   // one launch holds up to 16 layers: room for the largest such run of T blocks
+  // (aligned bf16 projectors leave it unused: their kernel keeps T in LDS)
   size_t best = 256;
   for (int f = 0; f < num_layers; f += dr::kBpLayers) {
     size_t o = 0;
     for (int l = f; l < num_layers && l < f + dr::kBpLayers; ++l)
       o = dr::align_up(o + (size_t)(layers[l].k_out > 0 ? layers[l].k_out : 0) *
-                               (size_t)(layers[l].d_in > 0 ? layers[l].d_in : 0) * 6, 256);
+                               (size_t)(layers[l].d_in > 0 ? layers[l].d_in : 0) * sizeof(float), 256);
     best = o > best ? o : best;
   }
   return best;
@@ -405,7 +406,7 @@ extern "C" dr_status dr_back_project(const dr_layer* layers, int num_layers, dr_
       g.p_out[j] = L.p_out;
       g.x[j] = u + L.col_offset;
       g.T[j] = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + o);
-      o = align_up(o + (size_t)L.k_out * (size_t)L.d_in * 6, 256);   // fp32 T or three bf16 planes
+      o = align_up(o + (size_t)L.k_out * (size_t)L.d_in * sizeof(float), 256);
       mfma = mfma && L.d_in % 8 == 0 && L.d_out % 8 == 0 && aligned16(L.p_out);
       g.U[j] = U + u_offset[f + j];
       g.k_in[j] = (int)L.k_in;

@@ -222,24 +222,12 @@ __global__ __launch_bounds__(kThreads, 2) void gram_tile_kernel(GramArgs a) {
 // goes out in non-temporal float4 stores.  The mirror is the accumulator as
 // it stands (four consecutive rows of one column are four consecutive
 // columns of the transposed row); the block itself after a 4 x 4 transpose
-// inside each quad of lanes (two rounds of DPP quad permutations).
+// inside each quad of lanes.
 __device__ __forceinline__ void big_store_block_fast(float* Kp, int n, int R, int C, f32x4 v, int lane) {
   const int lr = lane & 15, lg = lane >> 4, c = lane & 3, m = lr >> 2;
   __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(Kp + (long long)(C + lr) * n + R + 4 * lg));
-  float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
-  {  // exchange across bit 0 of the quad lane
-    const float s01 = (c & 1) ? x0 : x1, s23 = (c & 1) ? x2 : x3;
-    const float r01 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s01), 0xB1, 0xF, 0xF, false));
-    const float r23 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s23), 0xB1, 0xF, 0xF, false));
-    if (c & 1) { x0 = r01; x2 = r23; } else { x1 = r01; x3 = r23; }
-  }
-  {  // exchange across bit 1
-    const float s02 = (c & 2) ? x0 : x2, s13 = (c & 2) ? x1 : x3;
-    const float r02 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s02), 0x4E, 0xF, 0xF, false));
-    const float r13 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s13), 0x4E, 0xF, 0xF, false));
-    if (c & 2) { x0 = r02; x1 = r13; } else { x2 = r02; x3 = r13; }
-  }
-  __builtin_nontemporal_store(f32x4{x0, x1, x2, x3}, reinterpret_cast<f32x4*>(Kp + (long long)(R + 4 * lg + c) * n + C + 4 * m));
+  __builtin_nontemporal_store(quad_transpose(v),
+                              reinterpret_cast<f32x4*>(Kp + (long long)(R + 4 * lg + c) * n + C + 4 * m));
 }
 
 // fp32 rows, n + 1 > 128, where the 256-row tiles below would leave the chip
