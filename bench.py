@@ -279,12 +279,13 @@ def run_llama(args, api, _lib, workloads, dev, peaks):
             measured_peak=peaks.get("hbm_read_GBs") if peaks else None, traffic=traffic,
             algorithmic_bytes=by, avg_launch_ms=avg_blk, timed_calls=int(blk_ms.size)),
         # fp32 rows, (n(n+1) + 2n + 2 + m) kappa flops on 4 (n + m) kappa bytes:
-        # about 61 flops per byte, above the fp32 MFMA ridge (157.3 / 8), so
-        # the Gram is priced against the fp32 MFMA peak (its fp32 products run
-        # as six bf16 MFMA products of split values)
-        "gram_roofline": _roofline("dr_gram (fp32 rows: gram_split_kernel + gram_reduce_kernel)", "mfma",
-                                   _gram_f32_flops(n, m, ktot), stage["gram"], F32_MFMA_PEAK_TFLOPS, "TFLOP/s",
-                                   measured_peak=peaks.get("fp32_mfma_TFLOPs") if peaks else None,
+        # about 61 flops per byte.  Each fp32 product runs as six bf16 MFMA
+        # products of split values, so the Gram is priced at six times its
+        # flops against the bf16 MFMA peak
+        "gram_roofline": _roofline("dr_gram (fp32 rows: gram_split_kernel + gram_reduce_kernel, six bf16 products "
+                                   "per fp32 one)", "mfma", 6.0 * _gram_f32_flops(n, m, ktot), stage["gram"],
+                                   BF16_MFMA_PEAK_TFLOPS, "TFLOP/s",
+                                   measured_peak=peaks.get("bf16_mfma_TFLOPs") if peaks else None,
                                    algorithmic_flops=_gram_f32_flops(n, m, ktot), algorithmic_bytes=N * ktot * 4.0),
         "span_info": int(info[0]),
     }
@@ -329,8 +330,9 @@ def run_layerwise(api, _lib, st, dev):
         "nonzero_info_groups": bad,
         "span_roofline": _roofline("dr_project_span, 224 groups at n = 256 (span_small_kernel, one workgroup per "
                                    "group)", "hbm", kb, span_ms, HBM_PEAK_GBS, "GB/s", algorithmic_bytes=kb),
-        "gram_roofline": _roofline("dr_gram, 224 groups (fp32 rows)", "mfma", _gram_f32_flops(n, m, ktot), gram_ms,
-                                   F32_MFMA_PEAK_TFLOPS, "TFLOP/s", algorithmic_flops=_gram_f32_flops(n, m, ktot),
+        "gram_roofline": _roofline("dr_gram, 224 groups (fp32 rows, six bf16 products per fp32 one)", "mfma",
+                                   6.0 * _gram_f32_flops(n, m, ktot), gram_ms, BF16_MFMA_PEAK_TFLOPS, "TFLOP/s",
+                                   algorithmic_flops=_gram_f32_flops(n, m, ktot),
                                    algorithmic_bytes=(st["n"] + st["m"]) * ktot * 4.0),
     }
 
@@ -792,16 +794,17 @@ def time_next_rows(api, layers, lens, n, T, wt, wc, goff, dev, K=None, s=None, r
     res = {}
     for name, w in (("update_topk", wt), ("update_cone", wc)):
         wh = w.cpu().numpy()
-        flops = 0.0
+        flops, equal = 0.0, True
         for li, L in enumerate(layers):
             row = 0 if P == 1 else li
+            equal = equal and len(set(wh[row][wh[row] != 0].tolist())) <= 1
             flops += 2.0 * float(lh[wh[row] != 0].sum()) * L["x"].shape[2] * L["dy"].shape[2]
         ms = _event_ms(lambda: api.dr_assemble_update(ul, n, T, lens, w, U, offs, group_of_layer=gol,
                                                        workspace=ws), reps)
         res[name] = {"ms": ms, "examples": int((wh != 0).any(axis=0).sum()),
-                     "roofline": _roofline("dr_assemble_update (update_plan_kernel + update_sort_kernel + "
-                                           "update_bf16_kernel)", "mfma", flops, ms, BF16_MFMA_PEAK_TFLOPS,
-                                           "TFLOP/s", algorithmic_flops=flops)}
+                     "roofline": _roofline("dr_assemble_update (update_list_kernel + " +
+                                           ("update_tile_kernel)" if equal else "update_bf16_kernel)"), "mfma",
+                                           flops, ms, BF16_MFMA_PEAK_TFLOPS, "TFLOP/s", algorithmic_flops=flops)}
     if K is not None:
         P, nn = s.shape
         idx = torch.empty(P, nn, dtype=torch.int32, device=dev)

@@ -155,11 +155,12 @@ size_t dr_sketch_workspace_size(const dr_layer* layers, int num_layers, int64_t 
  *                             DR_BF16), n >= 0, m >= 1, ld >= goff[P].
  *   goff  (host) int64 [P+1], 0 <= goff[0] <= ... <= goff[P], P >= 1.
  *   K     fp32 [P][n][n], both triangles written.  s fp32 [P][n].  t2 fp32 [P].
- * Arithmetic: fp32 inputs -> fp32 products with fp32 accumulation (n < 128:
- * fp32 MFMA; n >= 128: each value as three bf16 parts, which hold it to
- * 2^-25, and each product as six bf16 MFMA products, exact in fp32; fp32 MFMA
- * from the first columns on that hold a value of 2^50 or more, or a nonzero one
- * below 2^-109); bf16 inputs -> bf16 MFMA with fp32 accumulation.
+ * Arithmetic: fp32 inputs -> fp32 products with fp32 accumulation, chunks of
+ * columns summed in fp64: on fp32 MFMA for n < 128 and wherever that is faster,
+ * else with each value as three bf16 parts, which hold it to 2^-25, and each
+ * product as six bf16 MFMA products, exact in fp32 (and on fp32 MFMA from the
+ * first columns on that hold a value of 2^50 or more, or a nonzero one below
+ * 2^-109); bf16 inputs -> bf16 MFMA with fp32 accumulation.
  * Requirements: ldG, ldGt and every goff[p] multiples of 4 (f32) or 8 (bf16);
  * G and Gt 16-byte aligned.
  * ------------------------------------------------------------------------- */
@@ -211,6 +212,10 @@ dr_status dr_gram_noalloc(const void* G, int64_t n, int64_t ldG, const void* Gt,
  * takes one step.  When two steps do not get there (the corrections do not
  * shrink fast enough, which happens when cond(K + lam_eff I) * 2^-24 is not
  * small), info = DR_INFO_NOT_CONVERGED and w holds the last iterate.
+ *   workspace: none for n <= 256.  Above, at least one group's,
+ *   dr_span_workspace_size(n, 1); dr_span_workspace_size(n, P) holds as many
+ *   groups as run side by side (n <= 4096: up to P, within 1 GiB), which is
+ *   faster.
  * ------------------------------------------------------------------------- */
 dr_status dr_project_span(const float* K, const float* s, const float* t2, int64_t n, int P,
                           float lambda, dr_ridge_mode mode, float* w, float* lam_eff,
@@ -378,7 +383,11 @@ size_t dr_combine_workspace_size(int64_t n, const int64_t* goff, int P);
  *               row-major [d_out][d_in].  Blocks must not overlap.  Every
  *               element of every block is written (zeros if no example has a
  *               non-zero weight).
- *   workspace   at least dr_update_workspace_size() bytes.
+ *   workspace   at least dr_update_workspace_size() bytes.  For DR_BF16 it
+ *               grows with n * T: 128 bytes per layer, example and 32 tokens
+ *               of T, for the token tables that the kernel for equal weights
+ *               needs.  Where these would pass 256 MiB they are left out, and
+ *               equal weights run at the speed of different ones.
  * Requirements (else DR_ERR_ARG): d_in, d_out, ldx, lddy multiples of 8
  *   (bf16) or 4 (f32); x, dy 16-byte aligned.  One example's rows must span
  *   less than 4 GiB (T * ld * element size), else DR_ERR_UNSUPPORTED.
