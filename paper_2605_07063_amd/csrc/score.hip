@@ -5,7 +5,8 @@
 //           inner product with gbar* (update-assembly kernel in score mode,
 //           update.hip);
 //   PIP     sum_t dy_{i,t}^T gbar* x_{i,t}: a GEMM of the example's token
-//           rows with gbar* followed by a dot with the dy rows (pip_kernel);
+//           rows with gbar* followed by a dot with the dy rows (pip_kernel;
+//           pip_small_kernel for calls of few tiles);
 //   GIP     (1/m) sum_j <D_i D*_j^T, X_i X*_j^T>: the two T x T token
 //           cross-correlations of every (example, target) pair, multiplied
 //           elementwise and summed (gip_kernel).

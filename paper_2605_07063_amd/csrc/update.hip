@@ -12,9 +12,10 @@
 //                        ties) by ranking every entry against all others.
 //   update_steps_kernel  whether the weights of a list are all equal, and if
 //                        so its token steps.
-//   update_tile_kernel   lists of equal weights (top-k, a mean): one 256 x 256
-//                        tile of U per workgroup, 4 waves of 128 x 128, the
-//                        examples' tokens one after another.
+//   update_list_kernel   the three above in one, for at most 1024 examples.
+//   update_tile_kernel   lists of equal weights (top-k, a mean) of larger
+//                        calls: one 256 x 256 tile of U per workgroup, 4 waves
+//                        of 128 x 128, the examples' tokens one after another.
 //   update_bf16_kernel   other lists (and the Direct scorer): the same tile on
 //                        8 waves of 128 (d_out) x 64 (d_in), example by
 //                        example, tokens through a 2-stage LDS ring in steps of
@@ -631,7 +632,8 @@ __global__ __launch_bounds__(kBThreads) void update_bf16_kernel(UpdArgs a) {
 // block, top-32 of 64 (8 layers 2048 x 2048, 0.69 TFLOP): 0.86 ms on eight
 // waves of 128 x 64 in steps of 64 tokens padded per example (their fragment
 // reads waited for all DMA, and read half as much again per product), 0.71 ms
-// here (MFMA busy 52 % at 1.9 GHz; 0.51 without any DMA, 0.61 with every read an
+// here on the benchmark's inputs (0.59 to 0.61 on others of the same size, which
+// is not explained; MFMA busy 52 % at 1.9 GHz; 0.51 without any DMA, 0.61 with every read an
 // L2 hit), 0.73 with two stages of 64 tokens.  (Several weights would need
 // the accumulators rescaled between steps, which makes the compiler spill them.)
 constexpr int kUStage = 2 * kUK * 512;   // dy rows, then x rows
